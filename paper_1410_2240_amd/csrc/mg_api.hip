@@ -107,6 +107,7 @@ struct mg_ctx {
   bool own_stream = false;              // a lane: `stream` was created by the library
   hipEvent_t order_event = nullptr;     // joins this context's stream with the caller's
   int device = 0;                       // a lane: the device its stream belongs to
+  int sharing = 1;   // right-hand sides being solved at once, this context's own among them
 
   View<double> v64(int l) const {
     const Level& a = lv[l];
@@ -144,7 +145,7 @@ long long cells(const Level& a) { return static_cast<long long>(a.n) * a.n * a.n
 // anything; half-sweep grids still need it zeroed).  first_done: the first sweep
 // (p -> second buffer) has already been queued (see first_sweep), so start from its output.
 // Grids whose sweeps run two to a pass: the density form (the finest grid of a context
-// set up from rho, in its FP64 cycles and in a mixed context's FP32 cycles), 256^3 and up.
+// set up from rho, in its FP64 cycles and in a mixed context's FP32 cycles), 128^3 and up.
 template <typename T>
 bool two_sweep_grid(const mg_ctx* c, int l) {
   return c->view<T>(l).rt != nullptr && mg::fused2_supported(c->lv[l].q);
@@ -162,7 +163,7 @@ hipError_t launch_two_sweeps(const mg_ctx* c, int l, const T* pin, T* pout, cons
                              bool zero_in, const ZwSums* zw = nullptr) {
   const Level& a = c->lv[l];
   return mg::launch_rbgs_fused2(pin, pout, f, c->view<T>(l).rt, a.q, a.h, order, fshift, zero_in ? 1 : 0, c->stream,
-                                zw ? &zw->x : nullptr, zw ? zw->nblocks : nullptr);
+                                c->sharing, zw ? &zw->x : nullptr, zw ? zw->nblocks : nullptr);
 }
 
 template <typename T>
@@ -433,7 +434,9 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
     };
     // FP64 preconditioning on a two-sweep finest grid: z.w comes out of its last pass,
     // and, where the workspace holds a second residual, the residual update out of its first
-    const bool zw_fused = !mixed && two_sweep_grid<double>(c, 0) && a.n > mg::kCoarseCycleMaxN;
+    // (256^3 and up: at 128^3 the separate passes take 18 us of a 250 us step, and a setup
+    // from rho keeps the bits of one from face arrays)
+    const bool zw_fused = !mixed && two_sweep_grid<double>(c, 0) && a.n >= 256;
     const bool ru_fused = zw_fused && c->kr2 != nullptr;
     double* kr_other = c->kr2;
     auto precondition_first_sweep = [&]() -> int {
@@ -904,6 +907,8 @@ int solve_lanes(mg_ctx* ctx, const double* f, double* p, int batch, double tol, 
   const long long n3 = cells(ctx->lv[0]);
   MG_HIP(hipEventRecord(ctx->order_event, ctx->stream));
   for (int w = 1; w < W; ++w) MG_HIP(hipStreamWaitEvent(ctx->lanes[w - 1]->stream, ctx->order_event, 0));
+  ctx->sharing = W;
+  for (int w = 1; w < W; ++w) ctx->lanes[w - 1]->sharing = W;
   std::vector<std::thread> threads;
   std::vector<int> unthreaded;   // lanes whose thread could not be started
   for (int w = 1; w < W; ++w) {
@@ -916,6 +921,7 @@ int solve_lanes(mg_ctx* ctx, const double* f, double* p, int batch, double tol, 
   run_lane(ctx, 0, W, f, p, batch, n3, tol, max_cycles, hist, &res);
   for (int w : unthreaded) run_lane(ctx->lanes[w - 1], w, W, f, p, batch, n3, tol, max_cycles, hist, &res);
   for (auto& t : threads) t.join();
+  ctx->sharing = 1;   // (the lanes run only from here, where it is set)
   int rc = MG_OK;
   for (int w = 1; w < W; ++w) {
     mg_ctx* lane = ctx->lanes[w - 1];

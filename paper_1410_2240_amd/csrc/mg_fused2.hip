@@ -41,6 +41,7 @@
 // (pre-smoothing from zero, f = r) forms the residual update r - alpha w where it reads
 // f, sweeps with it, writes it out of place and sums its squares; the last
 // (post-smoothing, writing z) sums z.w.  Each sum is one partial per workgroup.
+#include <algorithm>
 #include <type_traits>
 
 #include "mg_buffer.h"
@@ -421,11 +422,16 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
 
 }  // namespace
 
-int fused2_supported(int q) { return (1 << q) >= 256; }
+// Below 128^3 a plane holds too few tiles to give every compute unit a chunk of the least
+// length (8 planes, entered six early).  At 128^3 (8-plane chunks, 256 FP64 or 128 FP32
+// workgroups) four sweeps take 69.8 us in FP64 and 62.8 us in FP32 in two passes, against
+// 102.6 and 69.4 us in four one-pass sweeps.
+int fused2_supported(int q) { return (1 << q) >= 128; }
 
 template <typename T>
 hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, int q, double h, int order,
-                              const double* fshift, int zero_in, hipStream_t s, const Fused2Extra* x, int* nblocks) {
+                              const double* fshift, int zero_in, hipStream_t s, int sharing, const Fused2Extra* x,
+                              int* nblocks) {
   constexpr int TX = Shape<T>::TX, TY = Shape<T>::TY;
   const int n = 1 << q;
   if (!fused2_supported(q) || !rt || pin == pout) return hipErrorInvalidValue;
@@ -434,9 +440,15 @@ hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, in
   if (wx && zero_in && (!x->rnew || static_cast<const void*>(x->rnew) == static_cast<const void*>(f) || !x->s_dr || !x->s_dw || !x->s_alpha || fshift))
     return hipErrorInvalidValue;
   const long long tiles = static_cast<long long>(n / TX) * (n / TY);
-  // z-chunks as long as possible while every compute unit still gets a workgroup
+  // z-chunks as long as possible while every compute unit still gets a workgroup, over all
+  // the right-hand sides solved at once (down to a quarter of the chip for each): a chunk
+  // repeats six planes of the one below, so longer chunks are less work in all.  Eight
+  // 128^3 solves and their adjoints, four at once: 26.6 ms at 128 workgroups a pass and
+  // 25.8 ms at 64, against 30.1 ms at 256 (one 128^3 solve alone: 7.80, 9.31 and 7.16 ms).
+  // A pass with sums keeps its chunks: their order is that of the workgroups.
+  const int want = wx ? 256 : std::max(256 / std::max(sharing, 1), 64);
   int kc = n;
-  while (kc > 8 && tiles * (n / kc) < 256) kc /= 2;
+  while (kc > 8 && tiles * (n / kc) < want) kc /= 2;
   const long long blocks = tiles * (n / kc);
   if (wx && blocks > kNumPartials) return hipErrorInvalidValue;
   const T h2 = static_cast<T>(h * h);
@@ -464,8 +476,8 @@ hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, in
 }
 
 template hipError_t launch_rbgs_fused2<float>(const float*, float*, const float*, const float*, int, double, int,
-                                              const double*, int, hipStream_t, const Fused2Extra*, int*);
+                                              const double*, int, hipStream_t, int, const Fused2Extra*, int*);
 template hipError_t launch_rbgs_fused2<double>(const double*, double*, const double*, const double*, int, double, int,
-                                               const double*, int, hipStream_t, const Fused2Extra*, int*);
+                                               const double*, int, hipStream_t, int, const Fused2Extra*, int*);
 
 }  // namespace mg
