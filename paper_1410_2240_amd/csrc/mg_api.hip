@@ -137,13 +137,25 @@ long long cells(const Level& a) { return static_cast<long long>(a.n) * a.n * a.n
 
 // ---------------------------------------------------------------- V-cycle (T = double/float)
 
-// `sweeps` red-black sweeps of A p = f on level l.  Grids of 64^3 and up use the one-pass
-// fused sweep (32^3 and 64^3 grids with face arrays the block-per-workgroup sweep), which
-// alternates p with the level's second buffer; an odd count ends with a copy back.
-// Smaller grids use two in-place half-sweeps per sweep.  zero_in: p is known to
-// be zero, so the first one-pass sweep does not read it (p's memory may then hold
+// `sweeps` red-black sweeps of A p = f on level l.  Grids of 128^3 and up use the one-pass
+// and two-pass fused sweeps, 32^3 and 64^3 grids the block-per-workgroup sweep; these
+// alternate p with the level's second buffer, and an odd count of passes ends with a copy
+// back.  Smaller grids use two in-place half-sweeps per sweep.  zero_in: p is known to
+// be zero, so the first out-of-place sweep does not read it (p's memory may then hold
 // anything; half-sweep grids still need it zeroed).  first_done: the first sweep
 // (p -> second buffer) has already been queued (see first_sweep), so start from its output.
+bool out_of_place_sweeps(int q) { return mg::fused_sweep_supported(q) || mg::box_sweep_supported(q); }
+
+// The density form a block sweep of level l reads, or null: it reads the face arrays.
+// FP32 cycles of a hierarchy with an FP32 density have no other form; FP64 has both, and
+// reads the density at 64^3 (a V-cycle in 85.5 us, 88.0 us from face arrays) but not at
+// 32^3, where 64 workgroups leave the faces' reciprocals exposed (50.7 and 48.6 us).
+template <typename T>
+const T* box_rt(const mg_ctx* c, int l) {
+  if constexpr (sizeof(T) == 8) return c->lv[l].q == 6 ? c->view<T>(l).rt : nullptr;
+  return c->view<T>(l).rt;
+}
+
 // Grids whose sweeps run two to a pass: the density form (the finest grid of a context
 // set up from rho, in its FP64 cycles and in a mixed context's FP32 cycles), 128^3 and up.
 template <typename T>
@@ -171,8 +183,8 @@ int smooth(mg_ctx* c, int l, T* p, const T* f, const double* fshift, int sweeps,
            bool first_done = false) {
   const Level& a = c->lv[l];
   const View<T> v = c->view<T>(l);
-  const bool box = !v.rt && mg::box_sweep_supported(a.q);   // 32^3 and 64^3 from face arrays
-  if (mg::fused_sweep_supported(a.q) || box) {
+  const bool box = mg::box_sweep_supported(a.q);
+  if (out_of_place_sweeps(a.q)) {
     T* src = first_done ? v.t : p;
     T* dst = first_done ? p : v.t;
     const bool two = two_sweep_grid<T>(c, l);
@@ -187,8 +199,8 @@ int smooth(mg_ctx* c, int l, T* p, const T* f, const double* fshift, int sweeps,
     }
     for (; s < sweeps; ++s) {
       if (box)
-        MG_HIP(mg::launch_rbgs_box<T>(src, dst, f, v.bx, v.by, v.bz, a.q, a.h, order, fshift, zero_in && s == 0,
-                                      c->stream));
+        MG_HIP(mg::launch_rbgs_box<T>(src, dst, f, v.bx, v.by, v.bz, box_rt<T>(c, l), a.q, a.h, order, fshift,
+                                      zero_in && s == 0, c->stream));
       else
         MG_HIP(mg::launch_rbgs_fused<T>(src, dst, f, v.bx, v.by, v.bz, v.rt, a.q, a.h, order, fshift,
                                         zero_in && s == 0, c->stream));
@@ -220,7 +232,7 @@ int residual_restrict(mg_ctx* c, int l, const T* p, const T* f, const double* fs
   return MG_OK;
 }
 
-// The first pre-smoothing sweep of a finest-grid cycle on a one-pass-swept grid: it
+// The first pre-smoothing sweep of a finest-grid cycle on a grid swept out of place: it
 // writes only the grid's second buffer (p is read, or not at all with zero_in), so it can
 // be queued before the host has read the convergence check, and the cycle then starts
 // from its output (vcycle with first_done); if the check ends the solve, it is discarded.
@@ -233,7 +245,11 @@ int first_sweep(mg_ctx* c, T* p, const T* f, const double* fshift, bool zero_in)
     MG_HIP(launch_two_sweeps<T>(c, 0, p, v.t, f, fshift, MG_PRE, zero_in));
     return MG_OK;
   }
-  MG_HIP(mg::launch_rbgs_fused<T>(p, v.t, f, v.bx, v.by, v.bz, v.rt, a.q, a.h, MG_PRE, fshift, zero_in, c->stream));
+  if (mg::box_sweep_supported(a.q))
+    MG_HIP(mg::launch_rbgs_box<T>(p, v.t, f, v.bx, v.by, v.bz, box_rt<T>(c, 0), a.q, a.h, MG_PRE, fshift, zero_in,
+                                  c->stream));
+  else
+    MG_HIP(mg::launch_rbgs_fused<T>(p, v.t, f, v.bx, v.by, v.bz, v.rt, a.q, a.h, MG_PRE, fshift, zero_in, c->stream));
   return MG_OK;
 }
 
@@ -279,18 +295,18 @@ int vcycle(mg_ctx* c, int l, T* p, const T* f, const double* fshift, bool zero_i
   if (zw) return fail(MG_EINVAL, "z.w sums asked of a grid that does not sweep two to a pass");
   const Level& a = c->lv[l];
   const View<T> v = c->view<T>(l);
-  if (!v.rt && mg::box_sweep_supported(a.q)) {
-    // 32^3 and 64^3 from face arrays, four launches: pre-smoothing p -> t -> p, the second
-    // sweep also restricting its residual; post-smoothing from p plus the prolongated
-    // correction -> t -> p
+  if (mg::box_sweep_supported(a.q)) {
+    // 32^3 and 64^3, four launches: pre-smoothing p -> t -> p, the second sweep also
+    // restricting its residual; post-smoothing from p plus the prolongated correction -> t -> p
+    const T* rt = box_rt<T>(c, l);
     if (!first_done)
-      MG_HIP(mg::launch_rbgs_box<T>(p, v.t, f, v.bx, v.by, v.bz, a.q, a.h, MG_PRE, fshift, zero_in, c->stream));
-    MG_HIP(mg::launch_rbgs_box_restrict<T>(v.t, p, f, v.bx, v.by, v.bz, a.q, a.h, MG_PRE, fshift, next.f, next.e,
+      MG_HIP(mg::launch_rbgs_box<T>(p, v.t, f, v.bx, v.by, v.bz, rt, a.q, a.h, MG_PRE, fshift, zero_in, c->stream));
+    MG_HIP(mg::launch_rbgs_box_restrict<T>(v.t, p, f, v.bx, v.by, v.bz, rt, a.q, a.h, MG_PRE, fshift, next.f, next.e,
                                            c->stream));
     MG_TRY(vcycle<T>(c, l + 1, next.e, next.f, nullptr, true));
-    MG_HIP(mg::launch_rbgs_box_prolong<T>(p, v.t, f, v.bx, v.by, v.bz, a.q, a.h, MG_POST, fshift, next.e, a.mask,
+    MG_HIP(mg::launch_rbgs_box_prolong<T>(p, v.t, f, v.bx, v.by, v.bz, rt, a.q, a.h, MG_POST, fshift, next.e, a.mask,
                                           c->stream));
-    MG_HIP(mg::launch_rbgs_box<T>(v.t, p, f, v.bx, v.by, v.bz, a.q, a.h, MG_POST, fshift, 0, c->stream));
+    MG_HIP(mg::launch_rbgs_box<T>(v.t, p, f, v.bx, v.by, v.bz, rt, a.q, a.h, MG_POST, fshift, 0, c->stream));
     return MG_OK;
   }
   MG_TRY(smooth<T>(c, l, p, f, fshift, 2, MG_PRE, zero_in, first_done));
@@ -371,14 +387,14 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
   // the residual pass also leaves the FP32 copy of r that the next FP32 cycle solves for
   float* r32 = mixed ? a.f32 : nullptr;
   float* e32 = mixed ? a.e32 : nullptr;
-  // corrections enter their cycle as zero; a one-pass-swept finest grid does not read
+  // corrections enter their cycle as zero; a finest grid swept out of place does not read
   // them, so the passes before the cycle need not clear them
-  const bool zin = mg::fused_sweep_supported(a.q);
+  const bool zin = out_of_place_sweeps(a.q);
   float* e32_zero = zin ? nullptr : e32;
   MG_TRY(residual_norm(c, p, f, fshift, r32, e32_zero));
   // The next cycle's first finest-grid sweep is queued before each convergence check is
   // read back (first_sweep), so the GPU does not idle while the host decides.
-  const bool spec = mg::fused_sweep_supported(a.q) && a.n > mg::kCoarseCycleMaxN;
+  const bool spec = zin;
   const bool krylov = (c->flags & MG_KRYLOV) != 0;
   auto cycle_first_sweep = [&]() -> int {
     if (mixed) return first_sweep<float>(c, e32, r32, nullptr, true);
@@ -542,7 +558,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
   // Mixed refinement on a density-form finest grid: the FP64 update p + e and the next
   // residual in one pass, p alternating with the finest grid's second FP64 buffer (free
   // while the cycles run in FP32); the last iterate is copied back into p below.  Only
-  // where the pass need not also clear e32 (one-pass-swept grids), since it reads e32.
+  // where the pass need not also clear e32 (grids swept out of place), since it reads e32.
   const bool fuse_update = mixed && a.rt && mg::march_supported(a.q) && e32_zero == nullptr;
   double* cur = p;
   while (!(c->flags & MG_KRYLOV) && std::isfinite(r) && r > tol && *cycles < max_cycles) {
@@ -756,9 +772,9 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
   }
   if (rho) {
     if (plan.lv[0].rt32 != mg::kAbsent) {
-      // the FP32 cycles form their finest faces from an FP32 copy (one-pass sweep grids,
+      // the FP32 cycles form their finest faces from an FP32 copy (grids swept out of place,
       // so that smoother and residual use the same FP32 operator)
-      if (!mg::fused_sweep_supported(f0.q)) return cleanup(fail(MG_EINVAL, "internal: FP32 density copy below 64^3"));
+      if (!out_of_place_sweeps(f0.q)) return cleanup(fail(MG_EINVAL, "internal: FP32 density copy below 64^3"));
       f0.rt32 = at<float>(c->ws, plan.lv[0].rt32);
       hip(mg::launch_to_f32(f0.rt, f0.rt32, cells(f0), s), "to_f32(rt)");
     }

@@ -1,5 +1,5 @@
-// One red-black Gauss-Seidel sweep of a small grid (32^3 and 64^3, face arrays) in a
-// single launch (CDNA4).
+// One red-black Gauss-Seidel sweep of a small grid (32^3 and 64^3, from face arrays or the
+// density form) in a single launch (CDNA4).
 //
 // On grids this small a sweep costs latency, not bytes: two half-sweep launches, or a
 // z-march whose steps each wait for a load, take several microseconds for a few
@@ -12,6 +12,10 @@
 // (p_in -> p_out), since workgroups read halo cells that others write.  The update is
 // that of the one-pass z-marching sweep (the same fused multiply-adds in the same order
 // and the same quotient), so both give the same bits.
+//
+// Finest grids set up from rho are swept here too: four sweeps at 64^3 take 29.8 us (FP64)
+// and 24.7 us (FP32), 51.8 and 42.4 us in one-pass z-marches; at 32^3 18.0 us, 30.5 us in
+// half-sweep launches.
 //
 // Two variants take the launches around a V-cycle's coarse correction (section 3.1's
 // cycle: smooth, restrict the residual, correct from the grid below, smooth).  The
@@ -126,7 +130,10 @@ struct BoxExtra {
   T inv_h2;
 };
 
-template <typename T, int MODE, bool ZIN>
+// RHO: bx is the density form of the finest grid (by, bz unused).  It is staged like p, and
+// each update forms its six faces from LDS, so a cell costs one load of f besides its share
+// of the box.
+template <typename T, int MODE, bool ZIN, bool RHO>
 __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* __restrict__ pout,
                                                   const T* __restrict__ f, const T* __restrict__ bx,
                                                   const T* __restrict__ by, const T* __restrict__ bz, int q, T h2,
@@ -136,6 +143,7 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
   constexpr int kPerS = (G::Cells + kBT - 1) / kBT, kPer1 = (G::N1 + kBT - 1) / kBT, kPer2 = (G::N2 + kBT - 1) / kBT;
   // box cell (x, y, z) is grid cell (i0 - H + x, j0 - H + y, k0 - H + z), at (z E + y) E + x
   __shared__ T P[G::Cells];
+  __shared__ T R[RHO ? G::Cells : 1];
   // restrict: the block's residuals; prolong: the coarse correction around the box (8^3)
   __shared__ T X[MODE == kBoxPlain ? 1 : 2 * kBT];
   const int n = 1 << q, nb = n / kBB;
@@ -143,11 +151,32 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
   const int i0 = (b % nb) * kBB, j0 = ((b / nb) % nb) * kBB, k0 = (b / (nb * nb)) * kBB;
   const T fs = fshift ? static_cast<T>(*fshift) : T(0);
   const Rsrc rp = whole_rsrc(pin, q), rf = whole_rsrc(f, q);
-  const Rsrc rx = whole_rsrc(bx, q), ry = whole_rsrc(by, q), rz = whole_rsrc(bz, q);
+  const Rsrc rx = whole_rsrc(bx, q), ry = whole_rsrc(RHO ? bx : by, q), rz = whole_rsrc(RHO ? bx : bz, q);
+  auto coef = [&](int i, int j, int k) {
+    if constexpr (RHO) {
+      BoxCoef<T> C{};
+      C.f = ld1(rf, off3<T>(i, j, k, q), T());
+      return C;
+    } else {
+      return load_coef<T>(rf, rx, ry, rz, i, j, k, q);
+    }
+  };
+  // the faces of box cell c (density form)
+  auto faces = [&](int c, BoxCoef<T>& C) {
+    if constexpr (RHO) {
+      const T rc = R[c];
+      C.xm = face_beta(R[c - 1], rc);
+      C.xp = face_beta(rc, R[c + 1]);
+      C.ym = face_beta(R[c - E], rc);
+      C.yp = face_beta(rc, R[c + E]);
+      C.zm = face_beta(R[c - E * E], rc);
+      C.zp = face_beta(rc, R[c + E * E]);
+    }
+  };
 
   // ---- one round of loads: the box of p, the coefficients of every cell this thread
   // updates (and, restricting, of its block cells), the coarse correction (prolonging)
-  T sv[kPerS];
+  T sv[kPerS], rv[RHO ? kPerS : 1];
   bool live[kPerS];   // prolong: an active cell inside the grid
 #pragma unroll
   for (int u = 0; u < kPerS; ++u) {
@@ -155,6 +184,10 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
     const int x = e % E, y = (e / E) % E, z = e / (E * E);
     const int gi = i0 - H + x, gj = j0 - H + y, gk = k0 - H + z;
     sv[u] = (ZIN || e >= G::Cells) ? T(0) : ld1(rp, off3<T>(gi, gj, gk, q), T());
+    if constexpr (RHO) {
+      const T inf = __builtin_huge_val();   // beyond a z wall
+      rv[u] = (e < G::Cells && gk >= 0 && gk < n) ? ld1(rx, off3<T>(gi, gj, gk, q), T()) : inf;
+    }
     live[u] = false;
     if constexpr (MODE == kBoxProlong) {
       if (e < G::Cells && gk >= 0 && gk < n) live[u] = xa.mask[off3<uint8_t>(gi, gj, gk, q)] != 0;
@@ -183,7 +216,7 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
       const int gi0 = i0 - (H - 1), gy = j0 - (H - 1) + yy, gz = k0 - (H - 1) + zz;
       const int lx = 2 * xh + ((first + gi0 + gy + gz) & 1);   // colour: parity of i + j + k
       l1[u] = ((zz + 1) * E + (yy + 1)) * E + (lx + 1);
-      c1[u] = load_coef<T>(rf, rx, ry, rz, gi0 + lx, gy, gz, q);
+      c1[u] = coef(gi0 + lx, gy, gz);
     }
   }
   BoxCoef<T> c2[kPer2];
@@ -198,7 +231,7 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
       const int gi0 = i0 - (H - 2), gy = j0 - (H - 2) + yy, gz = k0 - (H - 2) + zz;
       const int lx = 2 * xh + ((1 - first + gi0 + gy + gz) & 1);
       l2[u] = ((zz + 2) * E + (yy + 2)) * E + (lx + 2);
-      c2[u] = load_coef<T>(rf, rx, ry, rz, gi0 + lx, gy, gz, q);
+      c2[u] = coef(gi0 + lx, gy, gz);
     }
   }
   BoxCoef<T> cr[2];   // restrict: block cells tid and tid + 256
@@ -206,7 +239,7 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int e = tid + u * kBT;
-      cr[u] = load_coef<T>(rf, rx, ry, rz, i0 + e % kBB, j0 + (e / kBB) % kBB, k0 + e / (kBB * kBB), q);
+      cr[u] = coef(i0 + e % kBB, j0 + (e / kBB) % kBB, k0 + e / (kBB * kBB));
     }
   }
 
@@ -238,16 +271,25 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
 #pragma unroll
   for (int u = 0; u < kPerS; ++u) {
     const int e = tid + u * kBT;
-    if (e < G::Cells) P[e] = sv[u];
+    if (e < G::Cells) {
+      P[e] = sv[u];
+      if constexpr (RHO) R[e] = rv[u];
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kPer1; ++u)
-    if (l1[u] >= 0) box_gs<T, E>(P, l1[u], c1[u], h2, fs);
+    if (l1[u] >= 0) {
+      faces(l1[u], c1[u]);
+      box_gs<T, E>(P, l1[u], c1[u], h2, fs);
+    }
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < kPer2; ++u)
-    if (l2[u] >= 0) box_gs<T, E>(P, l2[u], c2[u], h2, fs);
+    if (l2[u] >= 0) {
+      faces(l2[u], c2[u]);
+      box_gs<T, E>(P, l2[u], c2[u], h2, fs);
+    }
   __syncthreads();
   // ---- restrict: the residual of each block cell, then the mean over each coarse cell's
   // children in the order of the restriction passes: (row 2J, plane 2K), (row 2J+1, plane
@@ -257,6 +299,7 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
     for (int u = 0; u < 2; ++u) {
       const int e = tid + u * kBT;
       const int c = ((e / (kBB * kBB) + H) * E + ((e / kBB) % kBB + H)) * E + (e % kBB + H);
+      faces(c, cr[u]);
       X[e] = box_residual<T, E>(P, c, cr[u], xa.inv_h2, fs);
     }
     __syncthreads();
@@ -285,13 +328,19 @@ __global__ __launch_bounds__(kBT) void k_rbgs_box(const T* __restrict__ pin, T* 
 }
 
 template <typename T, int MODE, bool ZIN>
-hipError_t launch_box(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, int q, double h,
-                      int order, const double* fshift, const BoxExtra<T>& xa, hipStream_t s) {
+hipError_t launch_box(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt, int q,
+                      double h, int order, const double* fshift, const BoxExtra<T>& xa, hipStream_t s) {
+  if (!rt && (!bx || !by || !bz)) return hipErrorInvalidValue;
   const int nb = (1 << q) / kBB;
   const T h2 = static_cast<T>(h * h);
   const int first = order == 0 ? 0 : 1;   // pre-smoothing: red first; post-smoothing: black first
-  hipLaunchKernelGGL((k_rbgs_box<T, MODE, ZIN>), dim3(static_cast<unsigned>(nb * nb * nb)), dim3(kBT), 0, s, pin,
-                     pout, f, bx, by, bz, q, h2, first, fshift, xa);
+  const dim3 grid(static_cast<unsigned>(nb * nb * nb)), block(kBT);
+  if (rt)
+    hipLaunchKernelGGL((k_rbgs_box<T, MODE, ZIN, true>), grid, block, 0, s, pin, pout, f, rt, nullptr, nullptr, q, h2,
+                       first, fshift, xa);
+  else
+    hipLaunchKernelGGL((k_rbgs_box<T, MODE, ZIN, false>), grid, block, 0, s, pin, pout, f, bx, by, bz, q, h2, first,
+                       fshift, xa);
   return hipGetLastError();
 }
 
@@ -300,43 +349,44 @@ hipError_t launch_box(const T* pin, T* pout, const T* f, const T* bx, const T* b
 int box_sweep_supported(int q) { return q == 5 || q == 6; }
 
 template <typename T>
-hipError_t launch_rbgs_box(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, int q, double h,
-                           int order, const double* fshift, int zero_in, hipStream_t s) {
+hipError_t launch_rbgs_box(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt, int q,
+                           double h, int order, const double* fshift, int zero_in, hipStream_t s) {
   if (!box_sweep_supported(q) || pin == pout) return hipErrorInvalidValue;
   const BoxExtra<T> none{};
-  return zero_in ? launch_box<T, kBoxPlain, true>(pin, pout, f, bx, by, bz, q, h, order, fshift, none, s)
-                 : launch_box<T, kBoxPlain, false>(pin, pout, f, bx, by, bz, q, h, order, fshift, none, s);
+  return zero_in ? launch_box<T, kBoxPlain, true>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, none, s)
+                 : launch_box<T, kBoxPlain, false>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, none, s);
 }
 
 template <typename T>
-hipError_t launch_rbgs_box_restrict(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, int q,
-                                    double h, int order, const double* fshift, T* fc, T* ec, hipStream_t s) {
+hipError_t launch_rbgs_box_restrict(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz,
+                                    const T* rt, int q, double h, int order, const double* fshift, T* fc, T* ec,
+                                    hipStream_t s) {
   if (!box_sweep_supported(q) || pin == pout || !fc || !ec) return hipErrorInvalidValue;
   BoxExtra<T> xa{};
   xa.fc = fc;
   xa.ec = ec;
   xa.inv_h2 = static_cast<T>(1.0 / (h * h));
-  return launch_box<T, kBoxRestrict, false>(pin, pout, f, bx, by, bz, q, h, order, fshift, xa, s);
+  return launch_box<T, kBoxRestrict, false>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, xa, s);
 }
 
 template <typename T>
-hipError_t launch_rbgs_box_prolong(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, int q,
-                                   double h, int order, const double* fshift, const T* ec, const uint8_t* mask,
-                                   hipStream_t s) {
+hipError_t launch_rbgs_box_prolong(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz,
+                                   const T* rt, int q, double h, int order, const double* fshift, const T* ec,
+                                   const uint8_t* mask, hipStream_t s) {
   if (!box_sweep_supported(q) || pin == pout || !ec || !mask) return hipErrorInvalidValue;
   BoxExtra<T> xa{};
   xa.ecin = ec;
   xa.mask = mask;
-  return launch_box<T, kBoxProlong, false>(pin, pout, f, bx, by, bz, q, h, order, fshift, xa, s);
+  return launch_box<T, kBoxProlong, false>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, xa, s);
 }
 
 #define MG_BOX_INSTANCES(T)                                                                                           \
-  template hipError_t launch_rbgs_box<T>(const T*, T*, const T*, const T*, const T*, const T*, int, double, int,      \
-                                         const double*, int, hipStream_t);                                            \
-  template hipError_t launch_rbgs_box_restrict<T>(const T*, T*, const T*, const T*, const T*, const T*, int, double, \
-                                                  int, const double*, T*, T*, hipStream_t);                           \
-  template hipError_t launch_rbgs_box_prolong<T>(const T*, T*, const T*, const T*, const T*, const T*, int, double,  \
-                                                 int, const double*, const T*, const uint8_t*, hipStream_t);
+  template hipError_t launch_rbgs_box<T>(const T*, T*, const T*, const T*, const T*, const T*, const T*, int, double, \
+                                         int, const double*, int, hipStream_t);                                       \
+  template hipError_t launch_rbgs_box_restrict<T>(const T*, T*, const T*, const T*, const T*, const T*, const T*,     \
+                                                  int, double, int, const double*, T*, T*, hipStream_t);              \
+  template hipError_t launch_rbgs_box_prolong<T>(const T*, T*, const T*, const T*, const T*, const T*, const T*, int, \
+                                                 double, int, const double*, const T*, const uint8_t*, hipStream_t);
 MG_BOX_INSTANCES(double)
 MG_BOX_INSTANCES(float)
 #undef MG_BOX_INSTANCES

@@ -300,8 +300,8 @@ __device__ __forceinline__ void gs(T (*cur)[2][W / 2], int r, int c, T lo, T hi,
 }
 
 
-// Tiles of TX x TY cells, one thread per x-pair of tile cells: 64 x 8 and 128 x 8 for
-// N = 64 and 128 (the x halo wraps onto the tile's own cache lines), 128 x 16 above
+// Tiles of TX x TY cells, one thread per x-pair of tile cells: 128 x 8 for N = 128 (the x
+// halo wraps onto the tile's own cache lines), 128 x 16 above
 // (one wave per tile row; fewer halo rows and ring cells per tile cell than 256 x 8).
 template <typename T, int TX, int TY, bool RHO, bool ZIN>
 __global__ __launch_bounds__(TX / 2 * TY) void k_rbgs_fused(const T* __restrict__ pin, T* __restrict__ pout,
@@ -632,14 +632,13 @@ hipError_t launch_tx(const T* pin, T* pout, const T* f, const T* bx, const T* by
 
 }  // namespace
 
-// (a 32^3 grid is faster with two half-sweeps: the one-pass sweep's prologue dominates)
-int fused_sweep_supported(int q) { return (1 << q) >= 64; }
+// (smaller grids are latency-bound: a z-march pays a load latency per plane)
+int fused_sweep_supported(int q) { return (1 << q) >= 128; }
 
 template <typename T, bool ZIN>
 hipError_t launch_shape(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt, int q,
                         double h, int order, const double* fshift, hipStream_t s) {
   const int n = 1 << q;
-  if (n == 64) return launch_tx<T, 64, 8, ZIN>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, s);
   if (n == 128) return launch_tx<T, 128, 8, ZIN>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, s);
   return launch_tx<T, 128, 16, ZIN>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, s);
 }
@@ -647,7 +646,7 @@ hipError_t launch_shape(const T* pin, T* pout, const T* f, const T* bx, const T*
 template <typename T>
 hipError_t launch_rbgs_fused(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt,
                              int q, double h, int order, const double* fshift, int zero_in, hipStream_t s) {
-  if ((1 << q) < 64) return hipErrorInvalidValue;
+  if (!fused_sweep_supported(q)) return hipErrorInvalidValue;
   return zero_in ? launch_shape<T, true>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, s)
                  : launch_shape<T, false>(pin, pout, f, bx, by, bz, rt, q, h, order, fshift, s);
 }

@@ -1,9 +1,12 @@
 """Kernels chosen on the smaller grids, at the edges of the rules that choose them."""
+import numpy as np
 import pytest
 import torch
 
 import fields
-from tests.gpu_helpers import dev
+from oracle import multigrid as omg
+from oracle.operator import face_coeffs_from_rho, project
+from tests.gpu_helpers import dev, host, maxrel
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +49,38 @@ def test_two_sweep_pass_128_concurrent(lanes):
     q, hist1, _ = MG.from_rho(rho, mask).solve(f, tol=1e-6, max_cycles=60, raise_on_fail=False)
     assert hist == hist1
     assert torch.equal(p, q)
+
+
+@pytest.mark.parametrize("N", [32, 64])
+@pytest.mark.parametrize("form", ["rho", "faces"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["fp32", "fp64"])
+def test_block_sweeps_against_oracle(N, form, dtype):
+    """The finest grid swept in blocks, from the density (FP32 and FP64 at 64^3) and from
+    face arrays (32^3, and any size set up from faces): sweeps of both orders and a cycle
+    (restriction and prolongation inside the sweeps) against the oracle.  FP64 within
+    1e-13 of the largest value for a sweep and 1e-12 for a cycle; FP32 within 2e-5 and
+    1e-4, as the other FP32 kernels."""
+    from paper_1410_2240_amd import MG, coeffs_from_rho
+    inp = fields.make("c5", N)
+    H = omg.setup(*face_coeffs_from_rho(inp.rho, inp.mask), inp.mask, inp.h)
+    rho, mask = dev(inp.rho), dev(inp.mask)
+    if form == "rho":
+        mg = MG.from_rho(rho, mask, mixed=True)
+    else:
+        mg = MG(*coeffs_from_rho(rho, mask), mask, mixed=True)
+    fp32 = dtype == torch.float32
+    # 64^3 and up from rho: the FP32 faces come from the FP32 density
+    lv32 = (omg.fp32_levels_from_rho(H, inp.rho) if form == "rho" and N >= 64 else omg.fp32_levels(H)) if fp32 else None
+    lev = lv32[0] if fp32 else H.levels[0]
+    g = np.random.default_rng(N)
+    cast = np.float32 if fp32 else np.float64
+    p = np.where(lev.mask, g.standard_normal(lev.bx.shape), 0.0).astype(cast)
+    f = project(g.standard_normal(lev.bx.shape), lev.mask).astype(cast)
+    for order in (0, 1):
+        for sweeps in (1, 2):
+            print(f"block sweep {N}^3 {form} {dtype} order={order} sweeps={sweeps}", flush=True)
+            want = omg.smooth(p, f, lev, sweeps, (omg.RED, omg.BLACK) if order == 0 else (omg.BLACK, omg.RED))
+            got = host(mg.smooth(0, dev(p), dev(f), sweeps, order))
+            assert maxrel(got, want) <= (2e-5 if fp32 else 1e-13)
+    want = omg.vcycle(H, p, f, lv32) if fp32 else omg.vcycle(H, p, f)
+    assert maxrel(host(mg.vcycle(dev(p), dev(f))), want) <= (1e-4 if fp32 else 1e-12)
