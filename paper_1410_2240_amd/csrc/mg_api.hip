@@ -489,8 +489,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
                                  c->stream));
       }
       cur = next_dir(cur);
-      MG_TRY(reduce_set(c, 0, nb, S_DW));
-      MG_TRY(reduce_set(c, 1, nb, S_DR));
+      MG_HIP(mg::launch_reduce_final2(part(c, 0), part(c, 1), nb, c->scal + S_DW, c->scal + S_DR, c->stream));
       return MG_OK;
     };
     double* kz_zero = (mixed || zin) ? nullptr : kz;

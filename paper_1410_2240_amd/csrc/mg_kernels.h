@@ -263,7 +263,10 @@ hipError_t launch_masked_sum(const double* x, const uint8_t* mask, int q, int mo
                              double* partials, int* nblocks, hipStream_t s);
 // out[0] = scale * sum(partials[0..nparts))  (single block, fixed order)
 hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s);
-// p = mask ? p - *mean : 0   (mean may be nullptr: p = mask ? p : 0)
+// two sums of nparts partials each, as launch_reduce_final with scale 1, in one launch
+hipError_t launch_reduce_final2(const double* parts0, const double* parts1, int nparts, double* out0, double* out1,
+                                hipStream_t s);
+// p = mask ? p - *mean : 0   (mean may be nullptr: only the 0s are written)
 hipError_t launch_gauge(double* p, const uint8_t* mask, int q, const double* mean, hipStream_t s);
 // p += mask ? double(e32) : 0
 hipError_t launch_update_p(double* p, const float* e32, const uint8_t* mask, int q, hipStream_t s);

@@ -84,3 +84,29 @@ def test_block_sweeps_against_oracle(N, form, dtype):
             assert maxrel(got, want) <= (2e-5 if fp32 else 1e-13)
     want = omg.vcycle(H, p, f, lv32) if fp32 else omg.vcycle(H, p, f)
     assert maxrel(host(mg.vcycle(dev(p), dev(f))), want) <= (1e-4 if fp32 else 1e-12)
+
+
+@pytest.mark.parametrize("N", [8, 16, 64])
+def test_guess_and_means_with_a_body(N):
+    """The passes over mask and vector around a solve, four cells to a thread: a guess that
+    is NaN in the body is a guess of 0 there, the removed mean is the fluid mean of f, and
+    the solution has none.  Both means to 1e-13 of the mean magnitude."""
+    from paper_1410_2240_amd import MG
+    g = np.random.default_rng(N)
+    inp = fields.make("c2", N)
+    mask = inp.mask.copy()
+    mask[N // 4, 1:3, 1:4] = 0   # runs of 3: no group of four cells all alike
+    live = mask != 0
+    f = np.where(live, g.standard_normal(mask.shape) + 0.5, np.nan)
+    p0 = np.where(live, g.standard_normal(mask.shape), np.nan)
+    rho, m = dev(inp.rho), dev(mask)
+    print(f"guess and means {N}^3", flush=True)
+    mg = MG.from_rho(rho, m)
+    p, hist, stats = mg.solve(dev(np.where(live, f, 0.0)), dev(p0), tol=1e-8)
+    q, hist0, _ = mg.solve(dev(np.where(live, f, 0.0)), dev(np.where(live, p0, 0.0)), tol=1e-8)
+    assert hist == hist0 and torch.equal(p, q)
+    assert stats["active_cells"] == int(live.sum())
+    assert abs(stats["removed_mean"] - f[live].mean()) <= 1e-13 * np.abs(f[live]).mean()
+    out = host(p)
+    assert (out[~live] == 0).all()
+    assert abs(out[live].mean()) <= 1e-13 * np.abs(out[live]).mean()
