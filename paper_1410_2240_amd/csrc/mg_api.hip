@@ -1,7 +1,7 @@
 // C ABI and host driver of the multigrid pressure solve (declared in include/mg.h).
 //
 // The host side plans the hierarchy, carves the caller's workspace, queues kernels
-// on the caller's stream and reads back one scalar (the residual norm) per cycle.
+// on the caller's stream and waits for one scalar (the residual norm) per cycle.
 // It never allocates device memory; the only host allocation besides the context
 // object is a small pinned buffer for those read-backs.
 #include <hip/hip_runtime.h>
@@ -97,8 +97,8 @@ struct mg_ctx {
   double *kr = nullptr, *kz = nullptr, *kd = nullptr, *kd2 = nullptr, *kw = nullptr;   // flexible-CG vectors
   double* kr2 = nullptr;   // a second residual (absent unless the plan holds one)
   double* kd3 = nullptr;   // a third direction (likewise)
-  double* host = nullptr;   // pinned, S_COUNT doubles
-  hipEvent_t read_done = nullptr;   // the last read-back of scalars has landed in host
+  double* host = nullptr;   // pinned: S_COUNT doubles, then the ticket of the last ones sent
+  unsigned long long published = 0;   // the ticket of the last scalars asked for
   long long active = 0, dropped = 0;
   // Concurrent right-hand sides (mg_add_lanes): each lane is a context of its own that
   // shares this one's coefficients, masks and pseudo-inverse and owns its scratch, a
@@ -324,25 +324,54 @@ int reduce(mg_ctx* c, int nparts, double scale, int slot) {
   return MG_OK;
 }
 
-// Read-backs in two halves: work queued between them runs while the host waits.
-int issue_scalars(mg_ctx* c, int count) {
-  MG_HIP(hipMemcpyAsync(c->host, c->scal, sizeof(double) * count, hipMemcpyDeviceToHost, c->stream));
-  MG_HIP(hipEventRecord(c->read_done, c->stream));
+unsigned long long* ticket_of(const mg_ctx* c) { return reinterpret_cast<unsigned long long*>(c->host + S_COUNT); }
+
+// The first `count` scalars to the host, from the launch that sums partial set `set` into
+// `slot`; wait_scalars takes them.  Work queued between the two runs while the host waits.
+int reduce_and_publish(mg_ctx* c, int set, int nparts, int slot, int count) {
+  mg::Publish pub;
+  pub.host = c->host;
+  pub.scal = c->scal;
+  pub.count = count;
+  pub.ticket = ticket_of(c);
+  pub.value = ++c->published;
+  const double* parts = c->partials + static_cast<size_t>(set) * mg::kNumPartials;
+  const hipError_t e = mg::launch_reduce_final(parts, nparts, 1.0, c->scal + slot, c->stream, &pub);
+  if (e != hipSuccess) {
+    --c->published;   // nothing will come
+    return fail(MG_EHIP, "launch_reduce_final: %s", hipGetErrorString(e));
+  }
   return MG_OK;
 }
 
+// Polls the ticket: the scalars are there a few microseconds after the kernel wrote them,
+// where an event's completion took an interrupt or a queue packet longer.  Now and then the
+// stream is asked, so that a failed launch ends the wait.
 int wait_scalars(mg_ctx* c, double* out, int count) {
-  MG_HIP(hipEventSynchronize(c->read_done));
+  using clock = std::chrono::steady_clock;
+  const auto t0 = clock::now();
+  auto asked = t0;
+  bool done = false;   // the stream has run dry
+  for (unsigned spins = 1; __atomic_load_n(ticket_of(c), __ATOMIC_ACQUIRE) < c->published; ++spins) {
+    if (done) return fail(MG_EHIP, "the stream ended without its scalars");
+    if (spins % 64 != 0) {
+      __builtin_ia32_pause();
+      continue;
+    }
+    const auto now = clock::now();
+    if (now - t0 > std::chrono::microseconds(100)) std::this_thread::yield();
+    if (now - asked > std::chrono::milliseconds(2)) {
+      asked = now;
+      const hipError_t e = hipStreamQuery(c->stream);
+      if (e == hipSuccess) done = true;   // its writes are visible: look once more
+      else if (e != hipErrorNotReady) return fail(MG_EHIP, "waiting for the scalars: %s", hipGetErrorString(e));
+    }
+  }
   std::memcpy(out, c->host, sizeof(double) * count);
   return MG_OK;
 }
 
-int read_scalars(mg_ctx* c, double* out, int count) {
-  MG_TRY(issue_scalars(c, count));
-  return wait_scalars(c, out, count);
-}
-
-// ||r||^2 of the finest residual into scal[S_RNORM2]; optional FP32 copy of r (with
+// ||r||^2 of the finest residual into scal[S_RNORM2], published; optional FP32 copy of r (with
 // e32 = 0) and FP64 copy (with z64 = 0)
 int residual_norm(mg_ctx* c, const double* p, const double* f, const double* fshift, float* r32, float* e32,
                   double* r64 = nullptr, double* z64 = nullptr) {
@@ -354,7 +383,7 @@ int residual_norm(mg_ctx* c, const double* p, const double* f, const double* fsh
   else
     MG_HIP(mg::launch_residual_norm(p, f, a.bx, a.by, a.bz, a.rt, a.q, a.h, fshift, r32, e32, r64, z64, c->partials,
                                     &nb, c->stream));
-  return reduce(c, nb, 1.0, S_RNORM2);
+  return reduce_and_publish(c, 0, nb, S_RNORM2, S_COUNT);
 }
 
 double* part(mg_ctx* c, int set) { return c->partials + static_cast<size_t>(set) * mg::kNumPartials; }
@@ -391,18 +420,20 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
   // them, so the passes before the cycle need not clear them
   const bool zin = out_of_place_sweeps(a.q);
   float* e32_zero = zin ? nullptr : e32;
-  MG_TRY(residual_norm(c, p, f, fshift, r32, e32_zero));
+  const bool krylov = (c->flags & MG_KRYLOV) != 0;
+  // flexible CG starts from this residual: it is kept (and the preconditioner's output
+  // cleared where its cycle reads it)
+  MG_TRY(residual_norm(c, p, f, fshift, r32, e32_zero, krylov ? c->kr : nullptr,
+                       krylov && !mixed && !zin ? c->kz : nullptr));
   // The next cycle's first finest-grid sweep is queued before each convergence check is
   // read back (first_sweep), so the GPU does not idle while the host decides.
   const bool spec = zin;
-  const bool krylov = (c->flags & MG_KRYLOV) != 0;
   auto cycle_first_sweep = [&]() -> int {
     if (mixed) return first_sweep<float>(c, e32, r32, nullptr, true);
     return first_sweep<double>(c, p, f, fshift, false);
   };
   bool ahead = false;   // the next cycle's first sweep is queued
   double s[3];
-  MG_TRY(issue_scalars(c, 3));
   if (spec && !krylov && max_cycles > 0) {
     MG_TRY(cycle_first_sweep());
     ahead = true;
@@ -494,8 +525,6 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
     };
     double* kz_zero = (mixed || zin) ? nullptr : kz;
     if (std::isfinite(r) && r > tol && max_cycles > 0) {
-      // the first residual pass also wrote r (and zeroed the preconditioner output)
-      MG_TRY(residual_norm(c, p, f, fshift, r32, e32_zero, kr, kz_zero));
       MG_TRY(precondition(false));
       MG_TRY(direction(true));
     }
@@ -517,10 +546,9 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
         MG_HIP(mg::launch_fcg_rupdate(kr, kw, c->scal + S_DR, c->scal + S_DW, c->scal + S_ALPHA, q, kz_zero,
                                       mixed ? r32 : nullptr, mixed ? e32_zero : nullptr, part(c, 2), &nb, c->stream));
       }
-      MG_TRY(reduce_set(c, 2, nb, S_RNORM2));
+      MG_TRY(reduce_and_publish(c, 2, nb, S_RNORM2, 8));
       ++*cycles;
       double sn[8];
-      MG_TRY(issue_scalars(c, 8));
       ahead = spec && *cycles < max_cycles && !ru_fused;
       if (ahead) MG_TRY(precondition_first_sweep());
       MG_TRY(wait_scalars(c, sn, 8));
@@ -569,7 +597,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
         int nbu = 0;
         MG_HIP(mg::launch_residual_norm_update_march(cur, e32, next, f, a.rt, a.q, a.h, fshift, r32, e32_zero,
                                                      c->partials, &nbu, c->stream));
-        MG_TRY(reduce(c, nbu, 1.0, S_RNORM2));
+        MG_TRY(reduce_and_publish(c, 0, nbu, S_RNORM2, 3));
         cur = next;
       } else {
         MG_HIP(mg::launch_update_p(p, e32, a.mask, a.q, c->stream));
@@ -581,7 +609,6 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
     }
     ++*cycles;
     double sn[3];
-    MG_TRY(issue_scalars(c, 3));
     ahead = spec && *cycles < max_cycles;
     if (ahead) MG_TRY(cycle_first_sweep());
     MG_TRY(wait_scalars(c, sn, 3));
@@ -671,6 +698,17 @@ extern "C" void mg_destroy(mg_ctx* ctx);
 
 namespace {
 
+// the pinned memory scalars come back in; coherent, since the host polls it while kernels run
+int alloc_host(mg_ctx* c) {
+  void* ptr = nullptr;
+  const hipError_t e = hipHostMalloc(&ptr, sizeof(double) * S_COUNT + sizeof(unsigned long long),
+                                     hipHostMallocMapped | hipHostMallocCoherent);
+  if (e != hipSuccess) return fail(MG_EHIP, "hipHostMalloc of the read-back buffer: %s", hipGetErrorString(e));
+  c->host = static_cast<double*>(ptr);
+  *ticket_of(c) = 0;
+  return MG_OK;
+}
+
 // Shared by mg_setup (finest face coefficients given) and mg_setup_from_rho (cell
 // density given; face products formed here, or density and areas coarsened apart).
 int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx, const double* by, const double* bz,
@@ -734,15 +772,8 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
     mg_destroy(c);
     return rc;
   };
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->host), sizeof(double) * S_COUNT, hipHostMallocDefault) !=
-      hipSuccess) {
-    c->host = nullptr;
-    return cleanup(fail(MG_EHIP, "hipHostMalloc of the read-back buffer failed"));
-  }
-  if (hipEventCreateWithFlags(&c->read_done, hipEventDisableTiming) != hipSuccess) {
-    c->read_done = nullptr;
-    return cleanup(fail(MG_EHIP, "hipEventCreateWithFlags of the read-back event failed"));
-  }
+  const int rc_host = alloc_host(c);
+  if (rc_host != MG_OK) return cleanup(rc_host);
   hipStream_t s = c->stream;
   int rc = MG_OK;
   auto hip = [&](hipError_t e, const char* what) {
@@ -840,7 +871,7 @@ int make_lane(mg_ctx* ctx, unsigned char* ws, const mg::Plan& lp, int device, mg
   mg_ctx* c = new mg_ctx(*ctx);
   c->lanes.clear();
   c->host = nullptr;
-  c->read_done = nullptr;
+  c->published = 0;
   c->order_event = nullptr;
   c->stream = nullptr;
   c->own_stream = false;
@@ -865,14 +896,7 @@ int make_lane(mg_ctx* ctx, unsigned char* ws, const mg::Plan& lp, int device, mg
   c->kr2 = at<double>(ws, lp.kr2);
   c->kd3 = at<double>(ws, lp.kd3);
   *out = c;
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->host), sizeof(double) * S_COUNT, hipHostMallocDefault) != hipSuccess) {
-    c->host = nullptr;
-    return fail(MG_EHIP, "hipHostMalloc of a lane's read-back buffer failed");
-  }
-  if (hipEventCreateWithFlags(&c->read_done, hipEventDisableTiming) != hipSuccess) {
-    c->read_done = nullptr;
-    return fail(MG_EHIP, "hipEventCreateWithFlags of a lane's read-back event failed");
-  }
+  MG_TRY(alloc_host(c));
   if (hipEventCreateWithFlags(&c->order_event, hipEventDisableTiming) != hipSuccess) {
     c->order_event = nullptr;
     return fail(MG_EHIP, "hipEventCreateWithFlags of a lane's order event failed");
@@ -1284,8 +1308,11 @@ void mg_destroy(mg_ctx* ctx) {
     (void)hipStreamSynchronize(ctx->stream);
     (void)hipStreamDestroy(ctx->stream);
   }
-  if (ctx->host) (void)hipHostFree(ctx->host);
-  if (ctx->read_done) (void)hipEventDestroy(ctx->read_done);
+  if (ctx->host) {
+    // a solve that ended on an error may have scalars still on their way
+    if (*ticket_of(ctx) < ctx->published) (void)hipStreamSynchronize(ctx->stream);
+    (void)hipHostFree(ctx->host);
+  }
   if (ctx->order_event) (void)hipEventDestroy(ctx->order_event);
   delete ctx;
 }

@@ -261,8 +261,18 @@ hipError_t launch_fcg_dir(const double* z64, const float* z32, const double* d, 
 // mode 0: partials = sum_active x ; mode 1: sum_active (x - *shift)^2
 hipError_t launch_masked_sum(const double* x, const uint8_t* mask, int q, int mode, const double* shift,
                              double* partials, int* nblocks, hipStream_t s);
+// Device scalars handed to the host by the kernel that forms the last of them: scal[0 ..
+// count) written to host, then value to *ticket (both in coherent pinned memory).
+struct Publish {
+  double* host = nullptr;
+  const double* scal = nullptr;
+  int count = 0;   // at most 64
+  unsigned long long* ticket = nullptr;
+  unsigned long long value = 0;
+};
 // out[0] = scale * sum(partials[0..nparts))  (single block, fixed order)
-hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s);
+hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s,
+                               const Publish* pub = nullptr);
 // two sums of nparts partials each, as launch_reduce_final with scale 1, in one launch
 hipError_t launch_reduce_final2(const double* parts0, const double* parts1, int nparts, double* out0, double* out1,
                                 hipStream_t s);

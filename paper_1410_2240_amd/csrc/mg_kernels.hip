@@ -812,7 +812,7 @@ __global__ __launch_bounds__(kBlock) void k_masked_sum(const double* __restrict_
 // the set).  With 16384 partials 3.4 us, 5.9 us as a tree in LDS with ten barriers.
 __global__ __launch_bounds__(1024) void k_reduce_final(const double* __restrict__ parts0,
                                                        const double* __restrict__ parts1, int nparts, double scale,
-                                                       double* __restrict__ out0, double* __restrict__ out1) {
+                                                       double* out0, double* out1, Publish pub) {
   __shared__ double red[16];
   const double* __restrict__ parts = blockIdx.x ? parts1 : parts0;
   const int tid = threadIdx.x;
@@ -825,7 +825,14 @@ __global__ __launch_bounds__(1024) void k_reduce_final(const double* __restrict_
   if (tid < 64) {
     double v = tid < (static_cast<int>(blockDim.x) >> 6) ? red[tid] : 0.0;
     for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if (tid == 0) *(blockIdx.x ? out1 : out0) = v * scale;
+    v *= scale;   // (lane 0 holds the sum)
+    if (tid == 0) *(blockIdx.x ? out1 : out0) = v;
+    if (pub.host) {   // one set only
+      const double sum = __shfl(v, 0, 64);
+      if (tid < pub.count) pub.host[tid] = pub.scal + tid == out0 ? sum : pub.scal[tid];
+      __threadfence_system();
+      if (tid == 0) __hip_atomic_store(pub.ticket, pub.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
 
@@ -1212,16 +1219,20 @@ hipError_t launch_masked_sum(const double* x, const uint8_t* mask, int q, int mo
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s) {
+hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s,
+                               const Publish* pub) {
   const int threads = std::min(1024, (nparts + 63) / 64 * 64);
-  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(threads), 0, s, partials, nullptr, nparts, scale, out, nullptr);
+  if (pub && (!pub->host || !pub->ticket || !pub->scal || pub->count > 64)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(threads), 0, s, partials, nullptr, nparts, scale, out, nullptr,
+                     pub ? *pub : Publish{});
   return hipGetLastError();
 }
 
 hipError_t launch_reduce_final2(const double* parts0, const double* parts1, int nparts, double* out0, double* out1,
                                 hipStream_t s) {
   const int threads = std::min(1024, (nparts + 63) / 64 * 64);
-  hipLaunchKernelGGL(k_reduce_final, dim3(2), dim3(threads), 0, s, parts0, parts1, nparts, 1.0, out0, out1);
+  hipLaunchKernelGGL(k_reduce_final, dim3(2), dim3(threads), 0, s, parts0, parts1, nparts, 1.0, out0, out1,
+                     Publish{});
   return hipGetLastError();
 }
 
