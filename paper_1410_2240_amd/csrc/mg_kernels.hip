@@ -558,188 +558,6 @@ __global__ __launch_bounds__(64) void k_coarse_solve(const T* __restrict__ f, T*
   coarse_solve_wave(f, e, pinv, mask, fh);
 }
 
-// The whole V(2,2) sub-cycle on grids of 16^3 and smaller, by one workgroup: the same
-// per-cell steps as the multi-block kernels, separated by workgroup barriers instead of
-// kernel launches.  The corrections and right-hand sides of every grid live in LDS
-// (75 KB in FP64 for 16^3 + 8^3 + 4^3); only the coefficients and masks are read from
-// memory.  Level 0 of `a` enters with its right-hand side and its correction (zero, or
-// the current iterate when it is the finest grid) and gets the result back.  The level
-// loops are unrolled over the at most three grids so every field of `a` is read with a
-// constant index.
-constexpr int kCoarseThreads = 512;
-constexpr int kCoarseCells = 4096 + 512 + 64;
-
-// e = A_c^+ (f - active mean of f) on the 4^3 grid in FP64 by the whole block: the mean
-// by the first wavefront, then each row of the pseudo-inverse product by 8 threads.
-template <typename T>
-__device__ __forceinline__ void coarse_solve_block(const T* f, T* e, const double* __restrict__ pinv,
-                                                   const uint8_t* __restrict__ mask, double* fh) {
-  const int t = threadIdx.x;
-  if (t < 64) {
-    const bool act = mask[t] != 0;
-    const double v = act ? static_cast<double>(f[t]) : 0.0;
-    double s = v, cnt = act ? 1.0 : 0.0;
-    for (int off = 32; off > 0; off >>= 1) {
-      s += __shfl_xor(s, off, 64);
-      cnt += __shfl_xor(cnt, off, 64);
-    }
-    const double mean = cnt > 0.0 ? s / cnt : 0.0;
-    fh[t] = act ? v - mean : 0.0;
-  }
-  const int row = t >> 3, part = t & 7;
-  double pv[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) pv[c] = pinv[row * 64 + part * 8 + c];   // issued before the barrier
-  __syncthreads();
-  double acc = 0.0;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) acc = __builtin_fma(pv[c], fh[part * 8 + c], acc);
-  acc += __shfl_xor(acc, 1, 64);
-  acc += __shfl_xor(acc, 2, 64);
-  acc += __shfl_xor(acc, 4, 64);
-  if (part == 0) e[row] = static_cast<T>(acc);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_cycle(CoarseCycle<T> a) {
-  static_assert(kCoarseThreads == 512, "the pseudo-inverse product maps 64 rows x 8 threads");
-  __shared__ double fh[64];
-  __shared__ T se[kCoarseCells];
-  __shared__ T sf[kCoarseCells];
-  const int tid = threadIdx.x;
-  const int last = a.nlev - 1;
-  // LDS arrays of each grid
-  T* e[3];
-  T* f[3];
-  {
-    int off = 0;
-#pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      e[l] = se + off;
-      f[l] = sf + off;
-      if (l < a.nlev) off += 1 << (3 * a.q[l]);
-    }
-  }
-  const int n0 = 1 << (3 * a.q[0]);
-  for (int c = tid; c < n0; c += kCoarseThreads) {
-    e[0][c] = a.e[0][c];
-    f[0][c] = a.f[0][c];
-  }
-  __syncthreads();
-  // The face coefficients of the cells this thread updates on the grids that are
-  // smoothed, loaded once (every half-sweep would otherwise wait for them from L2 again):
-  // on the first grid in FP32, on the second in both precisions.  Pair slot u of grid l
-  // is pair tid + u x 512 (at most 4 on a 16^3 grid), colour 0 / 1 its red / black cell.
-  // FP64 reads the first grid's from L2 in each half-sweep, all of a thread's pairs at
-  // once: held in registers they would spill.
-  constexpr bool PRE = sizeof(T) == 4;
-  constexpr int U0 = (kCoarseCycleMaxN * kCoarseCycleMaxN * kCoarseCycleMaxN / 2) / kCoarseThreads;
-  struct CF {
-    T xm, xp, ym, yp, zm, zp;
-  };
-  CF cf0[U0][2], cf1[2];
-  auto pair_cell = [&](int l, int pr, int colour, int& i, int& j, int& k) {
-    const int q = a.q[l], m = (1 << q) - 1;
-    const int ip = pr & (m >> 1);
-    j = (pr >> (q - 1)) & m;
-    k = pr >> (2 * q - 1);
-    i = 2 * ip + ((colour + j + k) & 1);
-  };
-  auto load_cf = [&](int l, int pr, int colour) {
-    int i, j, k;
-    pair_cell(l, pr, colour, i, j, k);
-    const Faces<T> F = load_faces(a.bx[l], a.by[l], a.bz[l], i, j, k, a.q[l]);
-    return CF{F.xm, F.xp, F.ym, F.yp, F.zm, F.zp};
-  };
-  auto preload0 = [&]() {
-    if constexpr (!PRE) return;
-#pragma unroll
-    for (int u = 0; u < U0; ++u) {
-      const int pr = tid + u * kCoarseThreads;
-      if (last > 0 && pr < (1 << (3 * a.q[0] - 1))) {
-        cf0[u][0] = load_cf(0, pr, 0);
-        cf0[u][1] = load_cf(0, pr, 1);
-      }
-    }
-  };
-  preload0();
-  if (last > 1 && tid < (1 << (3 * a.q[1] - 1))) {   // the second grid's: both precisions
-    cf1[0] = load_cf(1, tid, 0);
-    cf1[1] = load_cf(1, tid, 1);
-  }
-  // the update of gs_pair with preloaded coefficients (same operations, same order)
-  auto gs_pre = [&](int l, int pr, int colour, const CF& C, T fs) {
-    const int q = a.q[l], n = 1 << q, m = n - 1;
-    int i, j, k;
-    pair_cell(l, pr, colour, i, j, k);
-    const int c = cell(i, j, k, q);
-    const int cxm = cell((i - 1) & m, j, k, q), cxp = cell((i + 1) & m, j, k, q);
-    const int cym = cell(i, (j - 1) & m, k, q), cyp = cell(i, (j + 1) & m, k, q);
-    const int czm = k > 0 ? c - (1 << (2 * q)) : c, czp = k < m ? c + (1 << (2 * q)) : c;
-    T* p = e[l];
-    const T pxm = p[cxm], pxp = p[cxp], pym = p[cym], pyp = p[cyp], pzm = p[czm], pzp = p[czp];
-    const T fc = f[l][c];
-    const T D = C.xm + C.xp + C.ym + C.yp + C.zm + C.zp;
-    if (!(D > T(0))) return;
-    const T S = C.xm * pxm + C.xp * pxp + C.ym * pym + C.yp * pyp + C.zm * pzm + C.zp * pzp;
-    p[c] = gs_quotient(S - a.h2[l] * (fc - fs), D);
-  };
-  auto sweep = [&](int l, int colour, const T* bx, const T* by, const T* bz) {
-    const T fs = (l == 0 && a.fshift) ? static_cast<T>(*a.fshift) : T(0);
-    if (l == 1) {
-      if (tid < (1 << (3 * a.q[1] - 1))) gs_pre(1, tid, colour, cf1[colour], fs);
-    } else if constexpr (!PRE) {
-      // a fixed trip count, unrolled, so that the coefficient loads of all of a thread's
-      // pairs are in flight together
-#pragma unroll
-      for (int u = 0; u < U0; ++u) {
-        const int pr = tid + u * kCoarseThreads;
-        if (pr < (1 << (3 * a.q[0] - 1))) gs_pair(e[0], f[0], bx, by, bz, a.q[0], a.h2[0], colour, fs, pr);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < U0; ++u) {
-        const int pr = tid + u * kCoarseThreads;
-        if (pr < (1 << (3 * a.q[0] - 1))) gs_pre(0, pr, colour, cf0[u][colour], fs);
-      }
-    }
-    __syncthreads();
-  };
-#pragma unroll
-  for (int l = 0; l < 2; ++l) {
-    if (l < last) {
-      for (int s = 0; s < 2; ++s) {
-        sweep(l, 0, a.bx[l], a.by[l], a.bz[l]);
-        sweep(l, 1, a.bx[l], a.by[l], a.bz[l]);
-      }
-      const T fs = (l == 0 && a.fshift) ? static_cast<T>(*a.fshift) : T(0);
-      for (int C = tid; C < (1 << (3 * (a.q[l] - 1))); C += kCoarseThreads)
-        restrict_cell<T, false>(e[l], f[l], Coefs<T>{a.bx[l], a.by[l], a.bz[l], nullptr}, a.q[l], a.inv_h2[l], fs,
-                                f[l + 1], e[l + 1], C);
-      __syncthreads();
-    }
-  }
-  const uint8_t* ml = last == 0 ? a.mask[0] : (last == 1 ? a.mask[1] : a.mask[2]);
-  coarse_solve_block(f[last], e[last], a.pinv, ml, fh);
-  __syncthreads();
-#pragma unroll
-  for (int l = 1; l >= 0; --l) {
-    if (l < last) {
-      // the first grid's coefficients again for its post-smoothing (not kept in
-      // registers through the coarser grids), in flight during the prolongation
-      if (l == 0) preload0();
-      for (int C = tid; C < (1 << (3 * (a.q[l] - 1))); C += kCoarseThreads)
-        prolong_cell(e[l + 1], e[l], a.mask[l], a.q[l], C);
-      __syncthreads();
-      for (int s = 0; s < 2; ++s) {
-        sweep(l, 1, a.bx[l], a.by[l], a.bz[l]);
-        sweep(l, 0, a.bx[l], a.by[l], a.bz[l]);
-      }
-    }
-  }
-  for (int c = tid; c < n0; c += kCoarseThreads) a.e[0][c] = e[0][c];
-}
-
 // ------------------------------------------------------------------ FP64 finest passes
 
 __device__ __forceinline__ double block_sum(double v) {
@@ -1312,13 +1130,6 @@ hipError_t launch_fcg_dir(const double* z64, const float* z32, const double* d, 
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s) {
-  if (a.nlev < 1 || a.nlev > 3) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_coarse_cycle<T>, dim3(1), dim3(kCoarseThreads), 0, s, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_divergence(const double* ux, const double* uy, const double* uz, const double* rx, const double* ry,
                              const double* rz, double dt, const uint8_t* mask, int q, double h, double* f,
                              hipStream_t s) {
@@ -1341,8 +1152,7 @@ hipError_t launch_project(double* ux, double* uy, double* uz, const double* rx, 
   template hipError_t launch_residual_restrict<T>(const T*, const T*, const T*, const T*, const T*, const T*, int, \
                                                   double, const double*, T*, T*, hipStream_t);                   \
   template hipError_t launch_prolong_add<T>(const T*, T*, const uint8_t*, int, hipStream_t);                     \
-  template hipError_t launch_coarse_solve<T>(const T*, T*, const double*, const uint8_t*, hipStream_t);    \
-  template hipError_t launch_coarse_cycle<T>(const CoarseCycle<T>&, hipStream_t);
+  template hipError_t launch_coarse_solve<T>(const T*, T*, const double*, const uint8_t*, hipStream_t);
 MG_INSTANTIATE(double)
 MG_INSTANTIATE(float)
 #undef MG_INSTANTIATE

@@ -1,0 +1,497 @@
+// The V(2,2) cycle on grids of 16^3 and below, by one workgroup (CDNA4).
+//
+// These grids hold less than a megabyte between them, so what they cost is latency: the
+// loads of each half-sweep, a barrier after it, and the length of an update's chain.  The
+// split follows from that.
+//   16^3  Each of the 512 threads owns a 2 x 2 x 2 block, the children of one 8^3 cell.  It
+//         holds the block's values, right-hand sides, faces, diagonals and their reciprocals
+//         in registers for the whole cycle: nothing but the values of the three neighbours
+//         outside the block is read in a half-sweep (12 LDS reads and 4 writes for 4
+//         independent updates), and the restriction and prolongation are thread-local.
+//   8^3   Each of 256 threads owns an x-pair, one cell of each colour, with the same things
+//         in registers; the values live in LDS.
+//   4^3   The pseudo-inverse product, 8 threads to a row, its entries loaded at the start.
+// All memory is read once, at the start, in one round of loads.  On the values of a 16^3
+// grid rows are split by column parity and padded to 20 words, so that the neighbours of a
+// wave's blocks fall in different banks.
+//
+// A cycle from 16^3 takes 12.4 us in FP64 and 10.7 us in FP32, launch included, and one
+// from 8^3 7.6 us.  With a barrier-separated copy of the many-block kernels instead (each
+// half-sweep reading its coefficients and six neighbours again) they took 26.1, 21.7 and
+// 10.2 us.
+#include "mg_kernels.h"
+#include "mg_plan.h"
+
+namespace mg {
+
+namespace {
+
+constexpr int kTailThreads = 512;
+constexpr int kRow = 20;            // a 16-cell row: 8 even columns, 8 odd ones, 4 unused
+constexpr int kPlane = 16 * kRow;
+
+template <typename T>
+struct Vec2of;
+template <>
+struct Vec2of<double> {
+  using type = double2;
+};
+template <>
+struct Vec2of<float> {
+  using type = float2;
+};
+
+template <typename T>
+__device__ __forceinline__ typename Vec2of<T>::type pair_at(const T* __restrict__ a, int c) {
+  return *reinterpret_cast<const typename Vec2of<T>::type*>(a + c);
+}
+
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// gs_quotient in two parts: the reciprocal of a diagonal, kept for the whole cycle, and the
+// quotient from it
+__device__ __forceinline__ double diag_recip(double d) {
+  const double r = __builtin_amdgcn_rcp(d);
+  return __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+}
+__device__ __forceinline__ float diag_recip(float d) { return __builtin_amdgcn_rcpf(d); }
+template <typename T>
+__device__ __forceinline__ T quotient(T n, T d, T r) {
+  const T q = n * r;
+  return fma_t(fma_t(-d, q, n), r, q);
+}
+
+template <typename T, bool TOP16>
+struct TailShared {
+  T e0[TOP16 ? 16 * kPlane : 1];
+  T e1[512], f1[512];
+  T x[256];   // residuals of the 8^3 grid's pairs
+  T e2[64];
+  double fh[64];
+  double pinv[TOP16 ? 8 * kTailThreads : 1];   // each thread its own column (no registers left for it)
+};
+
+// One cell: faces, diagonal and its reciprocal, right-hand side (less its shift).
+template <typename T>
+struct TailCell {
+  T xm, xp, ym, yp, zm, zp, D, r, f;
+};
+
+template <typename T, bool TOP16>
+struct Tail {
+  using V2 = typename Vec2of<T>::type;
+  TailShared<T, TOP16>& s;
+  const CoarseCycle<T>& a;
+  const int tid;
+
+  // the block of a 16^3 grid: [dz][dy][dx] values, faces by position along their direction
+  T e[2][2][2], f[2][2][2], D[2][2][2], r[2][2][2];
+  T fx[3][2][2], fy[3][2][2], fz[3][2][2];   // [x][dy][dz], [y][dx][dz], [z][dx][dy]
+  unsigned live0 = 0;                        // bit dz 4 + dy 2 + dx: an active cell
+  int o, oxm, oxp, oym, oyp, ozm, ozp;       // LDS offsets: the block, and to its neighbours
+  // the pair of an 8^3 grid: cell of colour 0 and of colour 1
+  TailCell<T> p1[2];
+  bool live1[2];
+  int c1[2], xm1[2], xp1[2], ym1, yp1, zm1, zp1;
+  double pv[TOP16 ? 1 : 8];
+  bool act2 = false;
+
+  static constexpr int L1 = TOP16 ? 1 : 0;   // the 8^3 grid's and the 4^3 grid's entry in a
+  static constexpr int L2 = L1 + 1;
+
+  __device__ Tail(TailShared<T, TOP16>& sh, const CoarseCycle<T>& args) : s(sh), a(args), tid(threadIdx.x) {}
+
+  // every load of the cycle but the top grid's values
+  __device__ __forceinline__ void load(T fs) {
+    if constexpr (TOP16) {
+      const int I = tid & 7, J = (tid >> 3) & 7, K = tid >> 6;
+      const T* __restrict__ bx = a.bx[0];
+      const T* __restrict__ by = a.by[0];
+      const T* __restrict__ bz = a.bz[0];
+      auto at = [](int i, int j, int k) { return (k << 8) + (j << 4) + i; };
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          const int c = at(2 * I, 2 * J + dy, 2 * K + dz);
+          const V2 xv = pair_at(bx, c), fv = pair_at(a.f[0], c);
+          fx[0][dy][dz] = xv.x;
+          fx[1][dy][dz] = xv.y;
+          fx[2][dy][dz] = bx[at((2 * I + 2) & 15, 2 * J + dy, 2 * K + dz)];
+          f[dz][dy][0] = fv.x - fs;
+          f[dz][dy][1] = fv.y - fs;
+          const uchar2 mk = *reinterpret_cast<const uchar2*>(a.mask[0] + c);
+          live0 |= (mk.x ? 1u : 0u) << (4 * dz + 2 * dy);
+          live0 |= (mk.y ? 2u : 0u) << (4 * dz + 2 * dy);
+        }
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          const V2 v = pair_at(by, at(2 * I, (2 * J + b) & 15, 2 * K + dz));
+          fy[b][0][dz] = v.x;
+          fy[b][1][dz] = v.y;
+        }
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          const bool in = 2 * K + c < 16;   // the top wall's face is 0, the bottom one's is stored as 0
+          const V2 v = in ? pair_at(bz, at(2 * I, 2 * J + dy, 2 * K + c)) : V2{T(0), T(0)};
+          fz[c][0][dy] = v.x;
+          fz[c][1][dy] = v.y;
+        }
+      o = 2 * K * kPlane + 2 * J * kRow + I;
+      oxm = 8 + ((I - 1) & 7) - I;          // column 2I-1, from column 2I
+      oxp = ((I + 1) & 7) - I;              // column 2I+2, from column 2I
+      oym = (((2 * J - 1) & 15) - 2 * J) * kRow;
+      oyp = (((2 * J + 2) & 15) - 2 * J) * kRow;
+      ozm = K > 0 ? -kPlane : 0;            // at a wall the cell itself: its face there is 0
+      ozp = K < 7 ? 2 * kPlane : kPlane;
+    }
+    if (tid < 256) {
+      const int ip = tid & 3, j = (tid >> 2) & 7, k = tid >> 5;
+      const T* __restrict__ bx = a.bx[L1];
+      const T* __restrict__ by = a.by[L1];
+      const T* __restrict__ bz = a.bz[L1];
+      ym1 = (((j - 1) & 7) - j) * 8;
+      yp1 = (((j + 1) & 7) - j) * 8;
+      zm1 = k > 0 ? -64 : 0;
+      zp1 = k < 7 ? 64 : 0;
+#pragma unroll
+      for (int col = 0; col < 2; ++col) {
+        const int i = 2 * ip + ((col + j + k) & 1);
+        const int c = (k * 8 + j) * 8 + i;
+        c1[col] = c;
+        xm1[col] = c - i + ((i - 1) & 7);
+        xp1[col] = c - i + ((i + 1) & 7);
+        TailCell<T>& q = p1[col];
+        q.xm = bx[c];
+        q.xp = bx[xp1[col]];
+        q.ym = by[c];
+        q.yp = by[c + yp1];
+        q.zm = bz[c];
+        q.zp = k < 7 ? bz[c + 64] : T(0);
+        live1[col] = a.mask[L1][c] != 0;
+        if constexpr (!TOP16) q.f = a.f[0][c] - fs;
+      }
+    }
+    if (tid < 64) act2 = a.mask[L2][tid] != 0;
+    {
+      const int row = tid >> 3, part = tid & 7;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const double v = a.pinv[row * 64 + part * 8 + c];
+        if constexpr (TOP16) s.pinv[c * kTailThreads + tid] = v;
+        else pv[c] = v;
+      }
+    }
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+          for (int dx = 0; dx < 2; ++dx) {
+            const T d = fx[dx][dy][dz] + fx[dx + 1][dy][dz] + fy[dy][dx][dz] + fy[dy + 1][dx][dz] + fz[dz][dx][dy] +
+                        fz[dz + 1][dx][dy];
+            D[dz][dy][dx] = d;
+            r[dz][dy][dx] = diag_recip(d);
+          }
+    }
+    if (tid < 256) {
+#pragma unroll
+      for (int col = 0; col < 2; ++col) {
+        TailCell<T>& q = p1[col];
+        q.D = q.xm + q.xp + q.ym + q.yp + q.zm + q.zp;
+        q.r = diag_recip(q.D);
+      }
+    }
+  }
+
+  // ---- 16^3
+
+  __device__ __forceinline__ void load_e() {
+    if constexpr (TOP16) {
+      const int I = tid & 7, J = (tid >> 3) & 7, K = tid >> 6;
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy) {
+          const V2 v = pair_at(a.e[0], ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I);
+          e[dz][dy][0] = v.x;
+          e[dz][dy][1] = v.y;
+        }
+    } else {
+      s.e1[tid] = a.e[0][tid];
+    }
+  }
+
+  __device__ __forceinline__ void store_e() {
+    if constexpr (TOP16) {
+      const int I = tid & 7, J = (tid >> 3) & 7, K = tid >> 6;
+#pragma unroll
+      for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy)
+          *reinterpret_cast<V2*>(a.e[0] + ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I) =
+              V2{e[dz][dy][0], e[dz][dy][1]};
+    } else {
+      a.e[0][tid] = s.e1[tid];
+    }
+  }
+
+  __device__ __forceinline__ int own(int dz, int dy, int dx) const { return o + dz * kPlane + dy * kRow + 8 * dx; }
+
+  __device__ __forceinline__ void put_block() {   // every value of the block into LDS
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 2; ++dx) s.e0[own(dz, dy, dx)] = e[dz][dy][dx];
+  }
+
+  struct Around {
+    T xm, xp, ym, yp, zm, zp;
+  };
+  __device__ __forceinline__ Around around(int dz, int dy, int dx) const {
+    const T* L = s.e0;
+    const int row = o + dz * kPlane + dy * kRow;
+    Around n;
+    n.xm = dx ? e[dz][dy][0] : L[row + oxm];
+    n.xp = dx ? L[row + oxp] : e[dz][dy][1];
+    n.ym = dy ? e[dz][0][dx] : L[o + dz * kPlane + 8 * dx + oym];
+    n.yp = dy ? L[o + dz * kPlane + 8 * dx + oyp] : e[dz][1][dx];
+    n.zm = dz ? e[0][dy][dx] : L[o + dy * kRow + 8 * dx + ozm];
+    n.zp = dz ? L[o + dy * kRow + 8 * dx + ozp] : e[1][dy][dx];
+    return n;
+  }
+
+  template <int COL>
+  __device__ __forceinline__ void half16() {
+    const T h2 = a.h2[0];
+    T v[4];
+    int u = 0;
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy) {
+        const int dx = (COL + dy + dz) & 1;
+        const Around n = around(dz, dy, dx);
+        const T S = fma_t(fz[dz + 1][dx][dy], n.zp, fma_t(fz[dz][dx][dy], n.zm, fma_t(fy[dy + 1][dx][dz], n.yp,
+                    fma_t(fy[dy][dx][dz], n.ym, fma_t(fx[dx + 1][dy][dz], n.xp, fx[dx][dy][dz] * n.xm)))));
+        const T q = quotient(fma_t(-h2, f[dz][dy][dx], S), D[dz][dy][dx], r[dz][dy][dx]);
+        v[u++] = D[dz][dy][dx] > T(0) ? q : e[dz][dy][dx];
+      }
+    u = 0;
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy) {
+        const int dx = (COL + dy + dz) & 1;
+        e[dz][dy][dx] = v[u];
+        s.e0[own(dz, dy, dx)] = v[u++];
+      }
+    __syncthreads();
+  }
+
+  __device__ __forceinline__ T residual16(int dz, int dy, int dx) const {
+    const Around n = around(dz, dy, dx);
+    const T pc = e[dz][dy][dx];
+    const T S = fma_t(fz[dz + 1][dx][dy], n.zp - pc, fma_t(fz[dz][dx][dy], n.zm - pc,
+                fma_t(fy[dy + 1][dx][dz], n.yp - pc, fma_t(fy[dy][dx][dz], n.ym - pc,
+                fma_t(fx[dx + 1][dy][dz], n.xp - pc, fx[dx][dy][dz] * (n.xm - pc))))));
+    return D[dz][dy][dx] > T(0) ? fma_t(-a.inv_h2[0], S, f[dz][dy][dx]) : T(0);
+  }
+
+  // the mean of the block's residuals: the right-hand side of 8^3 cell tid
+  __device__ __forceinline__ void restrict16() {
+    T sum = T(0);
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy) sum += residual16(dz, dy, 0) + residual16(dz, dy, 1);
+    s.f1[tid] = sum * T(0.125);
+    s.e1[tid] = T(0);
+    __syncthreads();
+  }
+
+  // the trilinear correction from an edge-long grid's correction ec at cell (I, J, K) to its
+  // child (dx, dy, dz): 1-D weights 3/4 and 1/4, x then y then z, each a fused multiply-add
+  template <int EDGE>
+  __device__ static __forceinline__ void around_coarse(const T* ec, int I, int J, int K, T (&ax)[3][3][2]) {
+    constexpr int m = EDGE - 1;
+    const int Ix[3] = {(I - 1) & m, I, (I + 1) & m}, Jy[3] = {(J - 1) & m, J, (J + 1) & m};
+    const int Kz[3] = {K > 0 ? K - 1 : K, K, K < m ? K + 1 : K};
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const T* row = ec + (Kz[b] * EDGE + Jy[c]) * EDGE;
+        const T e0 = row[Ix[0]], e1 = row[Ix[1]], e2 = row[Ix[2]];
+        ax[b][c][0] = fma_t(T(0.75), e1, T(0.25) * e0);
+        ax[b][c][1] = fma_t(T(0.75), e1, T(0.25) * e2);
+      }
+  }
+
+  __device__ __forceinline__ void prolong16() {
+    T ax[3][3][2];
+    around_coarse<8>(s.e1, tid & 7, (tid >> 3) & 7, tid >> 6, ax);
+#pragma unroll
+    for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 2; ++dx) {
+          const T lo = fma_t(T(0.75), ax[1][1][dx], T(0.25) * ax[1][2 * dy][dx]);
+          const T hi = fma_t(T(0.75), ax[2 * dz][1][dx], T(0.25) * ax[2 * dz][2 * dy][dx]);
+          if (live0 >> (4 * dz + 2 * dy + dx) & 1) e[dz][dy][dx] += fma_t(T(0.75), lo, T(0.25) * hi);
+        }
+    put_block();
+    __syncthreads();
+  }
+
+  // ---- 8^3
+
+  template <int COL>
+  __device__ __forceinline__ void half8() {
+    if (tid < 256) {
+      const TailCell<T>& q = p1[COL];
+      const int c = c1[COL];
+      const T* L = s.e1;
+      const T S = fma_t(q.zp, L[c + zp1], fma_t(q.zm, L[c + zm1], fma_t(q.yp, L[c + yp1], fma_t(q.ym, L[c + ym1],
+                  fma_t(q.xp, L[xp1[COL]], q.xm * L[xm1[COL]])))));
+      if (q.D > T(0)) s.e1[c] = quotient(fma_t(-a.h2[L1], q.f, S), q.D, q.r);
+    }
+    __syncthreads();
+  }
+
+  __device__ __forceinline__ T residual8(int col) const {
+    const TailCell<T>& q = p1[col];
+    const int c = c1[col];
+    const T* L = s.e1;
+    const T pc = L[c];
+    const T S = fma_t(q.zp, L[c + zp1] - pc, fma_t(q.zm, L[c + zm1] - pc, fma_t(q.yp, L[c + yp1] - pc,
+                fma_t(q.ym, L[c + ym1] - pc, fma_t(q.xp, L[xp1[col]] - pc, q.xm * (L[xm1[col]] - pc))))));
+    return q.D > T(0) ? fma_t(-a.inv_h2[L1], S, q.f) : T(0);
+  }
+
+  // the 8^3 grid's cycle on s.e1 with the right-hand side in p1[].f
+  __device__ __forceinline__ void cycle8() {
+    half8<0>();
+    half8<1>();
+    half8<0>();
+    half8<1>();
+    if (tid < 256) {
+      const T ra = residual8(0), rb = residual8(1);
+      s.x[tid] = ra + rb;
+    }
+    __syncthreads();
+    // the 4^3 grid: e = A^+ (f - active mean of f) in FP64
+    if (tid < 64) {
+      const int I = tid & 3, J = (tid >> 2) & 3, K = tid >> 4;
+      T sum = T(0);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) sum += s.x[((2 * K + (d >> 1)) * 8 + 2 * J + (d & 1)) * 4 + I];
+      const T f2 = sum * T(0.125);
+      const double v = act2 ? static_cast<double>(f2) : 0.0;
+      double total = v;
+      for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+      const int cnt = __popcll(__ballot(act2));
+      s.fh[tid] = act2 ? v - (cnt > 0 ? total / cnt : 0.0) : 0.0;
+    }
+    __syncthreads();
+    {
+      const int row = tid >> 3, part = tid & 7;
+      double acc = 0.0;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        double v;
+        if constexpr (TOP16) v = s.pinv[c * kTailThreads + tid];
+        else v = pv[c];
+        acc = __builtin_fma(v, s.fh[part * 8 + c], acc);
+      }
+      acc += __shfl_xor(acc, 1, 64);
+      acc += __shfl_xor(acc, 2, 64);
+      acc += __shfl_xor(acc, 4, 64);
+      if (part == 0) s.e2[row] = static_cast<T>(acc);
+    }
+    __syncthreads();
+    if (tid < 256) {
+      const int ip = tid & 3, j = (tid >> 2) & 7, k = tid >> 5;
+      T ax[3][3][2];
+      around_coarse<4>(s.e2, ip, j >> 1, k >> 1, ax);
+      const int dy = j & 1, dz = k & 1;
+#pragma unroll
+      for (int dx = 0; dx < 2; ++dx) {
+        const T near = dy ? ax[1][2][dx] : ax[1][0][dx];
+        const T far1 = dz ? ax[2][1][dx] : ax[0][1][dx];
+        const T far2 = dz ? (dy ? ax[2][2][dx] : ax[2][0][dx]) : (dy ? ax[0][2][dx] : ax[0][0][dx]);
+        const T lo = fma_t(T(0.75), ax[1][1][dx], T(0.25) * near);
+        const T hi = fma_t(T(0.75), far1, T(0.25) * far2);
+        const bool on = ((dx + j + k) & 1) ? live1[1] : live1[0];
+        if (on) s.e1[(k * 8 + j) * 8 + 2 * ip + dx] += fma_t(T(0.75), lo, T(0.25) * hi);
+      }
+    }
+    __syncthreads();
+    half8<1>();
+    half8<0>();
+    half8<1>();
+    half8<0>();
+  }
+
+  // one cycle; the top grid's values are in e (and in s.e0) or in s.e1, past a barrier
+  __device__ __forceinline__ void cycle() {
+    if constexpr (TOP16) {
+      half16<0>();
+      half16<1>();
+      half16<0>();
+      half16<1>();
+      restrict16();
+      if (tid < 256) {
+        p1[0].f = s.f1[c1[0]];
+        p1[1].f = s.f1[c1[1]];
+      }
+      cycle8();
+      prolong16();
+      half16<1>();
+      half16<0>();
+      half16<1>();
+      half16<0>();
+    } else {
+      cycle8();
+    }
+  }
+};
+
+template <typename T, bool TOP16>
+__global__ __launch_bounds__(kTailThreads) void k_coarse_cycle(CoarseCycle<T> a) {
+  __shared__ TailShared<T, TOP16> s;
+  Tail<T, TOP16> t(s, a);
+  t.load_e();
+  t.load(a.fshift ? static_cast<T>(*a.fshift) : T(0));
+  if constexpr (TOP16) t.put_block();
+  __syncthreads();
+  t.cycle();
+  t.store_e();
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s) {
+  if (a.nlev == 3 && a.q[0] == 4)
+    hipLaunchKernelGGL((k_coarse_cycle<T, true>), dim3(1), dim3(kTailThreads), 0, s, a);
+  else if (a.nlev == 2 && a.q[0] == 3)
+    hipLaunchKernelGGL((k_coarse_cycle<T, false>), dim3(1), dim3(kTailThreads), 0, s, a);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+template hipError_t launch_coarse_cycle<double>(const CoarseCycle<double>&, hipStream_t);
+template hipError_t launch_coarse_cycle<float>(const CoarseCycle<float>&, hipStream_t);
+
+}  // namespace mg
