@@ -93,7 +93,6 @@ struct mg_ctx {
   double* pinv = nullptr;
   double* partials = nullptr;
   double* scal = nullptr;
-  long long* counters = nullptr;
   double *kr = nullptr, *kz = nullptr, *kd = nullptr, *kd2 = nullptr, *kw = nullptr;   // flexible-CG vectors
   double* kr2 = nullptr;   // a second residual (absent unless the plan holds one)
   double* kd3 = nullptr;   // a third direction (likewise)
@@ -686,6 +685,26 @@ std::vector<int> coarse_components(const std::vector<double>& bx, const std::vec
   return comp;
 }
 
+// The 4^3 pseudo-inverse formed on the host, where the elimination on the device met a
+// pivot that is not positive: by Cholesky, or from the eigendecomposition.
+int host_pinv(mg_ctx* c, const Level& cl) {
+  const int nc = static_cast<int>(cells(cl));
+  std::vector<double> hbx(nc), hby(nc), hbz(nc), A, P;
+  std::vector<uint8_t> hm(nc);
+  MG_HIP(hipMemcpyAsync(hbx.data(), cl.bx, nc * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  MG_HIP(hipMemcpyAsync(hby.data(), cl.by, nc * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  MG_HIP(hipMemcpyAsync(hbz.data(), cl.bz, nc * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  MG_HIP(hipMemcpyAsync(hm.data(), cl.mask, nc, hipMemcpyDeviceToHost, c->stream));
+  MG_HIP(hipStreamSynchronize(c->stream));
+  coarse_dense(hbx, hby, hbz, hm, cl.n, cl.h, A);
+  // the null space is known exactly from the graph; eigendecomposition only as fallback
+  if (!mg::graph_pinv(nc, A, coarse_components(hbx, hby, hbz, hm, cl.n), 1e-14, P))
+    mg::symmetric_pinv(nc, A, kPinvRtol, P);
+  MG_HIP(hipMemcpyAsync(c->pinv, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  MG_HIP(hipStreamSynchronize(c->stream));
+  return MG_OK;
+}
+
 int check_level(mg_ctx* c, int level, int need_coarser) {
   if (!c) return fail(MG_EINVAL, "null context");
   if (level < 0 || level >= c->L - need_coarser) return fail(MG_EINVAL, "level %d out of range", level);
@@ -698,15 +717,57 @@ extern "C" void mg_destroy(mg_ctx* ctx);
 
 namespace {
 
-// the pinned memory scalars come back in; coherent, since the host polls it while kernels run
+// The pinned memory scalars come back in; coherent, since the host polls it while kernels
+// run.  Allocating and freeing it for every context cost a setup and a destroy about 60 us
+// (the free waits for the device), so contexts take slots of one block, made for the first
+// of them; with every slot taken a context gets an allocation of its own, as before.
+constexpr size_t kSlotBytes = 128;   // S_COUNT doubles and the ticket
+constexpr int kSlots = 64;
+static_assert(sizeof(double) * S_COUNT + sizeof(unsigned long long) <= kSlotBytes, "a slot holds the scalars");
+std::mutex g_slots_mutex;
+unsigned char* g_slots = nullptr;
+unsigned long long g_slots_taken = 0;   // bit i: slot i
+
+hipError_t pinned_alloc(void** ptr, size_t bytes) {
+  return hipHostMalloc(ptr, bytes, hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable);
+}
+
 int alloc_host(mg_ctx* c) {
   void* ptr = nullptr;
-  const hipError_t e = hipHostMalloc(&ptr, sizeof(double) * S_COUNT + sizeof(unsigned long long),
-                                     hipHostMallocMapped | hipHostMallocCoherent);
-  if (e != hipSuccess) return fail(MG_EHIP, "hipHostMalloc of the read-back buffer: %s", hipGetErrorString(e));
+  {
+    std::lock_guard<std::mutex> lock(g_slots_mutex);
+    if (!g_slots && pinned_alloc(&ptr, kSlotBytes * kSlots) == hipSuccess) g_slots = static_cast<unsigned char*>(ptr);
+    ptr = nullptr;
+    if (g_slots && ~g_slots_taken) {
+      const int i = __builtin_ctzll(~g_slots_taken);
+      g_slots_taken |= 1ULL << i;
+      ptr = g_slots + i * kSlotBytes;
+    }
+  }
+  if (!ptr) {
+    const hipError_t e = pinned_alloc(&ptr, kSlotBytes);
+    if (e != hipSuccess) return fail(MG_EHIP, "hipHostMalloc of the read-back buffer: %s", hipGetErrorString(e));
+  }
   c->host = static_cast<double*>(ptr);
-  *ticket_of(c) = 0;
+  __atomic_store_n(ticket_of(c), 0ULL, __ATOMIC_RELEASE);
+  c->published = 0;
   return MG_OK;
+}
+
+void free_host(mg_ctx* c) {
+  if (!c->host) return;
+  // after an error scalars may still be on their way
+  if (__atomic_load_n(ticket_of(c), __ATOMIC_ACQUIRE) < c->published) (void)hipStreamSynchronize(c->stream);
+  unsigned char* p = reinterpret_cast<unsigned char*>(c->host);
+  c->host = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_slots_mutex);
+    if (g_slots && p >= g_slots && p < g_slots + kSlotBytes * kSlots) {
+      g_slots_taken &= ~(1ULL << ((p - g_slots) / kSlotBytes));
+      return;
+    }
+  }
+  (void)hipHostFree(p);
 }
 
 // Shared by mg_setup (finest face coefficients given) and mg_setup_from_rho (cell
@@ -759,7 +820,6 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
   c->pinv = at<double>(c->ws, plan.pinv);
   c->partials = at<double>(c->ws, plan.partials);
   c->scal = at<double>(c->ws, plan.scalars);
-  c->counters = at<long long>(c->ws, plan.counters);
   c->kr = at<double>(c->ws, plan.kr);
   c->kz = at<double>(c->ws, plan.kz);
   c->kd = at<double>(c->ws, plan.kd);
@@ -779,40 +839,51 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
   auto hip = [&](hipError_t e, const char* what) {
     if (e != hipSuccess && rc == MG_OK) rc = fail(MG_EHIP, "%s: %s", what, hipGetErrorString(e));
   };
-  hip(hipMemsetAsync(c->counters, 0, 16 * sizeof(long long), s), "hipMemsetAsync(counters)");
+  const bool mixed = (flags & MG_MIXED) != 0;
   Level& f0 = c->lv[0];
+  int* counts = reinterpret_cast<int*>(c->partials);   // 3 x nparts: fits the four sets of doubles
+  int nparts = 0;
+  // FP32 copies of a grid's faces, written as the faces are formed; not by the density
+  // coarsening, which forms them again at the end
+  auto f32_faces = [&](const Level& a) {
+    return mixed && !density ? mg::F32Faces{a.bx32, a.by32, a.bz32} : mg::F32Faces{};
+  };
   if (rho) {
     // density form of the finest coefficients, read by the finest-grid passes in place
-    // of the three face arrays
+    // of the three face arrays; the FP32 cycles form their finest faces from an FP32 copy
+    // (grids swept out of place, so that smoother and residual use the same FP32 operator),
+    // and then never read FP32 face arrays there
     f0.rt = at<double>(c->ws, plan.lv[0].rt);
+    f0.rt32 = at<float>(c->ws, plan.lv[0].rt32);
+    if (f0.rt32 && !out_of_place_sweeps(f0.q))
+      return cleanup(fail(MG_EINVAL, "internal: FP32 density copy below 64^3"));
     if (density) {
       // open-face areas into the workspace, then validation and activity without
       // rewriting them, then the density form
       hip(mg::launch_coeffs_from_rho(nullptr, mask, f0.q, f0.bx, f0.by, f0.bz, s), "coeffs_from_rho");
-      hip(mg::launch_setup_fine(f0.bx, f0.by, f0.bz, mask, f0.q, nullptr, nullptr, nullptr, f0.mask, c->counters, s),
+      hip(mg::launch_setup_fine(f0.bx, f0.by, f0.bz, mask, f0.q, nullptr, nullptr, nullptr, f0.mask, {}, counts,
+                                &nparts, s),
           "setup_fine");
       hip(mg::launch_rho_tilde(rho, f0.mask, f0.q, f0.rt, s), "rho_tilde");
+      if (f0.rt32) hip(mg::launch_to_f32(f0.rt, f0.rt32, cells(f0), s), "to_f32(rt)");
     } else {
       // face products, validation, activity and the density form in one pass
-      hip(mg::launch_setup_from_rho(rho, mask, f0.q, f0.bx, f0.by, f0.bz, f0.mask, f0.rt, c->counters, s),
+      hip(mg::launch_setup_from_rho(rho, mask, f0.q, f0.bx, f0.by, f0.bz, f0.mask, f0.rt, f0.rt32,
+                                    f0.rt32 ? mg::F32Faces{} : f32_faces(f0), counts, &nparts, s),
           "setup_from_rho");
     }
   } else {
-    hip(mg::launch_setup_fine(bx, by, bz, mask, f0.q, f0.bx, f0.by, f0.bz, f0.mask, c->counters, s), "setup_fine");
+    hip(mg::launch_setup_fine(bx, by, bz, mask, f0.q, f0.bx, f0.by, f0.bz, f0.mask, f32_faces(f0), counts, &nparts, s),
+        "setup_fine");
   }
-  if (rho) {
-    if (plan.lv[0].rt32 != mg::kAbsent) {
-      // the FP32 cycles form their finest faces from an FP32 copy (grids swept out of place,
-      // so that smoother and residual use the same FP32 operator)
-      if (!out_of_place_sweeps(f0.q)) return cleanup(fail(MG_EINVAL, "internal: FP32 density copy below 64^3"));
-      f0.rt32 = at<float>(c->ws, plan.lv[0].rt32);
-      hip(mg::launch_to_f32(f0.rt, f0.rt32, cells(f0), s), "to_f32(rt)");
-    }
-  }
-  for (int l = 1; l < c->L; ++l) {
+  // the coarse grids; those below 16^3 come out of the last launch, except where the faces
+  // are formed again on every grid
+  int top = 0;   // the first grid of that launch
+  while (c->lv[top].n > (density ? mg::kCoarsest : mg::kCoarseCycleMaxN)) ++top;
+  for (int l = 1; l <= top; ++l) {
     const Level& a = c->lv[l - 1];
     Level& b = c->lv[l];
-    hip(mg::launch_coarsen(a.bx, a.by, a.bz, a.mask, b.q, b.bx, b.by, b.bz, b.mask, s), "coarsen");
+    hip(mg::launch_coarsen(a.bx, a.by, a.bz, a.mask, b.q, b.bx, b.by, b.bz, b.mask, f32_faces(b), s), "coarsen");
   }
   if (density) {
     // the coarsening section 3.1 rejects: density restricted cell centre to cell centre
@@ -825,42 +896,44 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
       Level& a = c->lv[l];
       hip(mg::launch_area_to_beta(l == 0 ? rho : a.t, a.q, a.bx, a.by, a.bz, s), "area_to_beta");
     }
-  }
-  if (flags & MG_MIXED) {
-    // (a finest grid with an FP32 density copy never reads its FP32 face arrays)
-    for (int l = f0.rt32 ? 1 : 0; l < c->L; ++l) {
+    for (int l = f0.rt32 ? 1 : 0; mixed && l < c->L; ++l) {
       const Level& a = c->lv[l];
       hip(mg::launch_to_f32(a.bx, a.bx32, cells(a), s), "to_f32");
       hip(mg::launch_to_f32(a.by, a.by32, cells(a), s), "to_f32");
       hip(mg::launch_to_f32(a.bz, a.bz32, cells(a), s), "to_f32");
     }
   }
-  // coarsest operator to the host, FP64 pseudo-inverse back to the device
   const Level& cl = c->lv[c->L - 1];
-  const int nc = static_cast<int>(cells(cl));
-  std::vector<double> hbx(nc), hby(nc), hbz(nc), A, P;
-  std::vector<uint8_t> hm(nc);
-  long long cnt[3] = {0, 0, 0};
-  hip(hipMemcpyAsync(hbx.data(), cl.bx, nc * sizeof(double), hipMemcpyDeviceToHost, s), "copy coarse bx");
-  hip(hipMemcpyAsync(hby.data(), cl.by, nc * sizeof(double), hipMemcpyDeviceToHost, s), "copy coarse by");
-  hip(hipMemcpyAsync(hbz.data(), cl.bz, nc * sizeof(double), hipMemcpyDeviceToHost, s), "copy coarse bz");
-  hip(hipMemcpyAsync(hm.data(), cl.mask, nc, hipMemcpyDeviceToHost, s), "copy coarse mask");
-  hip(hipMemcpyAsync(cnt, c->counters, sizeof cnt, hipMemcpyDeviceToHost, s), "copy counters");
-  hip(hipStreamSynchronize(s), "hipStreamSynchronize(setup)");
+  mg::CoarseSetup cs{};
+  cs.nlev = c->L - top;
+  for (int l = top; l < c->L; ++l) {
+    const Level& a = c->lv[l];
+    const mg::F32Faces f = f32_faces(a);
+    cs.g[l - top] = {a.bx, a.by, a.bz, a.mask, f.bx, f.by, f.bz};
+  }
+  cs.inv_h2 = 1.0 / (cl.h * cl.h);
+  cs.parts = counts;
+  cs.nparts = nparts;
+  cs.pinv = c->pinv;
+  cs.pub.host = c->host;
+  cs.pub.ticket = ticket_of(c);
+  cs.pub.value = c->published + 1;
+  if (rc == MG_OK) hip(mg::launch_coarse_setup(cs, s), "coarse_setup");
+  if (rc != MG_OK) return cleanup(rc);
+  c->published = cs.pub.value;
+  double cnt[4];
+  rc = wait_scalars(c, cnt, 4);
   if (rc != MG_OK) return cleanup(rc);
   if (cnt[0] > 0)
-    return cleanup(fail(MG_EINVAL, "%lld face coefficients are negative or not finite%s", cnt[0],
+    return cleanup(fail(MG_EINVAL, "%lld face coefficients are negative or not finite%s", static_cast<long long>(cnt[0]),
                         rho ? " (density must be positive and finite in fluid cells)" : ""));
   if (cnt[1] == 0) return cleanup(fail(MG_EINVAL, "no fluid cell has an open face"));
-  c->active = cnt[1];
-  c->dropped = cnt[2];
-  coarse_dense(hbx, hby, hbz, hm, cl.n, cl.h, A);
-  // the null space is known exactly from the graph; eigendecomposition only as fallback
-  if (!mg::graph_pinv(nc, A, coarse_components(hbx, hby, hbz, hm, cl.n), 1e-14, P))
-    mg::symmetric_pinv(nc, A, kPinvRtol, P);
-  hip(hipMemcpyAsync(c->pinv, P.data(), P.size() * sizeof(double), hipMemcpyHostToDevice, s), "upload pinv");
-  hip(hipStreamSynchronize(s), "hipStreamSynchronize(pinv)");
-  if (rc != MG_OK) return cleanup(rc);
+  c->active = static_cast<long long>(cnt[1]);
+  c->dropped = static_cast<long long>(cnt[2]);
+  if (cnt[3] != 0) {
+    rc = host_pinv(c, cl);
+    if (rc != MG_OK) return cleanup(rc);
+  }
   *out = c;
   return MG_OK;
 }
@@ -1304,14 +1377,10 @@ int mg_project(mg_ctx* ctx, double* ux, double* uy, double* uz, const double* rx
 void mg_destroy(mg_ctx* ctx) {
   if (!ctx) return;
   for (mg_ctx* lane : ctx->lanes) mg_destroy(lane);
+  free_host(ctx);   // (before its stream goes)
   if (ctx->own_stream && ctx->stream) {
     (void)hipStreamSynchronize(ctx->stream);
     (void)hipStreamDestroy(ctx->stream);
-  }
-  if (ctx->host) {
-    // a solve that ended on an error may have scalars still on their way
-    if (*ticket_of(ctx) < ctx->published) (void)hipStreamSynchronize(ctx->stream);
-    (void)hipHostFree(ctx->host);
   }
   if (ctx->order_event) (void)hipEventDestroy(ctx->order_event);
   delete ctx;

@@ -63,6 +63,16 @@ __device__ __forceinline__ float gs_quotient(float n, float d) {
   return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
 }
 
+// Device scalars handed to the host by the kernel that forms the last of them: scal[0 ..
+// count) written to host, then value to *ticket (both in coherent pinned memory).
+struct Publish {
+  double* host = nullptr;
+  const double* scal = nullptr;
+  int count = 0;   // at most 64
+  unsigned long long* ticket = nullptr;
+  unsigned long long value = 0;
+};
+
 // ---- setup --------------------------------------------------------------------
 // beta_f = o_f 2/(rho_L + rho_R); with rho == nullptr the open-face areas o_f (0 or 1)
 hipError_t launch_coeffs_from_rho(const double* rho, const uint8_t* mask, int q,
@@ -75,17 +85,42 @@ hipError_t launch_rho_tilde(const double* rho, const uint8_t* mask, int q, doubl
 hipError_t launch_restrict_rho(const double* rho, const uint8_t* mask, int qc, double* crho, hipStream_t s);
 // beta = area * 2/(rho_L + rho_R) in place on the open faces
 hipError_t launch_area_to_beta(const double* rho, int q, double* bx, double* by, double* bz, hipStream_t s);
-// counters[0] += non-finite or negative beta values, [1] += active cells, [2] += dropped;
-// bx == nullptr: validate and mark only (the coefficients are already closed in place)
+// counts: three ints per block, counts[x nparts + block] with x = 0 the non-finite or
+// negative beta values, 1 the active cells, 2 the dropped ones (nparts <= kNumPartials, for
+// launch_coarse_setup); bx == nullptr: validate and mark only (the coefficients are already
+// closed in place).  F32Faces: FP32 copies of the faces too (null: none).
+struct F32Faces {
+  float *bx = nullptr, *by = nullptr, *bz = nullptr;
+};
 hipError_t launch_setup_fine(const double* ubx, const double* uby, const double* ubz,
                              const uint8_t* umask, int q, double* bx, double* by, double* bz,
-                             uint8_t* mask, long long* counters, hipStream_t s);
+                             uint8_t* mask, F32Faces f32, int* counts, int* nparts, hipStream_t s);
 // the three above for a hierarchy built from rho, in one pass: face products, their
-// validation and the active cells (counters as launch_setup_fine), and rt
+// validation and the active cells (counts as launch_setup_fine), and rt (rt32: an FP32 copy)
 hipError_t launch_setup_from_rho(const double* rho, const uint8_t* umask, int q, double* bx, double* by, double* bz,
-                                 uint8_t* mask, double* rt, long long* counters, hipStream_t s);
+                                 uint8_t* mask, double* rt, float* rt32, F32Faces f32, int* counts, int* nparts,
+                                 hipStream_t s);
 hipError_t launch_coarsen(const double* bx, const double* by, const double* bz, const uint8_t* mask,
-                          int qc, double* cbx, double* cby, double* cbz, uint8_t* cmask, hipStream_t s);
+                          int qc, double* cbx, double* cby, double* cbz, uint8_t* cmask, F32Faces f32, hipStream_t s);
+// The rest of a setup in one single-workgroup launch: grid 0 (16^3, 8^3 or 4^3: nlev 3, 2
+// or 1) is there; the ones below it are coarsened from it, the pseudo-inverse of the 4^3
+// operator is formed, and pub.host receives the sums of the three counts and 1 if the
+// elimination failed (else 0).
+struct CoarseSetup {
+  struct Grid {
+    double *bx, *by, *bz;
+    uint8_t* mask;
+    float *bx32, *by32, *bz32;   // FP32 copies (null: none)
+  };
+  int nlev;
+  Grid g[3];
+  double inv_h2;   // of the 4^3 grid
+  const int* parts;
+  int nparts;
+  double* pinv;
+  Publish pub;
+};
+hipError_t launch_coarse_setup(const CoarseSetup& a, hipStream_t s);
 hipError_t launch_to_f32(const double* src, float* dst, long long count, hipStream_t s);
 
 // ---- cut cells (setup) ---------------------------------------------------------
@@ -261,15 +296,6 @@ hipError_t launch_fcg_dir(const double* z64, const float* z32, const double* d, 
 // mode 0: partials = sum_active x ; mode 1: sum_active (x - *shift)^2
 hipError_t launch_masked_sum(const double* x, const uint8_t* mask, int q, int mode, const double* shift,
                              double* partials, int* nblocks, hipStream_t s);
-// Device scalars handed to the host by the kernel that forms the last of them: scal[0 ..
-// count) written to host, then value to *ticket (both in coherent pinned memory).
-struct Publish {
-  double* host = nullptr;
-  const double* scal = nullptr;
-  int count = 0;   // at most 64
-  unsigned long long* ticket = nullptr;
-  unsigned long long value = 0;
-};
 // out[0] = scale * sum(partials[0..nparts))  (single block, fixed order)
 hipError_t launch_reduce_final(const double* partials, int nparts, double scale, double* out, hipStream_t s,
                                const Publish* pub = nullptr);

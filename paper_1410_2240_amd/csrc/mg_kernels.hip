@@ -255,15 +255,30 @@ __global__ __launch_bounds__(kBlock) void k_area_to_beta(const double* __restric
   if (az != 0.0) bz[c] = az * face_beta(rho[c], rho[c - (1 << (2 * q))]);
 }
 
+// A block's three counts, each a partial one for the setup's last kernel to add up (no
+// counter to clear beforehand, no atomics).
+__device__ __forceinline__ void block_counts(int bad, int active, int dropped, int* __restrict__ counts) {
+  __shared__ int red[3][kBlock / 64];
+  int v[3] = {bad, active, dropped};
+  for (int x = 0; x < 3; ++x)
+    for (int off = 32; off > 0; off >>= 1) v[x] += __shfl_xor(v[x], off, 64);
+  if ((threadIdx.x & 63) == 0)
+    for (int x = 0; x < 3; ++x) red[x][threadIdx.x >> 6] = v[x];
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    int sum = 0;
+    for (int w = 0; w < kBlock / 64; ++w) sum += red[threadIdx.x][w];
+    counts[threadIdx.x * gridDim.x + blockIdx.x] = sum;
+  }
+}
+
 // Close the finest faces (copy unless bx is null), validate them, mark active cells.
-// Grid-stride over cells with a bounded block count, so the three counters take few
-// atomic adds.
 __global__ __launch_bounds__(kBlock) void k_setup_fine(const double* __restrict__ ubx, const double* __restrict__ uby,
                                                        const double* __restrict__ ubz,
                                                        const uint8_t* __restrict__ umask, int q,
                                                        double* __restrict__ bx, double* __restrict__ by,
                                                        double* __restrict__ bz, uint8_t* __restrict__ mask,
-                                                       long long* __restrict__ counters) {
+                                                       F32Faces f32, int* __restrict__ counts) {
   const int n = 1 << q, m = n - 1;
   const int total = 1 << (3 * q);
   const int nn = 1 << (2 * q);
@@ -287,25 +302,17 @@ __global__ __launch_bounds__(kBlock) void k_setup_fine(const double* __restrict_
       by[c] = ym;
       bz[c] = zm;
     }
+    if (f32.bx) {
+      f32.bx[c] = static_cast<float>(xm);
+      f32.by[c] = static_cast<float>(ym);
+      f32.bz[c] = static_cast<float>(zm);
+    }
     const bool act = mc && (xm + xp + ym + yp + zm + zp) > 0.0;
     mask[c] = act ? 1 : 0;
     active += act;
     dropped += mc && !act;
   }
-  __shared__ int red[3][kBlock / 64];
-  int v[3] = {bad, active, dropped};
-  for (int x = 0; x < 3; ++x)
-    for (int off = 32; off > 0; off >>= 1) v[x] += __shfl_xor(v[x], off, 64);
-  if ((threadIdx.x & 63) == 0)
-    for (int x = 0; x < 3; ++x) red[x][threadIdx.x >> 6] = v[x];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int x = 0; x < 3; ++x) {
-      long long sum = 0;
-      for (int w = 0; w < kBlock / 64; ++w) sum += red[x][w];
-      if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(&counters[x]), static_cast<unsigned long long>(sum));
-    }
-  }
+  block_counts(bad, active, dropped, counts);
 }
 
 // The finest grid of a hierarchy built from rho in one pass: the face products
@@ -318,7 +325,8 @@ __global__ __launch_bounds__(kBlock) void k_setup_from_rho(const double* __restr
                                                            const uint8_t* __restrict__ umask, int q,
                                                            double* __restrict__ bx, double* __restrict__ by,
                                                            double* __restrict__ bz, uint8_t* __restrict__ mask,
-                                                           double* __restrict__ rt, long long* __restrict__ counters) {
+                                                           double* __restrict__ rt, float* __restrict__ rt32,
+                                                           F32Faces f32, int* __restrict__ counts) {
   const int n = 1 << q, m = n - 1;
   const int total = 1 << (3 * q);
   const int nn = 1 << (2 * q);
@@ -340,26 +348,20 @@ __global__ __launch_bounds__(kBlock) void k_setup_from_rho(const double* __restr
     bx[c] = xm;
     by[c] = ym;
     bz[c] = zm;
+    if (f32.bx) {
+      f32.bx[c] = static_cast<float>(xm);
+      f32.by[c] = static_cast<float>(ym);
+      f32.bz[c] = static_cast<float>(zm);
+    }
     const bool act = mc && (xm + xp + ym + yp + zm + zp) > 0.0;
     mask[c] = act ? 1 : 0;
-    rt[c] = act ? rc : __builtin_huge_val();
+    const double r = act ? rc : __builtin_huge_val();
+    rt[c] = r;
+    if (rt32) rt32[c] = static_cast<float>(r);
     active += act;
     dropped += mc && !act;
   }
-  __shared__ int red[3][kBlock / 64];
-  int v[3] = {bad, active, dropped};
-  for (int x = 0; x < 3; ++x)
-    for (int off = 32; off > 0; off >>= 1) v[x] += __shfl_xor(v[x], off, 64);
-  if ((threadIdx.x & 63) == 0)
-    for (int x = 0; x < 3; ++x) red[x][threadIdx.x >> 6] = v[x];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int x = 0; x < 3; ++x) {
-      long long sum = 0;
-      for (int w = 0; w < kBlock / 64; ++w) sum += red[x][w];
-      if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(&counters[x]), static_cast<unsigned long long>(sum));
-    }
-  }
+  block_counts(bad, active, dropped, counts);
 }
 
 // Coarse face = mean of the 4 fine faces it covers; coarse cell active if any child is
@@ -367,7 +369,8 @@ __global__ __launch_bounds__(kBlock) void k_setup_from_rho(const double* __restr
 __global__ __launch_bounds__(kBlock) void k_coarsen(const double* __restrict__ bx, const double* __restrict__ by,
                                                     const double* __restrict__ bz, const uint8_t* __restrict__ mask,
                                                     int qc, double* __restrict__ cbx, double* __restrict__ cby,
-                                                    double* __restrict__ cbz, uint8_t* __restrict__ cmask) {
+                                                    double* __restrict__ cbz, uint8_t* __restrict__ cmask,
+                                                    F32Faces f32) {
   const int nc = 1 << qc, mc = nc - 1, q = qc + 1, mf = (1 << q) - 1;
   const long long t = static_cast<long long>(blockIdx.x) * kBlock + threadIdx.x;
   if (t >= (1LL << (3 * qc))) return;
@@ -393,6 +396,11 @@ __global__ __launch_bounds__(kBlock) void k_coarsen(const double* __restrict__ b
   cbx[C] = xm;
   cby[C] = ym;
   cbz[C] = zm;
+  if (f32.bx) {
+    f32.bx[C] = static_cast<float>(xm);
+    f32.by[C] = static_cast<float>(ym);
+    f32.bz[C] = static_cast<float>(zm);
+  }
   bool any = false;
   for (int d = 0; d < 8; ++d) any |= mask[cell(i + (d & 1), j + ((d >> 1) & 1), k + (d >> 2), q)] != 0;
   cmask[C] = (any && (xm + xp + ym + yp + zm + zp) > 0.0) ? 1 : 0;
@@ -938,17 +946,20 @@ hipError_t launch_coeffs_from_rho(const double* rho, const uint8_t* mask, int q,
 }
 
 hipError_t launch_setup_fine(const double* ubx, const double* uby, const double* ubz, const uint8_t* umask, int q,
-                             double* bx, double* by, double* bz, uint8_t* mask, long long* counters,
+                             double* bx, double* by, double* bz, uint8_t* mask, F32Faces f32, int* counts, int* nparts,
                              hipStream_t s) {
-  hipLaunchKernelGGL(k_setup_fine, dim3(reduction_blocks(1LL << (3 * q))), dim3(kBlock), 0, s, ubx, uby, ubz, umask, q,
-                     bx, by, bz, mask, counters);
+  *nparts = reduction_blocks(1LL << (3 * q));
+  hipLaunchKernelGGL(k_setup_fine, dim3(*nparts), dim3(kBlock), 0, s, ubx, uby, ubz, umask, q, bx, by, bz, mask, f32,
+                     counts);
   return hipGetLastError();
 }
 
 hipError_t launch_setup_from_rho(const double* rho, const uint8_t* umask, int q, double* bx, double* by, double* bz,
-                                 uint8_t* mask, double* rt, long long* counters, hipStream_t s) {
-  hipLaunchKernelGGL(k_setup_from_rho, dim3(reduction_blocks(1LL << (3 * q))), dim3(kBlock), 0, s, rho, umask, q, bx,
-                     by, bz, mask, rt, counters);
+                                 uint8_t* mask, double* rt, float* rt32, F32Faces f32, int* counts, int* nparts,
+                                 hipStream_t s) {
+  *nparts = reduction_blocks(1LL << (3 * q));
+  hipLaunchKernelGGL(k_setup_from_rho, dim3(*nparts), dim3(kBlock), 0, s, rho, umask, q, bx, by, bz, mask, rt, rt32,
+                     f32, counts);
   return hipGetLastError();
 }
 
@@ -968,9 +979,9 @@ hipError_t launch_area_to_beta(const double* rho, int q, double* bx, double* by,
 }
 
 hipError_t launch_coarsen(const double* bx, const double* by, const double* bz, const uint8_t* mask, int qc,
-                          double* cbx, double* cby, double* cbz, uint8_t* cmask, hipStream_t s) {
+                          double* cbx, double* cby, double* cbz, uint8_t* cmask, F32Faces f32, hipStream_t s) {
   hipLaunchKernelGGL(k_coarsen, dim3(grid_for(1LL << (3 * qc))), dim3(kBlock), 0, s, bx, by, bz, mask, qc, cbx, cby,
-                     cbz, cmask);
+                     cbz, cmask, f32);
   return hipGetLastError();
 }
 

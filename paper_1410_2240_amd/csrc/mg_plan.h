@@ -62,7 +62,7 @@ struct Plan {
   size_t pinv = 0;       // (4^3)^2 doubles: pseudo-inverse of the coarsest operator
   size_t partials = 0;   // kPartialSets x kNumPartials doubles
   size_t scalars = 0;    // 32 doubles of device scalars
-  size_t counters = 0;   // 16 int64 counters (setup validation and counts)
+  size_t counters = 0;   // 16 int64 words, not in use (a setup adds its counts up in partials)
   size_t total = 0;      // bytes
 };
 

@@ -478,6 +478,211 @@ __global__ __launch_bounds__(kTailThreads) void k_coarse_cycle(CoarseCycle<T> a)
   t.store_e();
 }
 
+// ---------------------------------------------------------------------------- setup
+
+// The grids below 16^3 and the 4^3 pseudo-inverse, by one workgroup in one launch: the
+// face products coarsened to 8^3 and 4^3 as k_coarsen does, the setup's counts added up,
+// and A^+ of the 4^3 operator.  Its null space is known: the constant on each connected
+// fluid region and one unit vector per inactive cell.  With Z that orthonormal basis,
+// M = Z Z^T - A is symmetric positive definite and A^+ = Z Z^T - M^-1; M^-1 comes from
+// Gauss-Jordan elimination in place, whose pivots need no exchange in a definite matrix.
+// Lane r of wave w holds M's row r in columns 8w .. 8w+7, so a pivot row is a broadcast
+// within each wave and only the pivot column goes through LDS, with one barrier per pivot.
+// A pivot that is not positive is reported; the host then takes its own way.
+// The launch takes 32 us; the elimination on the host, with the copies to it and back and
+// a launch per grid and array before it, held every setup to 310 us at the least (68 now).
+struct SetupLds {
+  double x8[512], y8[512], z8[512];
+  double x4[64], y4[64], z4[64];
+  uint8_t m8[512], m4[64];
+  double col[2][64], tiny;
+  int comp[64], size[64];
+  long long count[3][kTailThreads / 64];
+};
+
+// coarse cell (I, J, K) of the grid of edge 2^qc from the fine grid's accessors: its low
+// faces and activity (k_coarsen's arithmetic)
+template <typename BX, typename BY, typename BZ, typename M>
+__device__ __forceinline__ void coarsen_cell(int qc, int I, int J, int K, BX bx, BY by, BZ bz, M mask, double& xm,
+                                             double& ym, double& zm, bool& act) {
+  const int mf = (2 << qc) - 1, mc = (1 << qc) - 1, i = 2 * I, j = 2 * J, k = 2 * K;
+  auto fx = [&](int ii) { return 0.25 * (bx(ii, j, k) + bx(ii, j + 1, k) + bx(ii, j, k + 1) + bx(ii, j + 1, k + 1)); };
+  auto fy = [&](int jj) { return 0.25 * (by(i, jj, k) + by(i + 1, jj, k) + by(i, jj, k + 1) + by(i + 1, jj, k + 1)); };
+  auto fz = [&](int kk) { return 0.25 * (bz(i, j, kk) + bz(i + 1, j, kk) + bz(i, j + 1, kk) + bz(i + 1, j + 1, kk)); };
+  xm = fx(i);
+  ym = fy(j);
+  zm = fz(k);
+  const double xp = fx((i + 2) & mf), yp = fy((j + 2) & mf), zp = K < mc ? fz(k + 2) : 0.0;
+  bool any = false;
+#pragma unroll
+  for (int d = 0; d < 8; ++d) any |= mask(i + (d & 1), j + ((d >> 1) & 1), k + (d >> 2));
+  act = any && (xm + xp + ym + yp + zm + zp) > 0.0;
+}
+
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = __builtin_amdgcn_readlane(static_cast<unsigned>(b), lane);
+  const unsigned hi = __builtin_amdgcn_readlane(static_cast<unsigned>(b >> 32), lane);
+  return __builtin_bit_cast(double, (static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
+__global__ __launch_bounds__(kTailThreads) void k_coarse_setup(CoarseSetup a) {
+  __shared__ SetupLds s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int last = a.nlev - 1;
+  auto keep = [](const CoarseSetup::Grid& g, int c, double xm, double ym, double zm, bool act) {
+    g.bx[c] = xm;
+    g.by[c] = ym;
+    g.bz[c] = zm;
+    g.mask[c] = act ? 1 : 0;
+    if (g.bx32) {
+      g.bx32[c] = static_cast<float>(xm);
+      g.by32[c] = static_cast<float>(ym);
+      g.bz32[c] = static_cast<float>(zm);
+    }
+  };
+  // ---- the counts of the finest grid's setup, a set of partial ones per block
+  long long cnt[3] = {0, 0, 0};
+#pragma unroll
+  for (int x = 0; x < 3; ++x)
+    for (int b = tid; b < a.nparts; b += kTailThreads) cnt[x] += a.parts[x * a.nparts + b];
+#pragma unroll
+  for (int x = 0; x < 3; ++x) {
+    for (int off = 32; off > 0; off >>= 1) cnt[x] += __shfl_xor(cnt[x], off, 64);
+    if (lane == 0) s.count[x][wave] = cnt[x];
+  }
+  // ---- 16^3 -> 8^3, or the 8^3 grid as it is
+  if (a.nlev == 3) {
+    const CoarseSetup::Grid& g = a.g[0];
+    auto at = [](int i, int j, int k) { return (k << 8) + (j << 4) + i; };
+    double xm, ym, zm;
+    bool act;
+    coarsen_cell(
+        3, tid & 7, (tid >> 3) & 7, tid >> 6, [&](int i, int j, int k) { return g.bx[at(i, j, k)]; },
+        [&](int i, int j, int k) { return g.by[at(i, j, k)]; }, [&](int i, int j, int k) { return g.bz[at(i, j, k)]; },
+        [&](int i, int j, int k) { return g.mask[at(i, j, k)] != 0; }, xm, ym, zm, act);
+    keep(a.g[1], tid, xm, ym, zm, act);
+    s.x8[tid] = xm;
+    s.y8[tid] = ym;
+    s.z8[tid] = zm;
+    s.m8[tid] = act;
+  } else if (a.nlev == 2) {
+    const CoarseSetup::Grid& g = a.g[0];
+    s.x8[tid] = g.bx[tid];
+    s.y8[tid] = g.by[tid];
+    s.z8[tid] = g.bz[tid];
+    s.m8[tid] = g.mask[tid] != 0;
+  }
+  __syncthreads();
+  // ---- 8^3 -> 4^3, or the 4^3 grid as it is
+  if (tid < 64) {
+    if (a.nlev > 1) {
+      auto at = [](int i, int j, int k) { return (k << 6) + (j << 3) + i; };
+      double xm, ym, zm;
+      bool act;
+      coarsen_cell(
+          2, tid & 3, (tid >> 2) & 3, tid >> 4, [&](int i, int j, int k) { return s.x8[at(i, j, k)]; },
+          [&](int i, int j, int k) { return s.y8[at(i, j, k)]; }, [&](int i, int j, int k) { return s.z8[at(i, j, k)]; },
+          [&](int i, int j, int k) { return s.m8[at(i, j, k)] != 0; }, xm, ym, zm, act);
+      keep(a.g[last], tid, xm, ym, zm, act);
+      s.x4[tid] = xm;
+      s.y4[tid] = ym;
+      s.z4[tid] = zm;
+      s.m4[tid] = act;
+    } else {
+      const CoarseSetup::Grid& g = a.g[last];
+      s.x4[tid] = g.bx[tid];
+      s.y4[tid] = g.by[tid];
+      s.z4[tid] = g.bz[tid];
+      s.m4[tid] = g.mask[tid] != 0;
+    }
+    s.size[tid] = 0;
+  }
+  __syncthreads();
+  // ---- row `lane` of A: neighbours and faces (every wave the same)
+  const int i = lane & 3, j = (lane >> 2) & 3, k = lane >> 4;
+  const bool act = s.m4[lane] != 0;
+  const int nb[6] = {lane - i + ((i + 3) & 3),        lane - i + ((i + 1) & 3),
+                     lane + 4 * (((j + 3) & 3) - j),  lane + 4 * (((j + 1) & 3) - j),
+                     k > 0 ? lane - 16 : lane,        k < 3 ? lane + 16 : lane};
+  double b[6] = {s.x4[lane], s.x4[nb[1]], s.y4[lane], s.y4[nb[3]], k > 0 ? s.z4[lane] : 0.0, k < 3 ? s.z4[nb[5]] : 0.0};
+#pragma unroll
+  for (int f = 0; f < 6; ++f) b[f] = act ? b[f] * a.inv_h2 : 0.0;
+  double diag = 0.0;
+#pragma unroll
+  for (int f = 0; f < 6; ++f) diag -= b[f];
+  if (wave == 0) {
+    // connected regions of the active cells over open faces: the lowest cell of each
+    int lab = act ? lane : -1;
+    for (int round = 0; round < 64; ++round) {
+      int low = lab;
+#pragma unroll
+      for (int f = 0; f < 6; ++f) {
+        const int other = __shfl(lab, nb[f], 64);
+        if (act && b[f] > 0.0 && other >= 0) low = min(low, other);
+      }
+      const bool moved = low != lab;
+      lab = low;
+      if (!__any(moved)) break;
+    }
+    s.comp[lane] = lab;
+    if (lab >= 0) atomicAdd(&s.size[lab], 1);
+    double big = fabs(diag);
+    for (int off = 32; off > 0; off >>= 1) big = fmax(big, __shfl_xor(big, off, 64));
+    if (lane == 0) s.tiny = 1e-14 * fmax(big, 1.0);
+  }
+  __syncthreads();
+  const int own = s.comp[lane];
+  const double share = own >= 0 ? 1.0 / s.size[own] : 0.0;
+  const double tiny = s.tiny;
+  double zz[8], m[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const int cc = wave * 8 + c;
+    zz[c] = own >= 0 ? (s.comp[cc] == own ? share : 0.0) : (cc == lane ? 1.0 : 0.0);
+    double v = 0.0;
+#pragma unroll
+    for (int f = 0; f < 6; ++f)
+      if (nb[f] == cc) v += b[f];
+    if (cc == lane) v = diag;
+    m[c] = zz[c] - v;
+  }
+  bool bad = false;
+  for (int kb = 0; kb < 8; ++kb) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const int kp = kb * 8 + kk;
+      if (wave == kb) s.col[kk & 1][lane] = m[kk];
+      __syncthreads();
+      const double p = s.col[kk & 1][kp], ci = s.col[kk & 1][lane];
+      bad |= !(p > tiny);
+      double inv = __builtin_amdgcn_rcp(p);   // two Newton steps: within an ulp, half the division's chain
+      inv = __builtin_fma(inv, __builtin_fma(-p, inv, 1.0), inv);
+      inv = __builtin_fma(inv, __builtin_fma(-p, inv, 1.0), inv);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const double rk = from_lane(m[c], kp) * inv;
+        m[c] = lane == kp ? rk : __builtin_fma(-ci, rk, m[c]);
+      }
+      if (wave == kb) m[kk] = lane == kp ? inv : -ci * inv;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) a.pinv[lane * 64 + wave * 8 + c] = zz[c] - m[c];
+  __syncthreads();   // every wave's stores are out before the ticket
+  if (tid == 0) {
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      long long t = 0;
+      for (int v = 0; v < kTailThreads / 64; ++v) t += s.count[x][v];
+      a.pub.host[x] = static_cast<double>(t);
+    }
+    a.pub.host[3] = bad ? 1.0 : 0.0;
+    __threadfence_system();
+    __hip_atomic_store(a.pub.ticket, a.pub.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 }  // namespace
 
 template <typename T>
@@ -488,6 +693,12 @@ hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s) {
     hipLaunchKernelGGL((k_coarse_cycle<T, false>), dim3(1), dim3(kTailThreads), 0, s, a);
   else
     return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_coarse_setup(const CoarseSetup& a, hipStream_t s) {
+  if (a.nlev < 1 || a.nlev > 3 || a.nparts < 0 || !a.pinv || !a.pub.host || !a.pub.ticket) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_coarse_setup, dim3(1), dim3(kTailThreads), 0, s, a);
   return hipGetLastError();
 }
 

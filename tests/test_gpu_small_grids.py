@@ -140,3 +140,58 @@ def test_single_workgroup_cycle(N, dtype, field):
     got = host(mg.vcycle(dev(kept), dev(f)))
     assert (got[~lev.mask.astype(bool)] == 7.0).all()
     assert maxrel(np.where(lev.mask, got, 0), want) <= (1e-4 if fp32 else 1e-12)
+
+
+@pytest.mark.parametrize("N", [8, 16, 32])
+@pytest.mark.parametrize("case", ["open", "regions", "contrast"])
+def test_setup_below_16_and_pseudo_inverse(N, case):
+    """The setup's last launch, from each of its top grids: every grid's coefficients and
+    mask against the oracle's, and the 4^3 solve against numpy's pseudo-inverse of the 4^3
+    operator: without a body, with the fluid in two regions (a solid plane) and with face
+    products over six decades.  The pseudo-inverse's error is its condition number (at most
+    about 4e8 here) times eps: 1e-6 of the largest value; the faces within 1e-13."""
+    from paper_1410_2240_amd import MG
+    contrast = 1e6 if case == "contrast" else 1000.0
+    bx, by, bz, mask = raw_problem(N, 70 + N, body=False, contrast=contrast)
+    if case == "regions":
+        mask[N // 2: N // 2 + N // 4] = 0   # a solid quarter: whole planes of the 4^3 grid
+    H = omg.setup(bx, by, bz, mask, 1.0 / N)
+    mg = MG(dev(bx), dev(by), dev(bz), dev(mask), mixed=True)
+    print(f"setup {N}^3 {case}", flush=True)
+    for l, lev in enumerate(H.levels):
+        gx, gy, gz, gm = (host(t) for t in mg.level_coeffs(l))
+        assert (gm.astype(bool) == lev.mask).all(), l
+        for got, want in ((gx, lev.bx), (gy, lev.by), (gz, lev.bz)):
+            assert maxrel(got, want) <= 1e-13, l
+    lev = H.levels[-1]
+    A = np.zeros((64, 64))
+    for c in range(64):
+        e = np.zeros(64)
+        e[c] = 1.0
+        A[:, c] = -omg.residual(e.reshape(4, 4, 4), np.zeros((4, 4, 4)), lev).ravel()
+    live = lev.mask.ravel()
+    f = np.where(live, np.random.default_rng(N).standard_normal(64), 0.0)
+    g = np.where(live, f - f[live].mean(), 0.0)
+    want = np.linalg.pinv(A, rcond=1e-13) @ g
+    got = host(mg.coarse_solve(dev(f.reshape(4, 4, 4)))).ravel()
+    assert np.abs(got - want).max() <= 1e-6 * np.abs(want).max()
+
+
+def test_more_contexts_than_read_back_slots():
+    """Seventy contexts at once (the pinned block has 64 slots): each solves, in any order
+    of destruction, and slots are used again."""
+    from paper_1410_2240_amd import MG
+    inp = fields.make("c2", 8)
+    rho, mask, f = dev(inp.rho), dev(inp.mask), dev(inp.f)
+    print("70 contexts", flush=True)
+    want, hist, _ = MG.from_rho(rho, mask).solve(f, tol=1e-8)
+    held = [MG.from_rho(rho, mask) for _ in range(70)]
+    for order in (held[::3], held[1::3]):
+        for mg in order:
+            p, h, _ = mg.solve(f, tol=1e-8)
+            assert h == hist and torch.equal(p, want)
+    del held[::2]
+    held += [MG.from_rho(rho, mask) for _ in range(20)]
+    for mg in held:
+        p, h, _ = mg.solve(f, tol=1e-8)
+        assert h == hist and torch.equal(p, want)
