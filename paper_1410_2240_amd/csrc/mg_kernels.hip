@@ -272,7 +272,47 @@ __device__ __forceinline__ void block_counts(int bad, int active, int dropped, i
   }
 }
 
-// Close the finest faces (copy unless bx is null), validate them, mark active cells.
+__device__ __forceinline__ bool valid_beta(double v) { return v >= 0.0 && v <= 1.7976931348623157e308; }
+
+__device__ __forceinline__ void put_f32(const F32Faces& f32, int c, double2 x, double2 y, double2 z) {
+  if (!f32.bx) return;
+  *reinterpret_cast<float2*>(f32.bx + c) = float2{static_cast<float>(x.x), static_cast<float>(x.y)};
+  *reinterpret_cast<float2*>(f32.by + c) = float2{static_cast<float>(y.x), static_cast<float>(y.y)};
+  *reinterpret_cast<float2*>(f32.bz + c) = float2{static_cast<float>(z.x), static_cast<float>(z.y)};
+}
+
+// The masks around an x-pair: its cells, the cells left and right of it, and the pairs
+// below and above in y and in z (0 beyond a z wall).
+struct PairMask {
+  bool l, c0, c1, r;
+  uchar2 ym, yp, zm, zp;
+};
+__device__ __forceinline__ PairMask pair_mask(const uint8_t* __restrict__ mask, int i, int j, int k, int q) {
+  const int m = (1 << q) - 1, c = cell(i, j, k, q), nn = 1 << (2 * q);
+  auto at = [&](int x) {   // the caller's mask: any address
+    uchar2 v;
+    __builtin_memcpy(&v, mask + x, sizeof v);
+    return v;
+  };
+  const uchar2 own = at(c);
+  PairMask M;
+  M.l = mask[cell((i - 1) & m, j, k, q)] != 0;
+  M.c0 = own.x != 0;
+  M.c1 = own.y != 0;
+  M.r = mask[cell((i + 2) & m, j, k, q)] != 0;
+  M.ym = at(cell(i, (j - 1) & m, k, q));
+  M.yp = at(cell(i, (j + 1) & m, k, q));
+  M.zm = k > 0 ? at(c - nn) : uchar2{0, 0};
+  M.zp = k < m ? at(c + nn) : uchar2{0, 0};
+  return M;
+}
+
+// Setup of the finest grid, an x-pair per thread and step with 16-byte accesses.  A cell is
+// active if it is fluid and has an open face; its high faces, which its neighbours store,
+// are looked at only where its low ones are all closed.
+//
+// From given face arrays: close them (copy unless bx is null), validate them, mark active
+// cells.
 __global__ __launch_bounds__(kBlock) void k_setup_fine(const double* __restrict__ ubx, const double* __restrict__ uby,
                                                        const double* __restrict__ ubz,
                                                        const uint8_t* __restrict__ umask, int q,
@@ -280,47 +320,46 @@ __global__ __launch_bounds__(kBlock) void k_setup_fine(const double* __restrict_
                                                        double* __restrict__ bz, uint8_t* __restrict__ mask,
                                                        F32Faces f32, int* __restrict__ counts) {
   const int n = 1 << q, m = n - 1;
-  const int total = 1 << (3 * q);
+  const int pairs = 1 << (3 * q - 1);
   const int nn = 1 << (2 * q);
   int bad = 0, active = 0, dropped = 0;
-  for (int c = blockIdx.x * kBlock + threadIdx.x; c < total; c += gridDim.x * kBlock) {
-    const int i = c & m, j = (c >> q) & m, k = c >> (2 * q);
-    const bool mc = umask[c] != 0;
-    const int cxm = cell((i - 1) & m, j, k, q), cxp = cell((i + 1) & m, j, k, q);
-    const int cym = cell(i, (j - 1) & m, k, q), cyp = cell(i, (j + 1) & m, k, q);
-    const double vx = ubx[c], vy = uby[c], vz = ubz[c];
-    bad += !(vx >= 0.0 && vx <= 1.7976931348623157e308) + !(vy >= 0.0 && vy <= 1.7976931348623157e308) +
-           !(vz >= 0.0 && vz <= 1.7976931348623157e308);
-    const double xm = (mc && umask[cxm]) ? vx : 0.0;
-    const double ym = (mc && umask[cym]) ? vy : 0.0;
-    const double zm = (k > 0 && mc && umask[c - nn]) ? vz : 0.0;
-    const double xp = (mc && umask[cxp]) ? ubx[cxp] : 0.0;
-    const double yp = (mc && umask[cyp]) ? uby[cyp] : 0.0;
-    const double zp = (k < m && mc && umask[c + nn]) ? ubz[c + nn] : 0.0;
+  for (int t = blockIdx.x * kBlock + threadIdx.x; t < pairs; t += gridDim.x * kBlock) {
+    const int i = 2 * (t & (m >> 1)), j = (t >> (q - 1)) & m, k = t >> (2 * q - 1);
+    const int c = cell(i, j, k, q);
+    const PairMask M = pair_mask(umask, i, j, k, q);
+    const double2 vx = ld2(ubx, c), vy = ld2(uby, c), vz = ld2(ubz, c);
+    bad += !valid_beta(vx.x) + !valid_beta(vy.x) + !valid_beta(vz.x) + !valid_beta(vx.y) + !valid_beta(vy.y) +
+           !valid_beta(vz.y);
+    const double2 xm{M.c0 && M.l ? vx.x : 0.0, M.c1 && M.c0 ? vx.y : 0.0};
+    const double2 ym{M.c0 && M.ym.x ? vy.x : 0.0, M.c1 && M.ym.y ? vy.y : 0.0};
+    const double2 zm{M.c0 && M.zm.x ? vz.x : 0.0, M.c1 && M.zm.y ? vz.y : 0.0};
     if (bx) {
-      bx[c] = xm;
-      by[c] = ym;
-      bz[c] = zm;
+      *reinterpret_cast<double2*>(bx + c) = xm;
+      *reinterpret_cast<double2*>(by + c) = ym;
+      *reinterpret_cast<double2*>(bz + c) = zm;
     }
-    if (f32.bx) {
-      f32.bx[c] = static_cast<float>(xm);
-      f32.by[c] = static_cast<float>(ym);
-      f32.bz[c] = static_cast<float>(zm);
-    }
-    const bool act = mc && (xm + xp + ym + yp + zm + zp) > 0.0;
-    mask[c] = act ? 1 : 0;
-    active += act;
-    dropped += mc && !act;
+    put_f32(f32, c, xm, ym, zm);
+    const int cr = cell((i + 2) & m, j, k, q), cy = cell(i, (j + 1) & m, k, q);
+    bool a0 = M.c0 && (xm.x > 0.0 || ym.x > 0.0 || zm.x > 0.0);
+    bool a1 = M.c1 && (xm.y > 0.0 || ym.y > 0.0 || zm.y > 0.0);
+    if (M.c0 && !a0)
+      a0 = (M.c1 && vx.y > 0.0) || (M.yp.x && uby[cy] > 0.0) || (M.zp.x && ubz[c + nn] > 0.0);
+    if (M.c1 && !a1)
+      a1 = (M.r && ubx[cr] > 0.0) || (M.yp.y && uby[cy + 1] > 0.0) || (M.zp.y && ubz[c + nn + 1] > 0.0);
+    *reinterpret_cast<uchar2*>(mask + c) =
+        uchar2{static_cast<unsigned char>(a0 ? 1 : 0), static_cast<unsigned char>(a1 ? 1 : 0)};
+    active += a0 + a1;
+    dropped += (M.c0 && !a0) + (M.c1 && !a1);
   }
   block_counts(bad, active, dropped, counts);
 }
 
-// The finest grid of a hierarchy built from rho in one pass: the face products
-// beta = 2 / (rho_L + rho_R) on faces between fluid cells (0 elsewhere and on the
-// bottom wall), their validation, the active cells (fluid with an open face) and the
-// density form rt (rho on active cells, +inf elsewhere).  The same values as
-// k_coeffs_from_rho, then k_setup_fine and k_rho_tilde: each face, the low ones stored
-// and the high ones summed into the diagonal, is face_beta of the same two densities.
+// From the density, in one pass: the face products beta = 2 / (rho_L + rho_R) on faces
+// between fluid cells (0 elsewhere and on the bottom wall), their validation, the active
+// cells and the density form rt (rho on active cells, +inf elsewhere).  The same values as
+// k_coeffs_from_rho, then k_setup_fine and k_rho_tilde: each face is face_beta of the same
+// two densities.  512^3: 1.39 ms (4.1 TB/s), 2.68 ms with a
+// cell per thread and all six of its faces formed.
 __global__ __launch_bounds__(kBlock) void k_setup_from_rho(const double* __restrict__ rho,
                                                            const uint8_t* __restrict__ umask, int q,
                                                            double* __restrict__ bx, double* __restrict__ by,
@@ -328,38 +367,41 @@ __global__ __launch_bounds__(kBlock) void k_setup_from_rho(const double* __restr
                                                            double* __restrict__ rt, float* __restrict__ rt32,
                                                            F32Faces f32, int* __restrict__ counts) {
   const int n = 1 << q, m = n - 1;
-  const int total = 1 << (3 * q);
+  const int pairs = 1 << (3 * q - 1);
   const int nn = 1 << (2 * q);
+  const double inf = __builtin_huge_val();
   int bad = 0, active = 0, dropped = 0;
-  auto ok = [](double v) { return v >= 0.0 && v <= 1.7976931348623157e308; };
-  for (int c = blockIdx.x * kBlock + threadIdx.x; c < total; c += gridDim.x * kBlock) {
-    const int i = c & m, j = (c >> q) & m, k = c >> (2 * q);
-    const bool mc = umask[c] != 0;
-    const int cxm = cell((i - 1) & m, j, k, q), cxp = cell((i + 1) & m, j, k, q);
-    const int cym = cell(i, (j - 1) & m, k, q), cyp = cell(i, (j + 1) & m, k, q);
-    const double rc = rho[c];
-    const double xm = (mc && umask[cxm]) ? face_beta(rc, rho[cxm]) : 0.0;
-    const double ym = (mc && umask[cym]) ? face_beta(rc, rho[cym]) : 0.0;
-    const double zm = (k > 0 && mc && umask[c - nn]) ? face_beta(rc, rho[c - nn]) : 0.0;
-    const double xp = (mc && umask[cxp]) ? face_beta(rho[cxp], rc) : 0.0;
-    const double yp = (mc && umask[cyp]) ? face_beta(rho[cyp], rc) : 0.0;
-    const double zp = (k < m && mc && umask[c + nn]) ? face_beta(rho[c + nn], rc) : 0.0;
-    bad += !ok(xm) + !ok(ym) + !ok(zm);
-    bx[c] = xm;
-    by[c] = ym;
-    bz[c] = zm;
-    if (f32.bx) {
-      f32.bx[c] = static_cast<float>(xm);
-      f32.by[c] = static_cast<float>(ym);
-      f32.bz[c] = static_cast<float>(zm);
-    }
-    const bool act = mc && (xm + xp + ym + yp + zm + zp) > 0.0;
-    mask[c] = act ? 1 : 0;
-    const double r = act ? rc : __builtin_huge_val();
-    rt[c] = r;
-    if (rt32) rt32[c] = static_cast<float>(r);
-    active += act;
-    dropped += mc && !act;
+  for (int t = blockIdx.x * kBlock + threadIdx.x; t < pairs; t += gridDim.x * kBlock) {
+    const int i = 2 * (t & (m >> 1)), j = (t >> (q - 1)) & m, k = t >> (2 * q - 1);
+    const int c = cell(i, j, k, q);
+    const PairMask M = pair_mask(umask, i, j, k, q);
+    const double2 rc = ld2(rho, c), ry = ld2(rho, cell(i, (j - 1) & m, k, q)), rz = ld2(rho, k > 0 ? c - nn : c);
+    const double rl = rho[cell((i - 1) & m, j, k, q)];
+    const double2 xm{M.c0 && M.l ? face_beta(rc.x, rl) : 0.0, M.c1 && M.c0 ? face_beta(rc.y, rc.x) : 0.0};
+    const double2 ym{M.c0 && M.ym.x ? face_beta(rc.x, ry.x) : 0.0, M.c1 && M.ym.y ? face_beta(rc.y, ry.y) : 0.0};
+    const double2 zm{M.c0 && M.zm.x ? face_beta(rc.x, rz.x) : 0.0, M.c1 && M.zm.y ? face_beta(rc.y, rz.y) : 0.0};
+    bad += !valid_beta(xm.x) + !valid_beta(ym.x) + !valid_beta(zm.x) + !valid_beta(xm.y) + !valid_beta(ym.y) +
+           !valid_beta(zm.y);
+    *reinterpret_cast<double2*>(bx + c) = xm;
+    *reinterpret_cast<double2*>(by + c) = ym;
+    *reinterpret_cast<double2*>(bz + c) = zm;
+    put_f32(f32, c, xm, ym, zm);
+    bool a0 = M.c0 && (xm.x > 0.0 || ym.x > 0.0 || zm.x > 0.0);
+    bool a1 = M.c1 && (xm.y > 0.0 || ym.y > 0.0 || zm.y > 0.0);
+    const int cy = cell(i, (j + 1) & m, k, q);
+    if (M.c0 && !a0)
+      a0 = (M.c1 && face_beta(rc.y, rc.x) > 0.0) || (M.yp.x && face_beta(rho[cy], rc.x) > 0.0) ||
+           (M.zp.x && face_beta(rho[c + nn], rc.x) > 0.0);
+    if (M.c1 && !a1)
+      a1 = (M.r && face_beta(rho[cell((i + 2) & m, j, k, q)], rc.y) > 0.0) ||
+           (M.yp.y && face_beta(rho[cy + 1], rc.y) > 0.0) || (M.zp.y && face_beta(rho[c + nn + 1], rc.y) > 0.0);
+    *reinterpret_cast<uchar2*>(mask + c) =
+        uchar2{static_cast<unsigned char>(a0 ? 1 : 0), static_cast<unsigned char>(a1 ? 1 : 0)};
+    const double2 r{a0 ? rc.x : inf, a1 ? rc.y : inf};
+    *reinterpret_cast<double2*>(rt + c) = r;
+    if (rt32) *reinterpret_cast<float2*>(rt32 + c) = float2{static_cast<float>(r.x), static_cast<float>(r.y)};
+    active += a0 + a1;
+    dropped += (M.c0 && !a0) + (M.c1 && !a1);
   }
   block_counts(bad, active, dropped, counts);
 }
@@ -948,7 +990,7 @@ hipError_t launch_coeffs_from_rho(const double* rho, const uint8_t* mask, int q,
 hipError_t launch_setup_fine(const double* ubx, const double* uby, const double* ubz, const uint8_t* umask, int q,
                              double* bx, double* by, double* bz, uint8_t* mask, F32Faces f32, int* counts, int* nparts,
                              hipStream_t s) {
-  *nparts = reduction_blocks(1LL << (3 * q));
+  *nparts = reduction_blocks(1LL << (3 * q - 1), 4096);   // few counts for the last launch to add
   hipLaunchKernelGGL(k_setup_fine, dim3(*nparts), dim3(kBlock), 0, s, ubx, uby, ubz, umask, q, bx, by, bz, mask, f32,
                      counts);
   return hipGetLastError();
@@ -957,7 +999,7 @@ hipError_t launch_setup_fine(const double* ubx, const double* uby, const double*
 hipError_t launch_setup_from_rho(const double* rho, const uint8_t* umask, int q, double* bx, double* by, double* bz,
                                  uint8_t* mask, double* rt, float* rt32, F32Faces f32, int* counts, int* nparts,
                                  hipStream_t s) {
-  *nparts = reduction_blocks(1LL << (3 * q));
+  *nparts = reduction_blocks(1LL << (3 * q - 1), 4096);   // few counts for the last launch to add
   hipLaunchKernelGGL(k_setup_from_rho, dim3(*nparts), dim3(kBlock), 0, s, rho, umask, q, bx, by, bz, mask, rt, rt32,
                      f32, counts);
   return hipGetLastError();

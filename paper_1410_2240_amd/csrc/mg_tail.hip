@@ -543,9 +543,10 @@ __global__ __launch_bounds__(kTailThreads) void k_coarse_setup(CoarseSetup a) {
   };
   // ---- the counts of the finest grid's setup, a set of partial ones per block
   long long cnt[3] = {0, 0, 0};
+  for (int b = tid; b < a.nparts; b += kTailThreads) {
 #pragma unroll
-  for (int x = 0; x < 3; ++x)
-    for (int b = tid; b < a.nparts; b += kTailThreads) cnt[x] += a.parts[x * a.nparts + b];
+    for (int x = 0; x < 3; ++x) cnt[x] += a.parts[x * a.nparts + b];
+  }
 #pragma unroll
   for (int x = 0; x < 3; ++x) {
     for (int off = 32; off > 0; off >>= 1) cnt[x] += __shfl_xor(cnt[x], off, 64);

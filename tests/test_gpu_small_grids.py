@@ -195,3 +195,48 @@ def test_more_contexts_than_read_back_slots():
     for mg in held:
         p, h, _ = mg.solve(f, tol=1e-8)
         assert h == hist and torch.equal(p, want)
+
+
+@pytest.mark.parametrize("N", [8, 64])
+@pytest.mark.parametrize("form", ["rho", "faces"])
+def test_setup_pairs(N, form):
+    """The finest grid's setup, two cells at a time: against the oracle on masks whose runs
+    of one to three cells leave fluid cells with no open face, or with one on a high side
+    only; with arrays that start 8 bytes (the mask one byte) past an aligned address; and a
+    bad density or coefficient in either cell of a pair refused.  Faces within 1e-13."""
+    from paper_1410_2240_amd import MG, MGError
+    g = np.random.default_rng(90 + N)
+    mask = (g.random((N, N, N)) < 0.35).astype(np.uint8)
+    mask[:, : N // 2] |= (g.random((N, N // 2, N)) < 0.8).astype(np.uint8)
+    mask[0, 0, :4] = mask[0, 1, :4] = mask[1, 0, :4] = 1
+    rho = np.exp(g.uniform(np.log(1e-3), 0.0, (N, N, N)))
+    bx, by, bz, _ = raw_problem(N, 91, body=False)
+    if form == "rho":
+        bx, by, bz = face_coeffs_from_rho(rho, mask)
+    H = omg.setup(bx, by, bz, mask, 1.0 / N)
+
+    def shifted(x):
+        t = torch.empty(x.size + 1, dtype=torch.from_numpy(x).dtype, device="cuda")
+        v = t[1:].view(x.shape)
+        v.copy_(torch.from_numpy(x))
+        return v
+
+    print(f"setup pairs {N}^3 {form}", flush=True)
+    m = shifted(mask)
+    mg = MG.from_rho(shifted(rho), m) if form == "rho" else MG(shifted(bx), shifted(by), shifted(bz), m)
+    for l, lev in enumerate(H.levels):
+        gx, gy, gz, gm = (host(t) for t in mg.level_coeffs(l))
+        assert (gm.astype(bool) == lev.mask).all(), l
+        for got, want in ((gx, lev.bx), (gy, lev.by), (gz, lev.bz)):
+            assert np.abs(got - want).max() <= 1e-13 * max(np.abs(want).max(), 1e-300), l
+    live = np.argwhere(mask[2, 2] != 0)[:, 0]
+    for i in (int(live[live % 2 == 0][0]), int(live[live % 2 == 1][0])):
+        for value in (np.nan, -1.0):
+            rho2, bx2 = rho.copy(), bx.copy()
+            rho2[2, 2, i] = bx2[2, 2, i] = value
+            full = np.ones_like(mask)
+            with pytest.raises(MGError):
+                if form == "rho":
+                    MG.from_rho(dev(rho2), dev(full))
+                else:
+                    MG(dev(bx2), dev(by), dev(bz), dev(full))
