@@ -377,8 +377,8 @@ int residual_norm(mg_ctx* c, const double* p, const double* f, const double* fsh
   const Level& a = c->lv[0];
   int nb = 0;
   if (mg::march_supported(a.q))
-    MG_HIP(mg::launch_residual_norm_march(p, f, a.bx, a.by, a.bz, a.rt, a.q, a.h, fshift, r32, e32, r64, z64,
-                                          c->partials, &nb, c->stream));
+    MG_HIP(mg::launch_residual_norm_march(p, f, a.bx, a.by, a.bz, a.rt, a.q, a.h, fshift, r32, r64, c->partials, &nb,
+                                          c->stream));   // (its grids are swept out of place: nothing to clear)
   else
     MG_HIP(mg::launch_residual_norm(p, f, a.bx, a.by, a.bz, a.rt, a.q, a.h, fshift, r32, e32, r64, z64, c->partials,
                                     &nb, c->stream));
@@ -594,7 +594,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
       if (fuse_update) {
         double* next = cur == p ? a.t : p;
         int nbu = 0;
-        MG_HIP(mg::launch_residual_norm_update_march(cur, e32, next, f, a.rt, a.q, a.h, fshift, r32, e32_zero,
+        MG_HIP(mg::launch_residual_norm_update_march(cur, e32, next, f, a.rt, a.q, a.h, fshift, r32,
                                                      c->partials, &nbu, c->stream));
         MG_TRY(reduce_and_publish(c, 0, nbu, S_RNORM2, 3));
         cur = next;

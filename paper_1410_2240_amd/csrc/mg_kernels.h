@@ -228,22 +228,18 @@ hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s);
 int march_supported(int q);
 hipError_t launch_residual_norm_march(const double* p, const double* f, const double* bx, const double* by,
                                       const double* bz, const double* rt, int q, double h, const double* fshift,
-                                      float* r32, float* e32, double* r64, double* z64, double* partials,
-                                      int* nblocks, hipStream_t s);
+                                      float* r32, double* r64, double* partials, int* nblocks, hipStream_t s);
 // (FP64 and FP32: the restriction is the one pass an FP32 cycle marches)
 template <typename T>
 hipError_t launch_residual_restrict_march(const T* p, const T* f, const T* bx, const T* by, const T* bz, const T* rt,
                                           int q, double h, const double* fshift, T* fc, T* ec, hipStream_t s);
 // p + e (e in FP32, added on active cells) written to pout, and the norm pass of that
-// sum: partials, r32, e32 as launch_residual_norm_march.  The density form only (rt is
-// required); pout must not overlap p, and e32 (cleared) must be null or not overlap e.  The update and residual of one mixed-precision
+// sum: partials, r32 as launch_residual_norm_march.  The density form only (rt is
+// required); pout must not overlap p.  The update and residual of one mixed-precision
 // refinement step in one pass.
 hipError_t launch_residual_norm_update_march(const double* p, const float* e, double* pout, const double* f,
                                              const double* rt, int q, double h, const double* fshift, float* r32,
-                                             float* e32, double* partials, int* nblocks, hipStream_t s);
-hipError_t launch_fcg_aw_march(const double* d, const double* r, const double* bx, const double* by, const double* bz,
-                               const double* rt, int q, double h, double* w, double* part_dw, double* part_dr,
-                               int* nblocks, hipStream_t s);
+                                             double* partials, int* nblocks, hipStream_t s);
 // The flexible-CG direction and product in one pass (grids of 32^3 and up): dn = z +
 // beta d (beta = -*s_zw / *s_dw; with s_zw = s_dw = null the first direction dn = z,
 // and d is not used), w = A dn, partial sums of dn.w and dn.r, and p += *s_alpha d

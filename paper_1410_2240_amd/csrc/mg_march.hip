@@ -8,11 +8,11 @@
 // rows just below and above the thread's two rows and the x neighbours come from the
 // caches (neighbouring threads load them as their own).  All loads address one plane
 // through a buffer descriptor (mg_buffer.h).  Modes:
-//   NORM      partial sums of r^2 per workgroup; optionally r32 = float(r), e32 = 0,
-//             r64 = r, z64 = 0 (each output may be null)
+//   NORM      partial sums of r^2 per workgroup; optionally r32 = float(r), r64 = r (each
+//             may be null)
+//   UPDATE    NORM of p + e (e in FP32, added on active cells), which is also written out
 //   RESTRICT  fc = mean of r over the 8 children of each coarse cell (the pair's two
 //             cells on two rows and two planes), ec = 0
-//   AW        w = A d (flexible CG) with partial sums of d.w and d.r
 //   FCGX      the flexible-CG direction and product in one pass: d = z + beta d_old
 //             (z in FP64 or FP32; d = z on the first step), w = A d, partial sums of
 //             d.w and d.r, and the previous step's p += alpha d_old, deferred to this
@@ -39,7 +39,7 @@ using buf::Rsrc;
 using buf::Vec2;
 
 constexpr int kMarchThreads = 256;
-enum { kModeNorm = 0, kModeRestrict = 1, kModeAw = 2, kModeNormUpdate = 3, kModeFcgX = 4 };
+enum { kModeNorm = 0, kModeRestrict = 1, kModeNormUpdate = 2, kModeFcgX = 3 };
 
 __device__ __forceinline__ double fmad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -47,7 +47,7 @@ __device__ __forceinline__ float fmad(float a, float b, float c) { return __buil
 // T = float only in RESTRICT mode (the finest grid of an FP32 cycle)
 template <typename T>
 struct MarchArgs {
-  const T* p;         // p, or d in AW mode
+  const T* p;         // p, or the old direction in FCGX mode
   const T* f;         // NORM / RESTRICT
   const T* bx;
   const T* by;
@@ -58,17 +58,15 @@ struct MarchArgs {
   T inv_h2;
   // NORM
   float* r32;
-  float* e32;
   double* r64;
-  double* z64;
-  double* partials;   // NORM: r^2; AW: d.w
+  double* partials;   // NORM: r^2; FCGX: d.w
   // RESTRICT
   T* fc;
   T* ec;
-  // AW
+  // FCGX
   const double* r;
   double* w;
-  double* partials2;  // AW: d.r
+  double* partials2;  // d.r
   // NORM with update: the residual of p + e (e in FP32, added on active cells), and
   // p + e written to pout
   const float* eu;
@@ -144,7 +142,6 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
   constexpr bool UPD = MODE == kModeNormUpdate;
   constexpr bool NORM = MODE == kModeNorm || UPD;
   constexpr bool FX = MODE == kModeFcgX;
-  constexpr bool PROD = MODE == kModeAw || FX;   // w = A d and the two dot products
   static_assert(!UPD || RHO, "the update mode reads activity from the density form");
   constexpr int PAIRS = TX / 2;                 // x-pairs per tile row
   constexpr int RP = kMarchThreads / PAIRS;     // row pairs per tile
@@ -165,7 +162,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
   const unsigned od = off_of<T>(ip, ja - 1, q), ou = off_of<T>(ip, jb + 1, q);
   const unsigned ola = off_of<T>(ip - 1, ja, q), ora = off_of<T>(ip + 2, ja, q);
   const unsigned olb = off_of<T>(ip - 1, jb, q), orb = off_of<T>(ip + 2, jb, q);
-  const T fs = (!PROD && a.fshift) ? static_cast<T>(*a.fshift) : zero;
+  const T fs = (!FX && a.fshift) ? static_cast<T>(*a.fshift) : zero;
   // FCGX: the new direction from z and d_old at one point of the stencil
   const bool fx_first = FX && a.s_zw == nullptr;
   const double fx_beta = (FX && !fx_first) ? -*a.s_zw / *a.s_dw : 0.0;
@@ -253,7 +250,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
       erb = ld1(ek, orb >> 1, 0.0f);
     }
     V2 fa{zero, zero}, fb{zero, zero};
-    if constexpr (!PROD) {
+    if constexpr (!FX) {
       const Rsrc fk = plane_rsrc(a.f, k, q);
       fa = ld2(fk, oa, zero);
       fb = ld2(fk, ob, zero);
@@ -330,17 +327,9 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
         *reinterpret_cast<float2*>(a.r32 + ca) = float2{static_cast<float>(r0a), static_cast<float>(r1a)};
         *reinterpret_cast<float2*>(a.r32 + cb) = float2{static_cast<float>(r0b), static_cast<float>(r1b)};
       }
-      if (a.e32) {
-        *reinterpret_cast<float2*>(a.e32 + ca) = float2{0.0f, 0.0f};
-        *reinterpret_cast<float2*>(a.e32 + cb) = float2{0.0f, 0.0f};
-      }
       if (a.r64) {
         *reinterpret_cast<double2*>(a.r64 + ca) = double2{r0a, r1a};
         *reinterpret_cast<double2*>(a.r64 + cb) = double2{r0b, r1b};
-      }
-      if (a.z64) {
-        *reinterpret_cast<double2*>(a.z64 + ca) = double2{0.0, 0.0};
-        *reinterpret_cast<double2*>(a.z64 + cb) = double2{0.0, 0.0};
       }
     } else if constexpr (MODE == kModeRestrict) {
       // children in the order of every other restriction: (row a, plane 2K),
@@ -392,7 +381,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
   if constexpr (NORM) {
     const double s = block_sum(acc);
     if (tid == 0) a.partials[bid] = s;
-  } else if constexpr (PROD) {
+  } else if constexpr (FX) {
     const double s1 = block_sum(acc);
     __syncthreads();
     const double s2 = block_sum(acc2);
@@ -403,8 +392,8 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
   }
 }
 
-// RESTRICT on the density form (128 x 8 tiles), with the in-plane neighbours of every
-// plane exchanged through LDS instead of read again from the caches.  A thread loads its
+// RESTRICT and the two NORM modes on the density form (128 x 8 tiles), with the in-plane
+// neighbours of every plane exchanged through LDS instead of read again from the caches.  A thread loads its
 // pair's two rows of p and rt, plus its share of the plane's halo (the rows j0-1 and
 // j0+8 and the x neighbours of the tile rows), one plane before they are needed (f in
 // the step that uses it); at the
@@ -412,9 +401,18 @@ __global__ __launch_bounds__(kMarchThreads) void k_residual_march(MarchArgs<T> a
 // barrier everyone reads plane k from the other.  Each line of p and rt is then fetched
 // once per tile plane, the halo once more, however little of one step stays in L2.
 // The faces, sums and restriction are those of k_residual_march, so the bits are too.
-template <typename T>
-__global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) {
+// UPDATE: e is loaded with p, and p + e (the residual's argument, and what is written out)
+// formed where a plane is staged: 964 us at 512^3 (5.6 TB/s), 1178 us
+// with the neighbours read from the caches.  NORM at 256^3 79 us (5.1 TB/s), 91 us before.
+// Two of these workgroups fit a compute unit (170 and 178 VGPRs in FP64); held to three, the
+// registers spill and they take 1112 and 86 us.
+template <typename T, int MODE>
+__global__ __launch_bounds__(kMarchThreads) void k_residual_lds(MarchArgs<T> a) {
   using V2 = typename Vec2<T>::type;
+  constexpr bool UPD = MODE == kModeNormUpdate;
+  constexpr bool NORM = MODE == kModeNorm || UPD;
+  static_assert(NORM || MODE == kModeRestrict, "the modes staged here");
+  static_assert(sizeof(T) == 8 || !NORM, "FP32 marches restrict only");
   constexpr int TX = 128, PAIRS = TX / 2, RP = kMarchThreads / PAIRS, TY = 2 * RP;
   constexpr int LW = TX + 2, LH = TY + 2;   // a staged plane: the tile and a 1-cell halo
   __shared__ T Lp[2][LH][LW];
@@ -454,6 +452,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) 
   // one plane's loads: the pair's rows of p and rt, and the halo share
   struct Plane {
     V2 pa, pb, ra, rb, hp, hrt;
+    float2 ea, eb, he;   // UPDATE: e at the same places
   };
   auto load = [&](int kk) {
     const Rsrc pk = plane_rsrc(a.p, kk, q), rk = plane_rsrc(a.rt, kk, q);
@@ -471,9 +470,22 @@ __global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) 
       L.hp.x = ld1(pk, ho, zero);
       L.hrt.x = ld1(rk, ho, zero);
     }
+    if constexpr (UPD) {
+      const Rsrc ek = plane_rsrc(a.eu, kk, q);
+      L.ea = ld2(ek, oa >> 1, 0.0f);
+      L.eb = ld2(ek, ob >> 1, 0.0f);
+      L.he = float2{0.0f, 0.0f};
+      if (hpair) L.he = ld2(ek, ho >> 1, 0.0f);
+      else if (hr >= 0) L.he.x = ld1(ek, ho >> 1, 0.0f);
+    }
     return L;
   };
-  auto put = [&](int b, const Plane& L) {
+  auto put = [&](int b, Plane& L) {
+    if constexpr (UPD) {
+      L.pa = add_active(L.pa, L.ea, L.ra);
+      L.pb = add_active(L.pb, L.eb, L.rb);
+      L.hp = add_active(L.hp, L.he, L.hrt);
+    }
     Lp[b][ra_][cc] = L.pa.x;
     Lp[b][ra_][cc + 1] = L.pa.y;
     Lp[b][rb_][cc] = L.pb.x;
@@ -504,12 +516,18 @@ __global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) 
   const Rsrc p_lo = plane_rsrc(a.p, k0 - 1, q), r_lo = plane_rsrc(a.rt, k0 - 1, q);
   V2 pa_lo = ld2(p_lo, oa, zero), pb_lo = ld2(p_lo, ob, zero);
   const V2 la = ld2(r_lo, oa, zero), lb = ld2(r_lo, ob, zero);
+  if constexpr (UPD) {
+    const Rsrc e_lo = plane_rsrc(a.eu, k0 - 1, q);
+    pa_lo = add_active(pa_lo, ld2(e_lo, oa >> 1, 0.0f), la);
+    pb_lo = add_active(pb_lo, ld2(e_lo, ob >> 1, 0.0f), lb);
+  }
   Plane nxt = load(k0 + 1);
   put(k0 & 1, cur);
   const bool in_lo = k0 >= 1;
   V2 za = in_lo ? V2{face_beta(la.x, cur.ra.x), face_beta(la.y, cur.ra.y)} : V2{zero, zero};
   V2 zb = in_lo ? V2{face_beta(lb.x, cur.rb.x), face_beta(lb.y, cur.rb.y)} : V2{zero, zero};
   T csum = zero;
+  double acc = 0.0;
   for (int k = k0; k < k0 + a.kc; ++k) {
     __syncthreads();   // plane k staged; the other LDS plane no longer read
     put((k + 1) & 1, nxt);
@@ -555,16 +573,35 @@ __global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) 
     T r0a, r1a, r0b, r1b;
     pair_r(Fa, cur.pa, pla, pra, pd, cur.pb, pa_lo, hi.pa, fa, fs, a.inv_h2, r0a, r1a);
     pair_r(Fb, cur.pb, plb, prb, cur.pa, pup, pb_lo, hi.pb, fb, fs, a.inv_h2, r0b, r1b);
-    // children in the order of every other restriction: (row a, plane 2K),
-    // (row b, plane 2K), (row a, plane 2K+1), (row b, plane 2K+1)
-    if ((k & 1) == 0) csum = zero;
-    csum += r0a + r1a;
-    csum += r0b + r1b;
-    if (k & 1) {
-      const int qc = q - 1;
-      const int C = ((((k >> 1) << qc) | (ja >> 1)) << qc) | (ip >> 1);
-      a.fc[C] = csum * T(0.125);
-      a.ec[C] = zero;
+    if constexpr (NORM) {
+      const long long plane = static_cast<long long>(k) << (2 * q);
+      const long long ca = plane + oa / sizeof(T), cb = plane + ob / sizeof(T);
+      if constexpr (UPD) {   // read again only after the next FP32 cycle: streaming stores
+        stream_store(a.pout + ca, cur.pa);
+        stream_store(a.pout + cb, cur.pb);
+      }
+      acc = fmad(r1a, r1a, fmad(r0a, r0a, acc));
+      acc = fmad(r1b, r1b, fmad(r0b, r0b, acc));
+      if (a.r32) {
+        *reinterpret_cast<float2*>(a.r32 + ca) = float2{static_cast<float>(r0a), static_cast<float>(r1a)};
+        *reinterpret_cast<float2*>(a.r32 + cb) = float2{static_cast<float>(r0b), static_cast<float>(r1b)};
+      }
+      if (a.r64) {
+        *reinterpret_cast<double2*>(a.r64 + ca) = double2{r0a, r1a};
+        *reinterpret_cast<double2*>(a.r64 + cb) = double2{r0b, r1b};
+      }
+    } else {
+      // children in the order of every other restriction: (row a, plane 2K),
+      // (row b, plane 2K), (row a, plane 2K+1), (row b, plane 2K+1)
+      if ((k & 1) == 0) csum = zero;
+      csum += r0a + r1a;
+      csum += r0b + r1b;
+      if (k & 1) {
+        const int qc = q - 1;
+        const int C = ((((k >> 1) << qc) | (ja >> 1)) << qc) | (ip >> 1);
+        a.fc[C] = csum * T(0.125);
+        a.ec[C] = zero;
+      }
     }
     pa_lo = cur.pa;
     pb_lo = cur.pb;
@@ -572,10 +609,14 @@ __global__ __launch_bounds__(kMarchThreads) void k_restrict_lds(MarchArgs<T> a) 
     zb = V2{Fb.zp0, Fb.zp1};
     cur = hi;
   }
+  if constexpr (NORM) {
+    const double s = block_sum(acc);
+    if (tid == 0) a.partials[bid] = s;
+  }
 }
 
 // The flexible-CG pass of k_residual_march's FCGX mode on the density form (128 x 8
-// tiles), with the in-plane stencil exchanged through LDS as in k_restrict_lds.  A
+// tiles), with the in-plane stencil exchanged through LDS as in k_residual_lds.  A
 // thread loads d_old, z and rt of its pair's rows and of its share of the halo a plane
 // before they are needed, forms the new direction d = z + beta d_old there, and stages
 // d and rt; after the step's barrier the pair's neighbours come from LDS.  Products,
@@ -619,7 +660,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_lds(MarchArgs<double> a)
     if (a.zx64) return ld1(plane_rsrc(a.zx64, kk, q), off, 0.0);
     return static_cast<double>(ld1(plane_rsrc(a.zx32, kk, q), off >> 1, 0.0f));
   };
-  // halo share as in k_restrict_lds
+  // halo share as in k_residual_lds
   int hr = -1, hc = 0;
   bool hpair = false;
   unsigned ho = 0;
@@ -791,8 +832,32 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_lds(MarchArgs<double> a)
   }
 }
 
+// 128 x 8 tiles, z-chunks as launch_mode takes them
+template <typename T, int MODE>
+hipError_t launch_lds(MarchArgs<T> a, int* nblocks, hipStream_t s) {
+  const int n = 1 << a.q;
+  const long long tiles = static_cast<long long>(n / 128) * (n / 8);
+  int kc = 64;
+  while (kc > 2 && tiles * (n / kc) < 1024) kc /= 2;
+  if (kc > n) kc = n;
+  while (tiles * (n / kc) > kNumPartials) kc *= 2;
+  a.kc = kc;
+  const int blocks = static_cast<int>(tiles * (n / kc));
+  *nblocks = blocks;
+  if constexpr (MODE == kModeFcgX)
+    hipLaunchKernelGGL(k_fcgx_lds, dim3(blocks), dim3(kMarchThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_residual_lds<T, MODE>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+// the density form on grids of 128^3 and up: the stencil through LDS
+bool through_lds(const void* rt, int q) { return rt != nullptr && (1 << q) >= 128; }
+
 template <typename T, bool RHO, int MODE>
 hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
+  if constexpr (RHO)
+    if (through_lds(a.rt, a.q)) return launch_lds<T, MODE>(a, nblocks, s);
   const int n = 1 << a.q;
   const int TX = n >= 128 ? 128 : n;
   const int TY = 2 * (kMarchThreads / (TX / 2));
@@ -806,9 +871,10 @@ hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
   const int blocks = static_cast<int>(tiles * (n / kc));
   *nblocks = blocks;
   const dim3 grid(blocks), block(kMarchThreads);
-  if (TX == 128)
-    hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 128>), grid, block, 0, s, a);
-  else if (TX == 64)
+  if (TX == 128) {
+    if constexpr (!RHO)
+      hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 128>), grid, block, 0, s, a);
+  } else if (TX == 64)
     hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 64>), grid, block, 0, s, a);
   else
     hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 32>), grid, block, 0, s, a);
@@ -823,12 +889,11 @@ hipError_t launch_form(MarchArgs<T> a, int* nblocks, hipStream_t s) {
 }  // namespace
 
 int march_supported(int q) { return (1 << q) >= 32; }
-int fcgx_defer_supported(const double* rt, int q) { return rt != nullptr && (1 << q) >= 128; }
+int fcgx_defer_supported(const double* rt, int q) { return through_lds(rt, q); }
 
 hipError_t launch_residual_norm_march(const double* p, const double* f, const double* bx, const double* by,
                                       const double* bz, const double* rt, int q, double h, const double* fshift,
-                                      float* r32, float* e32, double* r64, double* z64, double* partials,
-                                      int* nblocks, hipStream_t s) {
+                                      float* r32, double* r64, double* partials, int* nblocks, hipStream_t s) {
   MarchArgs<double> a{};
   a.p = p;
   a.f = f;
@@ -840,9 +905,7 @@ hipError_t launch_residual_norm_march(const double* p, const double* f, const do
   a.q = q;
   a.inv_h2 = 1.0 / (h * h);
   a.r32 = r32;
-  a.e32 = e32;
   a.r64 = r64;
-  a.z64 = z64;
   a.partials = partials;
   return launch_form<kModeNorm>(a, nblocks, s);
 }
@@ -863,23 +926,13 @@ hipError_t launch_residual_restrict_march(const T* p, const T* f, const T* bx, c
   a.fc = fc;
   a.ec = ec;
   int nb = 0;
-  if (rt && (1 << q) >= 128) {   // the density form: neighbours through LDS
-    const int n = 1 << q;
-    const long long tiles = static_cast<long long>(n / 128) * (n / 8);
-    int kc = 64;
-    while (kc > 2 && tiles * (n / kc) < 1024) kc /= 2;
-    if (kc > n) kc = n;
-    a.kc = kc;
-    hipLaunchKernelGGL(k_restrict_lds<T>, dim3(static_cast<unsigned>(tiles * (n / kc))), dim3(kMarchThreads), 0, s, a);
-    return hipGetLastError();
-  }
   return launch_form<kModeRestrict>(a, &nb, s);
 }
 
 hipError_t launch_residual_norm_update_march(const double* p, const float* e, double* pout, const double* f,
                                              const double* rt, int q, double h, const double* fshift, float* r32,
-                                             float* e32, double* partials, int* nblocks, hipStream_t s) {
-  if (!rt || p == pout || e == e32) return hipErrorInvalidValue;
+                                             double* partials, int* nblocks, hipStream_t s) {
+  if (!rt || p == pout) return hipErrorInvalidValue;
   MarchArgs<double> a{};
   a.p = p;
   a.f = f;
@@ -888,7 +941,6 @@ hipError_t launch_residual_norm_update_march(const double* p, const float* e, do
   a.q = q;
   a.inv_h2 = 1.0 / (h * h);
   a.r32 = r32;
-  a.e32 = e32;
   a.partials = partials;
   a.eu = e;
   a.pout = pout;
@@ -901,24 +953,6 @@ template hipError_t launch_residual_restrict_march<double>(const double*, const 
 template hipError_t launch_residual_restrict_march<float>(const float*, const float*, const float*, const float*,
                                                           const float*, const float*, int, double, const double*,
                                                           float*, float*, hipStream_t);
-
-hipError_t launch_fcg_aw_march(const double* d, const double* r, const double* bx, const double* by, const double* bz,
-                               const double* rt, int q, double h, double* w, double* part_dw, double* part_dr,
-                               int* nblocks, hipStream_t s) {
-  MarchArgs<double> a{};
-  a.p = d;
-  a.bx = bx;
-  a.by = by;
-  a.bz = bz;
-  a.rt = rt;
-  a.q = q;
-  a.inv_h2 = 1.0 / (h * h);
-  a.r = r;
-  a.w = w;
-  a.partials = part_dw;
-  a.partials2 = part_dr;
-  return launch_form<kModeAw>(a, nblocks, s);
-}
 
 hipError_t launch_fcg_x_march(const double* z64, const float* z32, const double* d, double* dn, double* p,
                               const double* s_zw, const double* s_dw, const double* s_alpha, const double* r,
@@ -958,19 +992,6 @@ hipError_t launch_fcg_x_march(const double* z64, const float* z32, const double*
       a.dprev = df->d_prev;
       a.s_alpha_prev = df->s_alpha_prev;
     }
-  }
-  if (rt && (1 << q) >= 128) {   // the density form: the stencil through LDS
-    const int n = 1 << q;
-    const long long tiles = static_cast<long long>(n / 128) * (n / 8);
-    int kc = 64;
-    while (kc > 2 && tiles * (n / kc) < 1024) kc /= 2;
-    if (kc > n) kc = n;
-    while (tiles * (n / kc) > kNumPartials) kc *= 2;
-    a.kc = kc;
-    const int blocks = static_cast<int>(tiles * (n / kc));
-    *nblocks = blocks;
-    hipLaunchKernelGGL(k_fcgx_lds, dim3(blocks), dim3(kMarchThreads), 0, s, a);
-    return hipGetLastError();
   }
   return launch_form<kModeFcgX>(a, nblocks, s);
 }

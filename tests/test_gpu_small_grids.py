@@ -240,3 +240,27 @@ def test_setup_pairs(N, form):
                     MG.from_rho(dev(rho2), dev(full))
                 else:
                     MG(dev(bx2), dev(by), dev(bz), dev(full))
+
+
+@pytest.mark.parametrize("N", [128, 256])
+def test_norm_passes_through_lds(N):
+    """The residual norm and the mixed update + residual pass with their stencil through
+    LDS (128^3, the smallest; 256^3, two tiles to a row): the first residual of a guess
+    against the face-array context's, bit for bit (its pass reads neighbours from the
+    caches), and a mixed refinement against FP64, within 1e-9."""
+    from paper_1410_2240_amd import MG, coeffs_from_rho
+    inp = fields.make("c2", N)
+    rho, mask, f = dev(inp.rho), dev(inp.mask), dev(inp.f)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    p0 = torch.randn(rho.shape, generator=g, device="cuda", dtype=torch.float64)
+    print(f"norm passes {N}^3", flush=True)
+    a = MG.from_rho(rho, mask)
+    b = MG(*coeffs_from_rho(rho, mask), mask)
+    _, ha, _ = a.solve(f, p0.clone(), max_cycles=0, raise_on_fail=False)
+    _, hb, _ = b.solve(f, p0.clone(), max_cycles=0, raise_on_fail=False)
+    assert ha == hb and len(ha) == 1
+    m = MG.from_rho(rho, mask, mixed=True)
+    pm, hm, _ = m.solve(f, p0.clone(), tol=1e-12, max_cycles=80)
+    pa, _, _ = a.solve(f, p0.clone(), tol=1e-12, max_cycles=80)
+    assert hm[0] == ha[0]
+    assert float((pm - pa).norm() / pa.norm()) <= 1e-9
