@@ -65,6 +65,8 @@ enum {
   S_COUNT = 9
 };
 
+constexpr int kHostHistory = 118;   // residuals a small solve hands over with its scalars
+
 struct Level {
   int n = 0, q = 0;
   double h = 0;
@@ -96,7 +98,7 @@ struct mg_ctx {
   double *kr = nullptr, *kz = nullptr, *kd = nullptr, *kd2 = nullptr, *kw = nullptr;   // flexible-CG vectors
   double* kr2 = nullptr;   // a second residual (absent unless the plan holds one)
   double* kd3 = nullptr;   // a third direction (likewise)
-  double* host = nullptr;   // pinned: S_COUNT doubles, then the ticket of the last ones sent
+  double* host = nullptr;   // pinned: S_COUNT doubles, the ticket of the last ones sent, kHostHistory doubles
   unsigned long long published = 0;   // the ticket of the last scalars asked for
   long long active = 0, dropped = 0;
   // Concurrent right-hand sides (mg_add_lanes): each lane is a context of its own that
@@ -252,6 +254,29 @@ int first_sweep(mg_ctx* c, T* p, const T* f, const double* fshift, bool zero_in)
   return MG_OK;
 }
 
+// the grids from l (16^3 or below) down to 4^3, as the single-workgroup kernels take them
+template <typename T>
+mg::CoarseCycle<T> coarse_cycle_args(const mg_ctx* c, int l, T* p, const T* f, const double* fshift) {
+  mg::CoarseCycle<T> a{};
+  a.nlev = c->L - l;
+  for (int k = 0; k < a.nlev; ++k) {
+    const Level& lv = c->lv[l + k];
+    const View<T> v = c->view<T>(l + k);
+    a.q[k] = lv.q;
+    a.bx[k] = v.bx;
+    a.by[k] = v.by;
+    a.bz[k] = v.bz;
+    a.mask[k] = lv.mask;
+    a.f[k] = k == 0 ? const_cast<T*>(f) : v.f;
+    a.e[k] = k == 0 ? p : v.e;
+    a.h2[k] = static_cast<T>(lv.h * lv.h);
+    a.inv_h2[k] = static_cast<T>(1.0 / (lv.h * lv.h));
+  }
+  a.pinv = c->pinv;
+  a.fshift = fshift;
+  return a;
+}
+
 // zero_in: p enters as zero (a correction), see smooth(); first_done: see first_sweep();
 // zw: only on a two-sweep grid, where the last pass also sums p . zw->w (flexible CG's z.w)
 template <typename T>
@@ -259,23 +284,7 @@ int vcycle(mg_ctx* c, int l, T* p, const T* f, const double* fshift, bool zero_i
            const ZwSums* zw = nullptr) {
   if (c->lv[l].n <= mg::kCoarseCycleMaxN) {
     // grids of 16^3 and below: the rest of the cycle in one single-workgroup launch
-    mg::CoarseCycle<T> a{};
-    a.nlev = c->L - l;
-    for (int k = 0; k < a.nlev; ++k) {
-      const Level& lv = c->lv[l + k];
-      const View<T> v = c->view<T>(l + k);
-      a.q[k] = lv.q;
-      a.bx[k] = v.bx;
-      a.by[k] = v.by;
-      a.bz[k] = v.bz;
-      a.mask[k] = lv.mask;
-      a.f[k] = k == 0 ? const_cast<T*>(f) : v.f;
-      a.e[k] = k == 0 ? p : v.e;
-      a.h2[k] = static_cast<T>(lv.h * lv.h);
-      a.inv_h2[k] = static_cast<T>(1.0 / (lv.h * lv.h));
-    }
-    a.pinv = c->pinv;
-    a.fshift = fshift;
+    const mg::CoarseCycle<T> a = coarse_cycle_args<T>(c, l, p, f, fshift);
     MG_HIP(mg::launch_coarse_cycle<T>(a, c->stream));
     return MG_OK;
   }
@@ -399,10 +408,60 @@ int check_prec(mg_ctx* c, int prec) {
   return MG_OK;
 }
 
+// One right-hand side by FP64 V-cycles on a finest grid of 16^3 or 8^3: one launch.  The
+// history goes through the partial sums' memory (history_cap entries at most).
+constexpr int kHistoryCap = mg::kPartialSets * mg::kNumPartials;
+
+int solve_small(mg_ctx* c, const double* f, double* p, double tol, int max_cycles, double* hist, int* n_hist,
+                double* removed_mean, double* final_relres, int* cycles) {
+  mg::SmallSolve a{};
+  a.cyc = coarse_cycle_args<double>(c, 0, p, f, nullptr);
+  a.tol = tol;
+  a.active = static_cast<double>(c->active);
+  a.zero_rhs = kZeroRhs;
+  a.growth = kBreakdownGrowth;
+  a.max_cycles = max_cycles;
+  a.hist = c->partials;
+  a.host_hist = reinterpret_cast<double*>(ticket_of(c) + 1);
+  a.host_cap = kHostHistory;
+  a.pub.host = c->host;
+  a.pub.ticket = ticket_of(c);
+  a.pub.value = c->published + 1;
+  MG_HIP(mg::launch_small_solve(a, c->stream));
+  c->published = a.pub.value;
+  double s[6];
+  MG_TRY(wait_scalars(c, s, 6));
+  *removed_mean = s[0];
+  *final_relres = s[1];
+  *n_hist = static_cast<int>(s[3]);
+  *cycles = static_cast<int>(s[4]);
+  if (hist) {
+    const int near = std::min(*n_hist, kHostHistory);
+    std::memcpy(hist, a.host_hist, sizeof(double) * near);
+    if (*n_hist > near) {
+      MG_HIP(hipMemcpyAsync(hist + near, c->partials + near, sizeof(double) * (*n_hist - near), hipMemcpyDeviceToHost,
+                            c->stream));
+      MG_HIP(hipStreamSynchronize(c->stream));
+    }
+  }
+  switch (static_cast<int>(s[5])) {
+    case mg::kSmallNoConv:
+      return fail(MG_ENOCONV, "relative residual %g > tol %g after %d cycles", s[1], tol, *cycles);
+    case mg::kSmallBreakdown:
+      return fail(MG_EBREAKDOWN, "residual %g after %d cycles (initial %g)", s[1], *cycles, s[2]);
+    case mg::kSmallNotFinite:
+      return fail(MG_EBREAKDOWN, "right-hand side is not finite");
+    default:
+      return MG_OK;
+  }
+}
+
 // One right-hand side.  hist has room for max_cycles + 1 entries.
 int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles, double* hist, int* n_hist,
               double* removed_mean, double* final_relres, int* cycles) {
   const Level& a = c->lv[0];
+  if (a.n <= mg::kCoarseCycleMaxN && !(c->flags & (MG_MIXED | MG_KRYLOV)) && max_cycles < kHistoryCap)
+    return solve_small(c, f, p, tol, max_cycles, hist, n_hist, removed_mean, final_relres, cycles);
   const double* fshift = c->scal + S_FMEAN;
   int nb = 0;
   // P f: fluid mean of f (applied on the fly by every finest-grid kernel) and ||P f||
@@ -721,9 +780,9 @@ namespace {
 // run.  Allocating and freeing it for every context cost a setup and a destroy about 60 us
 // (the free waits for the device), so contexts take slots of one block, made for the first
 // of them; with every slot taken a context gets an allocation of its own, as before.
-constexpr size_t kSlotBytes = 128;   // S_COUNT doubles and the ticket
+constexpr size_t kSlotBytes = sizeof(double) * (S_COUNT + kHostHistory) + sizeof(unsigned long long);
 constexpr int kSlots = 64;
-static_assert(sizeof(double) * S_COUNT + sizeof(unsigned long long) <= kSlotBytes, "a slot holds the scalars");
+static_assert(kSlotBytes % 64 == 0, "slots on cache lines of their own");
 std::mutex g_slots_mutex;
 unsigned char* g_slots = nullptr;
 unsigned long long g_slots_taken = 0;   // bit i: slot i

@@ -222,6 +222,24 @@ struct CoarseCycle {
 template <typename T>
 hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s);
 
+// A whole FP64 V-cycle solve on a 16^3 or 8^3 finest grid in one launch (cyc.e[0]: the guess
+// in, the solution out; cyc.fshift unused): the mean removed from f, the cycles until the
+// relative residual is at most tol (or max_cycles, or a breakdown), and the gauge.  pub.host
+// receives the removed mean, the last and the first relative residual, the number of
+// entries of the history, the cycles and how it ended; host_hist the first host_cap entries
+// of the history, hist (device) all of them: room for max_cycles + 1.
+enum { kSmallDone = 0, kSmallNoConv = 1, kSmallBreakdown = 2, kSmallZero = 3, kSmallNotFinite = 4 };
+struct SmallSolve {
+  CoarseCycle<double> cyc;
+  double tol, active, zero_rhs, growth;   // zero_rhs: ||P f|| / ||f|| taken as zero
+  int max_cycles;
+  double* hist;
+  double* host_hist;
+  int host_cap;
+  Publish pub;
+};
+hipError_t launch_small_solve(const SmallSolve& a, hipStream_t s);
+
 // ---- z-marching FP64 residual passes (grids of 32^3 and up) ------------------------
 // Same results as the grid-stride kernels below (per cell), each plane of p and of the
 // coefficients read once per column; rt != nullptr selects the density form.

@@ -9,7 +9,7 @@
 //         outside the block is read in a half-sweep (12 LDS reads and 4 writes for 4
 //         independent updates), and the restriction and prolongation are thread-local.
 //   8^3   Each of 256 threads owns an x-pair, one cell of each colour, with the same things
-//         in registers; the values live in LDS.
+//         in registers, or below a 16^3 grid in LDS; the values live in LDS.
 //   4^3   The pseudo-inverse product, 8 threads to a row, its entries loaded at the start.
 // All memory is read once, at the start, in one round of loads.  On the values of a 16^3
 // grid rows are split by column parity and padded to 20 words, so that the neighbours of a
@@ -69,7 +69,9 @@ struct TailShared {
   T x[256];   // residuals of the 8^3 grid's pairs
   T e2[64];
   double fh[64];
-  double pinv[TOP16 ? 8 * kTailThreads : 1];   // each thread its own column (no registers left for it)
+  // what a thread's registers have no room for beside its block: each its own column
+  double pinv[TOP16 ? 8 * kTailThreads : 1];
+  T pair[TOP16 ? 8 : 1][2][TOP16 ? 256 : 1];   // faces, diagonal and reciprocal of its 8^3 pair
 };
 
 // One cell: faces, diagonal and its reciprocal, right-hand side (less its shift).
@@ -91,7 +93,7 @@ struct Tail {
   unsigned live0 = 0;                        // bit dz 4 + dy 2 + dx: an active cell
   int o, oxm, oxp, oym, oyp, ozm, ozp;       // LDS offsets: the block, and to its neighbours
   // the pair of an 8^3 grid: cell of colour 0 and of colour 1
-  TailCell<T> p1[2];
+  TailCell<T> p1[TOP16 ? 1 : 2];   // (in LDS below a 16^3 grid)
   bool live1[2];
   int c1[2], xm1[2], xp1[2], ym1, yp1, zm1, zp1;
   double pv[TOP16 ? 1 : 8];
@@ -166,7 +168,7 @@ struct Tail {
         c1[col] = c;
         xm1[col] = c - i + ((i - 1) & 7);
         xp1[col] = c - i + ((i + 1) & 7);
-        TailCell<T>& q = p1[col];
+        TailCell<T> q;
         q.xm = bx[c];
         q.xp = bx[xp1[col]];
         q.ym = by[c];
@@ -174,7 +176,16 @@ struct Tail {
         q.zm = bz[c];
         q.zp = k < 7 ? bz[c + 64] : T(0);
         live1[col] = a.mask[L1][c] != 0;
-        if constexpr (!TOP16) q.f = a.f[0][c] - fs;
+        q.D = q.xm + q.xp + q.ym + q.yp + q.zm + q.zp;
+        q.r = diag_recip(q.D);
+        if constexpr (TOP16) {
+          const T v[8] = {q.xm, q.xp, q.ym, q.yp, q.zm, q.zp, q.D, q.r};
+#pragma unroll
+          for (int x = 0; x < 8; ++x) s.pair[x][col][tid] = v[x];
+        } else {
+          q.f = a.f[0][c] - fs;
+          p1[col] = q;
+        }
       }
     }
     if (tid < 64) act2 = a.mask[L2][tid] != 0;
@@ -200,13 +211,16 @@ struct Tail {
             r[dz][dy][dx] = diag_recip(d);
           }
     }
-    if (tid < 256) {
-#pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        TailCell<T>& q = p1[col];
-        q.D = q.xm + q.xp + q.ym + q.yp + q.zm + q.zp;
-        q.r = diag_recip(q.D);
-      }
+  }
+
+  // the 8^3 cell of colour col this thread (tid < 256) owns
+  __device__ __forceinline__ TailCell<T> cell8(int col) const {
+    if constexpr (TOP16) {
+      return TailCell<T>{s.pair[0][col][tid], s.pair[1][col][tid], s.pair[2][col][tid], s.pair[3][col][tid],
+                         s.pair[4][col][tid], s.pair[5][col][tid], s.pair[6][col][tid], s.pair[7][col][tid],
+                         s.f1[c1[col]]};
+    } else {
+      return p1[col];
     }
   }
 
@@ -358,7 +372,7 @@ struct Tail {
   template <int COL>
   __device__ __forceinline__ void half8() {
     if (tid < 256) {
-      const TailCell<T>& q = p1[COL];
+      const TailCell<T> q = cell8(COL);
       const int c = c1[COL];
       const T* L = s.e1;
       const T S = fma_t(q.zp, L[c + zp1], fma_t(q.zm, L[c + zm1], fma_t(q.yp, L[c + yp1], fma_t(q.ym, L[c + ym1],
@@ -369,7 +383,7 @@ struct Tail {
   }
 
   __device__ __forceinline__ T residual8(int col) const {
-    const TailCell<T>& q = p1[col];
+    const TailCell<T> q = cell8(col);
     const int c = c1[col];
     const T* L = s.e1;
     const T pc = L[c];
@@ -378,7 +392,7 @@ struct Tail {
     return q.D > T(0) ? fma_t(-a.inv_h2[L1], S, q.f) : T(0);
   }
 
-  // the 8^3 grid's cycle on s.e1 with the right-hand side in p1[].f
+  // the 8^3 grid's cycle on s.e1
   __device__ __forceinline__ void cycle8() {
     half8<0>();
     half8<1>();
@@ -450,10 +464,6 @@ struct Tail {
       half16<0>();
       half16<1>();
       restrict16();
-      if (tid < 256) {
-        p1[0].f = s.f1[c1[0]];
-        p1[1].f = s.f1[c1[1]];
-      }
       cycle8();
       prolong16();
       half16<1>();
@@ -476,6 +486,148 @@ __global__ __launch_bounds__(kTailThreads) void k_coarse_cycle(CoarseCycle<T> a)
   __syncthreads();
   t.cycle();
   t.store_e();
+}
+
+// The sum over the workgroup, in every thread; its barriers also end every wave's reads of
+// the values the next half-sweep changes.
+__device__ __forceinline__ double sum_all(double v, double* red) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < kTailThreads / 64; ++w) s += red[w];
+  __syncthreads();
+  return s;
+}
+
+// A whole solve: the cycle above with its residual norm, stopping test and history, so that
+// a cycle costs neither launches nor a round trip to the host and the coefficients are
+// read once per solve.  A cycle and its norm take 12 us at 16^3 and 6 us at 8^3; launched
+// one by one, with the sums and the host's part, 28 and 22 us.
+template <bool TOP16>
+__global__ __launch_bounds__(kTailThreads) void k_small_solve(SmallSolve a) {
+  __shared__ TailShared<double, TOP16> s;
+  __shared__ double red[kTailThreads / 64];
+  Tail<double, TOP16> t(s, a.cyc);
+  const int tid = threadIdx.x;
+  t.load_e();
+  t.load(0.0);
+  // per thread: f(term) over its active cells, summed
+  auto over_f = [&](auto term) {
+    double v = 0.0;
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (t.live0 >> c & 1) v += term(t.f[c >> 2][(c >> 1) & 1][c & 1]);
+    } else if (tid < 256) {
+#pragma unroll
+      for (int col = 0; col < 2; ++col)
+        if (t.live1[col]) v += term(t.p1[col].f);
+    }
+    return v;
+  };
+  auto subtract = [&](double m) {
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) t.f[c >> 2][(c >> 1) & 1][c & 1] -= m;
+    } else {
+      t.p1[0].f -= m;
+      t.p1[1].f -= m;
+    }
+  };
+  // the guess, and at the end the solution less its mean: 0 on inactive cells
+  auto gauge = [&](double m) {
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        double& v = t.e[c >> 2][(c >> 1) & 1][c & 1];
+        v = (t.live0 >> c & 1) ? v - m : 0.0;
+      }
+    } else if (tid < 256) {
+#pragma unroll
+      for (int col = 0; col < 2; ++col) s.e1[t.c1[col]] = t.live1[col] ? s.e1[t.c1[col]] - m : 0.0;
+    }
+  };
+  auto residual2 = [&]() {
+    double v = 0.0;
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const double r = t.residual16(c >> 2, (c >> 1) & 1, c & 1);
+        v = __builtin_fma(r, r, v);
+      }
+    } else if (tid < 256) {
+      const double ra = t.residual8(0), rb = t.residual8(1);
+      v = __builtin_fma(rb, rb, ra * ra);
+    }
+    return sum_all(v, red);
+  };
+  const double inv_active = 1.0 / a.active;
+  const double mean = sum_all(over_f([](double v) { return v; }), red) * inv_active;
+  subtract(mean);
+  const double nf2 = sum_all(over_f([](double v) { return v * v; }), red);
+  const double nf = sqrt(nf2), nf_all = sqrt(nf2 + a.active * mean * mean);
+  gauge(0.0);
+  if constexpr (TOP16) t.put_block();
+  __syncthreads();
+  int nh = 0, cycles = 0, how = kSmallDone;
+  double r = 0.0, r0 = 0.0;
+  auto record = [&](double v) {
+    if (tid == 0) {
+      a.hist[nh] = v;
+      if (nh < a.host_cap) a.host_hist[nh] = v;
+    }
+    ++nh;
+  };
+  if (!(nf > a.zero_rhs * nf_all)) {   // P f = 0 to rounding: p = 0
+    how = __builtin_isfinite(nf) ? kSmallZero : kSmallNotFinite;
+    record(0.0);
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) t.e[c >> 2][(c >> 1) & 1][c & 1] = 0.0;
+    } else {
+      s.e1[tid] = 0.0;
+    }
+  } else {
+    r = r0 = sqrt(residual2()) / nf;
+    record(r);
+    while (__builtin_isfinite(r) && r > a.tol && cycles < a.max_cycles) {
+      t.cycle();
+      ++cycles;
+      r = sqrt(residual2()) / nf;
+      record(r);
+      if (!__builtin_isfinite(r) || r > a.growth * fmax(r0, 1.0)) {
+        how = kSmallBreakdown;
+        break;
+      }
+    }
+    if (how == kSmallDone && r > a.tol) how = kSmallNoConv;
+    double v = 0.0;
+    if constexpr (TOP16) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (t.live0 >> c & 1) v += t.e[c >> 2][(c >> 1) & 1][c & 1];
+    } else if (tid < 256) {
+#pragma unroll
+      for (int col = 0; col < 2; ++col)
+        if (t.live1[col]) v += s.e1[t.c1[col]];
+    }
+    gauge(sum_all(v, red) * inv_active);
+  }
+  if constexpr (!TOP16) __syncthreads();
+  t.store_e();
+  if (tid == 0) {
+    double* h = a.pub.host;
+    h[0] = mean;
+    h[1] = r;
+    h[2] = r0;
+    h[3] = nh;
+    h[4] = cycles;
+    h[5] = how;
+    __threadfence_system();
+    __hip_atomic_store(a.pub.ticket, a.pub.value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // ---------------------------------------------------------------------------- setup
@@ -692,6 +844,17 @@ hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s) {
     hipLaunchKernelGGL((k_coarse_cycle<T, true>), dim3(1), dim3(kTailThreads), 0, s, a);
   else if (a.nlev == 2 && a.q[0] == 3)
     hipLaunchKernelGGL((k_coarse_cycle<T, false>), dim3(1), dim3(kTailThreads), 0, s, a);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+hipError_t launch_small_solve(const SmallSolve& a, hipStream_t s) {
+  if (!a.hist || !a.pub.host || !a.pub.ticket || a.max_cycles < 0) return hipErrorInvalidValue;
+  if (a.cyc.nlev == 3 && a.cyc.q[0] == 4)
+    hipLaunchKernelGGL(k_small_solve<true>, dim3(1), dim3(kTailThreads), 0, s, a);
+  else if (a.cyc.nlev == 2 && a.cyc.q[0] == 3)
+    hipLaunchKernelGGL(k_small_solve<false>, dim3(1), dim3(kTailThreads), 0, s, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -264,3 +264,40 @@ def test_norm_passes_through_lds(N):
     pa, _, _ = a.solve(f, p0.clone(), tol=1e-12, max_cycles=80)
     assert hm[0] == ha[0]
     assert float((pm - pa).norm() / pa.norm()) <= 1e-9
+
+
+@pytest.mark.parametrize("N", [8, 16])
+def test_small_solve_in_one_launch(N):
+    """FP64 V-cycles on the grids solved in one launch: the history cycle by cycle against
+    the oracle's (to 1e-6 of each entry, down to 1e-8 where rounding takes over), more
+    entries than come back with the scalars, a warm start, and the ways to end: no
+    convergence, no cycles allowed, f constant, f not finite, an item of a batch on a lane."""
+    from paper_1410_2240_amd import MG, MGError
+    inp = fields.make("c2", N)
+    H = omg.setup(*face_coeffs_from_rho(inp.rho, inp.mask), inp.mask, inp.h)
+    rho, mask, f = dev(inp.rho), dev(inp.mask), dev(inp.f)
+    mg = MG.from_rho(rho, mask)
+    print(f"small solve {N}^3", flush=True)
+    p, hist, stats = mg.solve(f, tol=1e-30, max_cycles=150, raise_on_fail=False)
+    assert stats["status"] == -4 and stats["cycles"] == 150 and len(hist) == 151
+    _, want = omg.solve(H, inp.f, tol=1e-9, max_cycles=60)
+    for got, ref in zip(hist, want):
+        if ref > 1e-8:
+            assert abs(got - ref) <= 1e-6 * ref
+    assert max(hist[40:]) <= 1e-12
+    q, again, stats = mg.solve(f, p.clone(), tol=1e-10)
+    assert stats["cycles"] == 0 and len(again) == 1
+    assert float((p - q).abs().max()) <= 1e-13 * float(p.abs().max())
+    q, one, stats = mg.solve(f, tol=1e-10, max_cycles=0, raise_on_fail=False)
+    assert stats["status"] == -4 and one == hist[:1] and float(q.abs().max()) == 0.0
+    q, zero, stats = mg.solve(torch.full_like(f, 3.0), torch.ones_like(f))
+    assert stats["status"] == 0 and zero == [0.0] and float(q.abs().max()) == 0.0
+    bad = f.clone()
+    bad[tuple(int(x) for x in np.argwhere(inp.mask != 0)[5])] = float("nan")
+    with pytest.raises(MGError):
+        mg.solve(bad)
+    batch = torch.stack([f, 2.0 * f, torch.flip(f, [2]) * mask])
+    pl, hl, _ = MG.from_rho(rho, mask, lanes=2).solve(batch, tol=1e-9)
+    for b in range(3):
+        pb, hb, _ = mg.solve(batch[b].contiguous(), tol=1e-9)
+        assert hb == hl[b] and torch.equal(pb, pl[b])
