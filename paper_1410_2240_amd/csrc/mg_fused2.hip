@@ -90,10 +90,25 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // pout * w over the tile.  Its first pre-smoothing (ZIN, f = r): the residual update
 // r - alpha w (alpha = d.r / d.w) is formed where f is read and swept with, written to
 // x.rnew on the tile, and the sum is that of its squares.
-template <typename T, bool ZIN, bool W>
+//
+// PRO (post-smoothing of a cycle): sweeps pin + the trilinear interpolation of the coarse
+// correction ec on active cells, added where a plane is staged, so the prolongation is not
+// a pass of its own over pin.  The coarse box around the staged one lives in LDS, three
+// planes in turn (fine planes 2K and 2K+1 take coarse planes K-1, K and K, K+1; the slots
+// go round with the six fine planes, so they too are known at compile time).  Room for it
+// comes from the densities: only planes k+2 .. k+5 of them are ever used, so they keep four
+// slots here, indexed at run time.  The weights are applied as the prolongation pass
+// does (x, then y, then z, each a fused multiply-add): the same bits.  A cycle in FP64
+// 4.57 -> 4.24 ms at 512^3 and 670 -> 635 us at 256^3 (the pass of its own took 0.49 ms and
+// 62 us), in FP32 2.38 -> 2.32 ms and 393 -> 382 us (0.25 ms and 36 us; this pass is held by
+// its vector instructions).  One spilled register costs more than the whole gain (FP32 with
+// 26 of them: 475 us), so FP32 and the pass with sums keep the ring's f in LDS, and FP32
+// forms its LDS offsets in each step.
+template <typename T, bool ZIN, bool W, bool PRO>
 __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2(
-    const T* __restrict__ pin, T* __restrict__ pout, const T* __restrict__ f, const T* __restrict__ rt, int q, int kc,
-    T h2, int first, const double* __restrict__ fshift, Fused2Extra x) {
+    const T* __restrict__ pin, T* __restrict__ pout, const T* __restrict__ f, const T* __restrict__ rt,
+    const T* __restrict__ ec, int q, int kc, T h2, int first, const double* __restrict__ fshift, Fused2Extra x) {
+  static_assert(!(PRO && ZIN), "the correction is added to an iterate");
   constexpr bool ZW = W && !ZIN, RU = W && ZIN;
   const double* __restrict__ w = x.w;
   using V2 = typename buf::Vec2<T>::type;
@@ -107,7 +122,14 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   constexpr int kRingPairs = 6 * kWP + kTY * 4;
   static_assert(kRingPairs <= kNT, "one ring pair per thread at most");
   __shared__ T P[kSlots][kH][2][kWP];
-  __shared__ T R[kSlots][kH][2][kWP];
+  constexpr int kRSlots = PRO ? 4 : kSlots;
+  __shared__ T R[kRSlots][kH][2][kWP];
+  constexpr int kCW = kWP + 2, kCH = kH / 2 + 2;   // coarse box: the staged one's parents and a ring
+  constexpr int kCCells = kCW * kCH;
+  static_assert(!PRO || kCCells <= kNT, "one coarse cell per thread");
+  __shared__ T C[PRO ? 3 : 1][PRO ? kCCells : 1];
+  constexpr bool kRingF = PRO && (sizeof(T) == 4 || W);
+  __shared__ T FG[kRingF ? 4 : 1][2][kRingF ? kRingPairs : 1];   // f of the ring pairs (its own column each)
   const int n = 1 << q;
   const int tid = threadIdx.x;
   const int G = gridDim.x, bid = blockIdx.x;
@@ -128,6 +150,12 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   constexpr int kSlot = kH * kRow;   // floats per slot
   T* const Pf = &P[0][0][0][0];
   T* const Rf = &R[0][0][0][0];
+  const int ks = k0 - 6;   // even: chunks start at multiples of kc >= 8
+  // offset of a plane of densities: of its compile-time slot S, or by the plane itself
+  auto rslot = [&](int kk, auto s_tag) {
+    if constexpr (PRO) return ((kk - ks) & 3) * kSlot;
+    else return std::integral_constant<int, decltype(s_tag)::value * kSlot>{};
+  };
   using std::integral_constant;
 
   // ---- staging: box pair e = tid + u * kNT of each plane, global -> registers -> LDS
@@ -149,17 +177,57 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
       rn[u] = ld2(rk, so[u], T(0));
     }
   };
+  // PRO: this thread's cell of the coarse box, on the plane of fine plane kk (the parent is
+  // reused beyond a z wall)
+  T cnext = T(0);
+  const unsigned co = PRO && tid < kCCells ? off_of<T>((i0 >> 1) - 3 + tid % kCW, (j0 >> 1) - 3 + tid / kCW, q - 1) : 0u;
+  auto coarse_load = [&](int kk) {
+    if constexpr (PRO) return buf::ld1(plane_rsrc(ec, min(max(kk >> 1, 0), (n >> 1) - 1), q - 1), co, T(0));
+    else return T(0);
+  };
+  auto coarse_store = [&](auto s_tag, T v) {
+    if constexpr (PRO) {
+      if (tid < kCCells) C[decltype(s_tag)::value][tid] = v;
+    }
+  };
+  // 64 times the correction of the staged pair at LDS offset e (box row r, pair x) of a fine
+  // plane whose distance from ks is U mod 6: its parents' plane and the nearer neighbour's,
+  // with weights 3 and 1 in each direction (scaling by powers of two is exact: the bits are
+  // those of 3/4 and 1/4)
+  auto correction = [&](int e, auto u_tag) {
+    constexpr int U = decltype(u_tag)::value;
+    constexpr int K1 = (U / 2) % 3, K2 = (U & 1) ? (K1 + 1) % 3 : (K1 + 2) % 3;
+    const int r = e / kRow, x = e % kRow;
+    const int c = ((r >> 1) + 1) * kCW + x + 1, cy = (r & 1) ? c + kCW : c - kCW;
+    // x weights: the even cell towards at-1, the odd one at+1
+    auto row = [&](const T* p, int at) {
+      const T e1 = p[at];
+      return V2{fma_t(T(3), e1, p[at - 1]), fma_t(T(3), e1, p[at + 1])};
+    };
+    auto plane = [&](const T* p) {
+      const V2 a1 = row(p, c), a2 = row(p, cy);
+      return V2{fma_t(T(3), a1.x, a2.x), fma_t(T(3), a1.y, a2.y)};
+    };
+    const V2 lo = plane(C[PRO ? K1 : 0]), hi = plane(C[PRO ? K2 : 0]);
+    return V2{fma_t(T(3), lo.x, hi.x), fma_t(T(3), lo.y, hi.y)};
+  };
   // plane kk into slot S; densities beyond a z wall are +inf, replaced here (not at the load)
   auto store = [&](int kk, auto s_tag) {
     constexpr int S = decltype(s_tag)::value * kSlot;
+    const auto SR = rslot(kk, s_tag);
     if (kk >= 0 && kk < n) {   // the same for the whole workgroup: a branch, not selects
 #pragma unroll
       for (int u = 0; u < kPer; ++u) {
         if (sl[u] >= 0) {
+          if constexpr (PRO) {
+            const V2 add = correction(sl[u], s_tag);
+            if (rn[u].x < inf) pn[u].x = fma_t(T(1) / 64, add.x, pn[u].x);
+            if (rn[u].y < inf) pn[u].y = fma_t(T(1) / 64, add.y, pn[u].y);
+          }
           Pf[S + sl[u]] = pn[u].x;
           Pf[S + sl[u] + kWP] = pn[u].y;
-          Rf[S + sl[u]] = rn[u].x;
-          Rf[S + sl[u] + kWP] = rn[u].y;
+          Rf[SR + sl[u]] = rn[u].x;
+          Rf[SR + sl[u] + kWP] = rn[u].y;
         }
       }
     } else {
@@ -168,8 +236,8 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
         if (sl[u] >= 0) {
           Pf[S + sl[u]] = pn[u].x;
           Pf[S + sl[u] + kWP] = pn[u].y;
-          Rf[S + sl[u]] = inf;
-          Rf[S + sl[u] + kWP] = inf;
+          Rf[SR + sl[u]] = inf;
+          Rf[SR + sl[u] + kWP] = inf;
         }
       }
     }
@@ -212,11 +280,29 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   const unsigned gf_off = has_ring ? off_of<T>(i0 - 4 + 2 * gcp, gj, q) : 0u;
   const bool godd[2] = {((first + gj + 1) & 1) != 0, ((first + gj) & 1) != 0};
   const Cell gcell[2] = {cell_of(gr, gcp, godd[0]), cell_of(gr, gcp, godd[1])};
+  const int ring_off = gr * kRow + gcp;            // the ring pair's even column
+  // FP32 with the prolongation has no registers to keep both parities' offsets in: they are
+  // formed in every step from the pair's (the empty asm hides that they would be the same)
+  constexpr bool kReform = PRO && sizeof(T) == 4;
+  auto cell_at = [&](const Cell& kept, int even, bool odd) {
+    if constexpr (kReform) {
+      asm volatile("" : "+v"(even));
+      return odd ? Cell{even + kWP, even} : Cell{even, even + kWP - 1};
+    } else {
+      return kept;
+    }
+  };
   const int gd[2] = {ring_of<kTX, kTY>(gr, 2 * gcp + godd[0]), ring_of<kTX, kTY>(gr, 2 * gcp + godd[1])};
 
   // f of the owned pairs, plane kk at index (kk - ks) mod 6 (planes k .. k+3 in use at
   // step k, k+4 arriving)
-  V2 tfw[kSlots], gfw[kSlots];
+  // (kRingF: f of the ring pairs waits in LDS instead, planes k+1 .. k+3 in four slots, and
+  // only the plane that arrives is in registers)
+  V2 tfw[kSlots], gfw[kRingF ? 1 : kSlots];
+  auto ring_f = [&](int kk, auto s_tag, bool odd) {
+    if constexpr (kRingF) return FG[(kk - ks) & 3][odd ? 1 : 0][tid];
+    else return odd ? gfw[decltype(s_tag)::value].y : gfw[decltype(s_tag)::value].x;
+  };
   auto load_f = [&](int kk, V2& t, V2& g) {
     const Rsrc fk = plane_rsrc(f, kk, q);
     t = ld2(fk, tf_off, T(0));
@@ -230,8 +316,7 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   struct Faces {
     T xm, xp, ym, yp, zm, zp;
   };
-  auto faces = [&](auto s_tag, auto sa_tag, const Cell& x, T lo_r) {
-    constexpr int S = decltype(s_tag)::value * kSlot, SA = decltype(sa_tag)::value * kSlot;
+  auto faces = [&](auto S, auto SA, const Cell& x, T lo_r) {   // (S, SA: offsets of their densities)
     const T rc = Rf[S + x.own];
     return Faces{face_beta(Rf[S + x.left], rc), face_beta(rc, Rf[S + x.left + 1]),
                  face_beta(Rf[S + x.own - kRow], rc), face_beta(rc, Rf[S + x.own + kRow]),
@@ -243,8 +328,7 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   // whenever its column is worked on, also where its update is out of bounds (planes
   // beyond a wall hold +inf densities, which give faces of 0), so both are there
   // whenever B1 runs.
-  auto faces_b1 = [&](auto s_tag, const Cell& x, T zm, T zp) {
-    constexpr int S = decltype(s_tag)::value * kSlot;
+  auto faces_b1 = [&](auto S, const Cell& x, T zm, T zp) {
     const T rc = Rf[S + x.own];
     return Faces{face_beta(Rf[S + x.left], rc), face_beta(rc, Rf[S + x.left + 1]),
                  face_beta(Rf[S + x.own - kRow], rc), face_beta(rc, Rf[S + x.own + kRow]), zm, zp};
@@ -253,8 +337,7 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   // by the A1 update of one column and needed again by the B1 update of the other column
   // on the same plane a step later, so it is kept for it (one face fewer per step).
   constexpr bool kXKeep = sizeof(T) == 8;
-  auto faces_b1x = [&](auto s_tag, const Cell& x, T zm, T zp, T xpair, bool odd) {
-    constexpr int S = decltype(s_tag)::value * kSlot;
+  auto faces_b1x = [&](auto S, const Cell& x, T zm, T zp, T xpair, bool odd) {
     const T rc = Rf[S + x.own];
     const T xo = face_beta(rc, Rf[S + (odd ? x.left + 1 : x.left)]);   // the face away from the partner
     return Faces{odd ? xpair : xo, odd ? xo : xpair, face_beta(Rf[S + x.own - kRow], rc),
@@ -304,7 +387,13 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   T xt = T(0), xg = T(0);   // the pair's x face kept from the step before (tile, ring)
 
   // ---- prologue: planes ks .. ks+3 staged (slots 0..3), ks+4 in registers, f of ks .. ks+3
-  const int ks = k0 - 6;   // even: chunks start at multiples of kc >= 8
+  if constexpr (PRO) {
+    coarse_store(integral_constant<int, 0>{}, coarse_load(ks));
+    coarse_store(integral_constant<int, 1>{}, coarse_load(ks + 2));
+    coarse_store(integral_constant<int, 2>{}, coarse_load(ks + 4));
+    cnext = coarse_load(ks + 6);
+    __syncthreads();
+  }
   fetch(ks);
   store(ks, integral_constant<int, 0>{});
   fetch(ks + 1);
@@ -316,10 +405,10 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   fetch(ks + 4);
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
-    load_f(ks + d, tfw[d], gfw[d]);
+    load_f(ks + d, tfw[d], gfw[kRingF ? 0 : d]);   // (kRingF: the ring starts with ks+3)
     if constexpr (RU) {   // planes below the chunk: converted, not written; ks+3 in the first step
       load_w(ks + d);
-      if (d < 3) update_r(ks + d, tfw[d], gfw[d]);
+      if (d < 3) update_r(ks + d, tfw[d], gfw[kRingF ? 0 : d]);
     }
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -336,25 +425,38 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
     using S4 = integral_constant<int, (U + 4) % kSlots>;
     store(k + 4, S4{});
     fetch(k + 5);
+    if constexpr (PRO) {   // the next coarse plane: loaded in odd steps, stored in even ones
+      if constexpr (PAR == 0) coarse_store(integral_constant<int, ((U + 4) / 2 + 1) % 3>{}, cnext);
+      else cnext = coarse_load(k + 7);
+    }
+    const auto R2 = rslot(k + 2, S2{});
+    const auto R3 = rslot(k + 3, S3{});
+    const auto R4 = rslot(k + 4, S4{});
     if constexpr (RU) update_r(k + 3, tfw[S3::value], gfw[S3::value]);   // f and w came last step
-    load_f(k + 4, tfw[S4::value], gfw[S4::value]);
+    if constexpr (kRingF) {
+      if (has_ring) {
+        FG[(k + 3 - ks) & 3][0][tid] = gfw[0].x;
+        FG[(k + 3 - ks) & 3][1][tid] = gfw[0].y;
+      }
+    }
+    load_f(k + 4, tfw[S4::value], gfw[kRingF ? 0 : S4::value]);
     if constexpr (RU) load_w(k + 4);
     V2 wk{T(0), T(0)};   // ZW: w of the tile pair on plane k, read while the step runs
     if constexpr (ZW) wk = ld2(plane_rsrc(w, k, q), tf_off, 0.0);
     __syncthreads();
     const int ka = k + 3, kb = k + 2, kA = k + 1;
     {
-      const Cell c = tcell[PAR];
       const bool odd = todd[PAR];
+      const Cell c = cell_at(tcell[PAR], out_off, odd);
       const Faces a2f = ta[PAR], b2f = tb[PAR];   // from step k-2, before this step's A1, B1
-      ta[PAR] = faces(S3{}, S4{}, c, Rf[S2::value * kSlot + c.own]);
+      ta[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
       const T xprev = xt;
       if constexpr (kXKeep) xt = odd ? ta[PAR].xm : ta[PAR].xp;
       if (ka >= lo_a1 && ka < n)
         gs(S3{}, S4{}, c, ta[PAR], Pf[S2::value * kSlot + c.own], odd ? tfw[S3::value].y : tfw[S3::value].x);
       if (kb >= lo_b1 && kb < n) {
-        if constexpr (kXKeep) tb[PAR] = faces_b1x(S2{}, c, a2f.zp, ta[PAR].zm, xprev, odd);
-        else tb[PAR] = faces_b1(S2{}, c, a2f.zp, ta[PAR].zm);
+        if constexpr (kXKeep) tb[PAR] = faces_b1x(R2, c, a2f.zp, ta[PAR].zm, xprev, odd);
+        else tb[PAR] = faces_b1(R2, c, a2f.zp, ta[PAR].zm);
         gs(S2{}, S3{}, c, tb[PAR], Pf[S1::value * kSlot + c.own], odd ? tfw[S2::value].y : tfw[S2::value].x);
       }
       if (kA >= lo_a2 && kA < n)
@@ -372,25 +474,25 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
     }
     // the ring pair: as far as its ring distance allows (per lane)
     if (has_ring) {
-      const Cell c = gcell[PAR];
       const bool odd = godd[PAR];
+      const Cell c = cell_at(gcell[PAR], ring_off, odd);
       const int d = gd[PAR];
       const Faces a2f = ga[PAR];
       const T xgprev = xg;
       if (d <= 3) {   // every ring pair's columns are within 3 cells of the tile
-        ga[PAR] = faces(S3{}, S4{}, c, Rf[S2::value * kSlot + c.own]);
+        ga[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
         if constexpr (kXKeep) xg = odd ? ga[PAR].xm : ga[PAR].xp;
         if (ka >= lo_a1 && ka < n)
-          gs(S3{}, S4{}, c, ga[PAR], Pf[S2::value * kSlot + c.own], odd ? gfw[S3::value].y : gfw[S3::value].x);
+          gs(S3{}, S4{}, c, ga[PAR], Pf[S2::value * kSlot + c.own], ring_f(ka, S3{}, odd));
       }
       if (d <= 2 && kb >= lo_b1 && kb < n) {
         Faces fb;
-        if constexpr (kXKeep) fb = faces_b1x(S2{}, c, a2f.zp, ga[PAR].zm, xgprev, odd);
-        else fb = faces_b1(S2{}, c, a2f.zp, ga[PAR].zm);
-        gs(S2{}, S3{}, c, fb, Pf[S1::value * kSlot + c.own], odd ? gfw[S2::value].y : gfw[S2::value].x);
+        if constexpr (kXKeep) fb = faces_b1x(R2, c, a2f.zp, ga[PAR].zm, xgprev, odd);
+        else fb = faces_b1(R2, c, a2f.zp, ga[PAR].zm);
+        gs(S2{}, S3{}, c, fb, Pf[S1::value * kSlot + c.own], ring_f(kb, S2{}, odd));
       }
       if (d <= 1 && kA >= lo_a2 && kA < n)
-        gs(S1{}, S2{}, c, a2f, Pf[S0::value * kSlot + c.own], odd ? gfw[S1::value].y : gfw[S1::value].x);
+        gs(S1{}, S2{}, c, a2f, Pf[S0::value * kSlot + c.own], ring_f(kA, S1{}, odd));
     }
   };
   // kc + 6 steps, an even number, from an even plane; six to a round of the slots
@@ -430,11 +532,12 @@ int fused2_supported(int q) { return (1 << q) >= 128; }
 
 template <typename T>
 hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, int q, double h, int order,
-                              const double* fshift, int zero_in, hipStream_t s, int sharing, const Fused2Extra* x,
-                              int* nblocks) {
+                              const double* fshift, int zero_in, hipStream_t s, int sharing, const T* ec,
+                              const Fused2Extra* x, int* nblocks) {
   constexpr int TX = Shape<T>::TX, TY = Shape<T>::TY;
   const int n = 1 << q;
   if (!fused2_supported(q) || !rt || pin == pout) return hipErrorInvalidValue;
+  if (ec && zero_in) return hipErrorInvalidValue;
   const bool wx = x != nullptr && x->w != nullptr;
   if (wx && (sizeof(T) != 8 || !x->partials || !nblocks)) return hipErrorInvalidValue;
   if (wx && zero_in && (!x->rnew || static_cast<const void*>(x->rnew) == static_cast<const void*>(f) || !x->s_dr || !x->s_dw || !x->s_alpha || fshift))
@@ -455,29 +558,29 @@ hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, in
   const int first = order == 0 ? 0 : 1;   // pre-smoothing: red first; post-smoothing: black first
   const dim3 grid(static_cast<unsigned>(blocks)), block(TX / 2 * TY);
   const Fused2Extra none{};
+  auto launch = [&](auto kernel, const Fused2Extra& xa) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, pin, pout, f, rt, ec, q, kc, h2, first, fshift, xa);
+  };
   if (wx) {
     if constexpr (sizeof(T) == 8) {
-      if (zero_in)
-        hipLaunchKernelGGL((k_rbgs_fused2<T, true, true>), grid, block, 0, s, pin, pout, f, rt, q, kc, h2, first,
-                           fshift, *x);
-      else
-        hipLaunchKernelGGL((k_rbgs_fused2<T, false, true>), grid, block, 0, s, pin, pout, f, rt, q, kc, h2, first,
-                           fshift, *x);
+      if (zero_in) launch(k_rbgs_fused2<T, true, true, false>, *x);
+      else if (ec) launch(k_rbgs_fused2<T, false, true, true>, *x);
+      else return hipErrorInvalidValue;   // (the sum of z.w ends a cycle)
     }
     *nblocks = static_cast<int>(blocks);
   } else if (zero_in) {
-    hipLaunchKernelGGL((k_rbgs_fused2<T, true, false>), grid, block, 0, s, pin, pout, f, rt, q, kc, h2, first, fshift,
-                       none);
+    launch(k_rbgs_fused2<T, true, false, false>, none);
+  } else if (ec) {
+    launch(k_rbgs_fused2<T, false, false, true>, none);
   } else {
-    hipLaunchKernelGGL((k_rbgs_fused2<T, false, false>), grid, block, 0, s, pin, pout, f, rt, q, kc, h2, first,
-                       fshift, none);
+    launch(k_rbgs_fused2<T, false, false, false>, none);
   }
   return hipGetLastError();
 }
 
 template hipError_t launch_rbgs_fused2<float>(const float*, float*, const float*, const float*, int, double, int,
-                                              const double*, int, hipStream_t, int, const Fused2Extra*, int*);
+                                              const double*, int, hipStream_t, int, const float*, const Fused2Extra*, int*);
 template hipError_t launch_rbgs_fused2<double>(const double*, double*, const double*, const double*, int, double, int,
-                                               const double*, int, hipStream_t, int, const Fused2Extra*, int*);
+                                               const double*, int, hipStream_t, int, const double*, const Fused2Extra*, int*);
 
 }  // namespace mg

@@ -301,3 +301,25 @@ def test_small_solve_in_one_launch(N):
     for b in range(3):
         pb, hb, _ = mg.solve(batch[b].contiguous(), tol=1e-9)
         assert hb == hl[b] and torch.equal(pb, pl[b])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("N", [128, 256])
+def test_correction_inside_the_post_smoothing(N, dtype):
+    """A cycle whose post-smoothing pass adds the coarse correction itself (256^3; at 128^3
+    it has a pass of its own) against the same cycle step by step, bit for bit: two sweeps,
+    restriction, a cycle of the hierarchy one grid down, prolongation, two sweeps.  The
+    field has its body and both walls in reach of the interpolation."""
+    from paper_1410_2240_amd import MG
+    inp = fields.make("c5", N)
+    mg = MG.from_rho(dev(inp.rho), dev(inp.mask), mixed=True)
+    p, f = random_pair(inp, N, dtype)
+    print(f"correction inside post-smoothing {N}^3 {dtype}", flush=True)
+    got = mg.vcycle(p.clone(), f)
+    bx, by, bz, mask = mg.level_coeffs(1)
+    below = MG(bx, by, bz, mask, h=2.0 / N, mixed=True)
+    want = mg.smooth(0, p.clone(), f, 2, 0)
+    fc = mg.residual_restrict(0, want, f)
+    ec = below.vcycle(torch.zeros_like(fc), fc)
+    want = mg.smooth(0, mg.prolong_add(0, ec, want), f, 2, 1)
+    assert torch.equal(got, want)
