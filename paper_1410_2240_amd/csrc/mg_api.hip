@@ -157,11 +157,13 @@ const T* box_rt(const mg_ctx* c, int l) {
   return c->view<T>(l).rt;
 }
 
-// Grids whose sweeps run two to a pass: the density form (the finest grid of a context
-// set up from rho, in its FP64 cycles and in a mixed context's FP32 cycles), 128^3 and up.
+// Grids whose sweeps run two to a pass: 128^3 and up, but not a 128^3 grid's face arrays in
+// FP32 (four sweeps 64.2 us in two passes of 128 workgroups, 60.6 us in four one-pass
+// sweeps).
 template <typename T>
 bool two_sweep_grid(const mg_ctx* c, int l) {
-  return c->view<T>(l).rt != nullptr && mg::fused2_supported(c->lv[l].q);
+  const int q = c->lv[l].q;
+  return mg::fused2_supported(q) && (sizeof(T) == 8 || c->view<T>(l).rt != nullptr || q > 7);
 }
 
 // What an FP64 two-sweep pass of flexible CG also does (launch_rbgs_fused2), and where
@@ -175,7 +177,11 @@ template <typename T>
 hipError_t launch_two_sweeps(const mg_ctx* c, int l, const T* pin, T* pout, const T* f, const double* fshift, int order,
                              bool zero_in, const T* ec = nullptr, const ZwSums* zw = nullptr) {
   const Level& a = c->lv[l];
-  return mg::launch_rbgs_fused2(pin, pout, f, c->view<T>(l).rt, a.q, a.h, order, fshift, zero_in ? 1 : 0, c->stream,
+  const View<T> v = c->view<T>(l);
+  // FP64 at 128^3, whose arrays stay in the last-level cache: the stored faces are read rather
+  // than formed (the same bits; four sweeps 62.2 us, 68.8 us from the density)
+  const T* rt = sizeof(T) == 8 && a.q == 7 ? nullptr : v.rt;
+  return mg::launch_rbgs_fused2(pin, pout, f, v.bx, v.by, v.bz, rt, a.q, a.h, order, fshift, zero_in ? 1 : 0, c->stream,
                                 c->sharing, ec, zw ? &zw->x : nullptr, zw ? zw->nblocks : nullptr);
 }
 
@@ -299,7 +305,7 @@ int vcycle(mg_ctx* c, int l, T* p, const T* f, const double* fshift, bool zero_i
     // 256^3 and up: the post-smoothing pass adds the correction itself (at 128^3, where the
     // prolongation is 10 us, its longer steps cost as much: 160 us a cycle both ways in FP64,
     // 151 against 148 us in FP32)
-    const bool within = c->lv[l].n >= 256;
+    const bool within = c->lv[l].n >= 256 && c->view<T>(l).rt;
     if (!within) MG_HIP(mg::launch_prolong_add<T>(next.e, t, c->lv[l].mask, c->lv[l].q, c->stream));
     MG_HIP(launch_two_sweeps<T>(c, l, t, p, f, fshift, MG_POST, false, within ? next.e : nullptr, zw));
     return MG_OK;
@@ -545,7 +551,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
     // and, where the workspace holds a second residual, the residual update out of its first
     // (256^3 and up: at 128^3 the separate passes take 18 us of a 250 us step, and a setup
     // from rho keeps the bits of one from face arrays)
-    const bool zw_fused = !mixed && two_sweep_grid<double>(c, 0) && a.n >= 256;
+    const bool zw_fused = !mixed && a.rt && two_sweep_grid<double>(c, 0) && a.n >= 256;
     const bool ru_fused = zw_fused && c->kr2 != nullptr;
     double* kr_other = c->kr2;
     auto precondition_first_sweep = [&]() -> int {

@@ -1,6 +1,6 @@
-// Two red-black Gauss-Seidel sweeps in a single pass over memory (CDNA4, density form:
-// the finest grid of a hierarchy built from rho, FP64 cycles and the FP32 cycles of a
-// mixed-precision solve).
+// Two red-black Gauss-Seidel sweeps in a single pass over memory (CDNA4; from the density
+// form, the finest grid of a hierarchy built from rho, or from face arrays; FP64 cycles and
+// the FP32 cycles of a mixed-precision solve).
 //
 // A V(2,2) cycle smooths twice in a row before the restriction and twice after the
 // prolongation.  The one-pass sweep (mg_fused.hip) reads p, f and the density once per
@@ -104,11 +104,23 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // its vector instructions).  One spilled register costs more than the whole gain (FP32 with
 // 26 of them: 475 us), so FP32 and the pass with sums keep the ring's f in LDS, and FP32
 // forms its LDS offsets in each step.
-template <typename T, bool ZIN, bool W, bool PRO>
+//
+// RHO: faces from the density form rt.  Otherwise rt is bx, and with by and bz the faces
+// are read, a plane ahead of the first update that needs them: a pair's faces on plane k+3
+// come as five loads; those of its colour-A cell are used by A1 in that step, the x and y
+// faces of the other cell by B1 in the next, and both are kept two steps for A2 and B2 as
+// above.  LDS then stages p alone, and the registers for the loads in flight come from f and
+// from the faces B1 waits for, which wait there, each thread its own column of words.  Four
+// sweeps, against four one-pass sweeps: FP64 335 us (697) at 256^3 and 2.36 ms (4.65) at
+// 512^3; FP32 214 us (400) and 1.42 ms (2.67).  Here too a spill costs more than the pass
+// gains: with 15 of them FP64 took 684 us and 5.12 ms.
+template <typename T, bool ZIN, bool W, bool PRO, bool RHO>
 __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2(
     const T* __restrict__ pin, T* __restrict__ pout, const T* __restrict__ f, const T* __restrict__ rt,
-    const T* __restrict__ ec, int q, int kc, T h2, int first, const double* __restrict__ fshift, Fused2Extra x) {
+    const T* __restrict__ by, const T* __restrict__ bz, const T* __restrict__ ec, int q, int kc, T h2, int first,
+    const double* __restrict__ fshift, Fused2Extra x) {
   static_assert(!(PRO && ZIN), "the correction is added to an iterate");
+  static_assert(RHO || (!W && !PRO), "the sums and the correction are for the density form");
   constexpr bool ZW = W && !ZIN, RU = W && ZIN;
   const double* __restrict__ w = x.w;
   using V2 = typename buf::Vec2<T>::type;
@@ -122,14 +134,18 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   constexpr int kRingPairs = 6 * kWP + kTY * 4;
   static_assert(kRingPairs <= kNT, "one ring pair per thread at most");
   __shared__ T P[kSlots][kH][2][kWP];
-  constexpr int kRSlots = PRO ? 4 : kSlots;
-  __shared__ T R[kRSlots][kH][2][kWP];
+  constexpr int kRSlots = !RHO ? 1 : PRO ? 4 : kSlots;
+  __shared__ T R[kRSlots][RHO ? kH : 1][2][kWP];
+  __shared__ T FT[RHO ? 1 : 4][2][RHO ? 1 : kNT];   // faces read: f of the tile pairs, planes k .. k+3
+  __shared__ T BT[RHO ? 1 : 4][RHO ? 1 : kNT];      // and the x and y faces of their next B1,
+  constexpr bool kRingB = !RHO && sizeof(T) == 4;
   constexpr int kCW = kWP + 2, kCH = kH / 2 + 2;   // coarse box: the staged one's parents and a ring
   constexpr int kCCells = kCW * kCH;
   static_assert(!PRO || kCCells <= kNT, "one coarse cell per thread");
   __shared__ T C[PRO ? 3 : 1][PRO ? kCCells : 1];
-  constexpr bool kRingF = PRO && (sizeof(T) == 4 || W);
+  constexpr bool kRingF = (PRO && (sizeof(T) == 4 || W)) || !RHO;
   __shared__ T FG[kRingF ? 4 : 1][2][kRingF ? kRingPairs : 1];   // f of the ring pairs (its own column each)
+  __shared__ T BG[kRingB ? 4 : 1][kRingB ? kRingPairs : 1];   // FP32: of the ring pairs' too
   const int n = 1 << q;
   const int tid = threadIdx.x;
   const int G = gridDim.x, bid = blockIdx.x;
@@ -168,13 +184,13 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
     sl[u] = e < kBoxPairs ? r * kRow + x : -1;
     so[u] = e < kBoxPairs ? off_of<T>(i0 - 4 + 2 * x, j0 - 4 + r, q) : 0u;
   }
-  V2 pn[kPer], rn[kPer];
+  V2 pn[kPer], rn[RHO ? kPer : 1];
   auto fetch = [&](int kk) {   // a plane outside the grid reads 0
     const Rsrc pk = plane_rsrc(pin, kk, q), rk = plane_rsrc(rt, kk, q);
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
       pn[u] = ZIN ? V2{T(0), T(0)} : ld2(pk, so[u], T(0));
-      rn[u] = ld2(rk, so[u], T(0));
+      if constexpr (RHO) rn[u] = ld2(rk, so[u], T(0));
     }
   };
   // PRO: this thread's cell of the coarse box, on the plane of fine plane kk (the parent is
@@ -215,7 +231,15 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   auto store = [&](int kk, auto s_tag) {
     constexpr int S = decltype(s_tag)::value * kSlot;
     const auto SR = rslot(kk, s_tag);
-    if (kk >= 0 && kk < n) {   // the same for the whole workgroup: a branch, not selects
+    if constexpr (!RHO) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (sl[u] >= 0) {
+          Pf[S + sl[u]] = pn[u].x;
+          Pf[S + sl[u] + kWP] = pn[u].y;
+        }
+      }
+    } else if (kk >= 0 && kk < n) {   // the same for the whole workgroup: a branch, not selects
 #pragma unroll
       for (int u = 0; u < kPer; ++u) {
         if (sl[u] >= 0) {
@@ -281,9 +305,10 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   const bool godd[2] = {((first + gj + 1) & 1) != 0, ((first + gj) & 1) != 0};
   const Cell gcell[2] = {cell_of(gr, gcp, godd[0]), cell_of(gr, gcp, godd[1])};
   const int ring_off = gr * kRow + gcp;            // the ring pair's even column
-  // FP32 with the prolongation has no registers to keep both parities' offsets in: they are
-  // formed in every step from the pair's (the empty asm hides that they would be the same)
-  constexpr bool kReform = PRO && sizeof(T) == 4;
+  // FP32 with the prolongation or with faces read has no registers to keep both parities'
+  // offsets in: they are formed in every step from the pair's (the empty asm hides that they
+  // would be the same)
+  constexpr bool kReform = (PRO || !RHO) && sizeof(T) == 4;
   auto cell_at = [&](const Cell& kept, int even, bool odd) {
     if constexpr (kReform) {
       asm volatile("" : "+v"(even));
@@ -298,10 +323,14 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   // step k, k+4 arriving)
   // (kRingF: f of the ring pairs waits in LDS instead, planes k+1 .. k+3 in four slots, and
   // only the plane that arrives is in registers)
-  V2 tfw[kSlots], gfw[kRingF ? 1 : kSlots];
+  V2 tfw[RHO ? kSlots : 1], gfw[kRingF ? 1 : kSlots];
   auto ring_f = [&](int kk, auto s_tag, bool odd) {
     if constexpr (kRingF) return FG[(kk - ks) & 3][odd ? 1 : 0][tid];
     else return odd ? gfw[decltype(s_tag)::value].y : gfw[decltype(s_tag)::value].x;
+  };
+  auto tile_f = [&](int kk, auto s_tag, bool odd) {
+    if constexpr (!RHO) return FT[(kk - ks) & 3][odd ? 1 : 0][tid];
+    else return odd ? tfw[decltype(s_tag)::value].y : tfw[decltype(s_tag)::value].x;
   };
   auto load_f = [&](int kk, V2& t, V2& g) {
     const Rsrc fk = plane_rsrc(f, kk, q);
@@ -315,6 +344,31 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   // same column, on the same faces: they are kept in registers for it.
   struct Faces {
     T xm, xp, ym, yp, zm, zp;
+  };
+  // Faces read: those of a pair on one plane, its x faces, the low and high y faces of both
+  // cells, their low z faces and those of the plane above, loaded a step before A1 needs them
+  struct Raw {
+    T x0, x1, x2;
+    V2 ylo, yhi, zlo, zhi;
+  };
+  // byte offsets in a plane of the next pair in a row and of the pair in the row above
+  const unsigned xmask = (static_cast<unsigned>(sizeof(T)) << q) - 1, pmask = (static_cast<unsigned>(sizeof(T)) << (2 * q)) - 1;
+  auto load_faces = [&](int kk, unsigned o, Raw& r) {
+    if constexpr (kReform) asm volatile("" : "+v"(o));
+    const unsigned ox = (o & ~xmask) | ((o + 2 * sizeof(T)) & xmask), oy = (o + xmask + 1) & pmask;
+    const Rsrc xk = plane_rsrc(rt, kk, q), yk = plane_rsrc(by, kk, q), zk = plane_rsrc(bz, kk + 1, q);
+    const V2 xv = ld2(xk, o, T(0));
+    r.x0 = xv.x;
+    r.x1 = xv.y;
+    r.x2 = buf::ld1(xk, ox, T(0));
+    r.ylo = ld2(yk, o, T(0));
+    r.yhi = ld2(yk, oy, T(0));
+    r.zlo = r.zhi;
+    r.zhi = ld2(zk, o, T(0));
+  };
+  auto cell_faces = [&](const Raw& r, bool odd) {
+    return Faces{odd ? r.x1 : r.x0,       odd ? r.x2 : r.x1,       odd ? r.ylo.y : r.ylo.x,
+                 odd ? r.yhi.y : r.yhi.x, odd ? r.zlo.y : r.zlo.x, odd ? r.zhi.y : r.zhi.x};
   };
   auto faces = [&](auto S, auto SA, const Cell& x, T lo_r) {   // (S, SA: offsets of their densities)
     const T rc = Rf[S + x.own];
@@ -403,12 +457,29 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   fetch(ks + 3);
   store(ks + 3, integral_constant<int, 3>{});
   fetch(ks + 4);
+  Raw traw{}, graw{};
+  Faces gnext{};   // faces read: of the ring pair's next B1
+  if constexpr (!RHO) {   // (the planes below ks+3 are only staged)
+    traw.zhi = ld2(plane_rsrc(bz, ks + 3, q), tf_off, T(0));
+    load_faces(ks + 3, tf_off, traw);
+    if (has_ring) {
+      graw.zhi = ld2(plane_rsrc(bz, ks + 3, q), gf_off, T(0));
+      load_faces(ks + 3, gf_off, graw);
+    }
 #pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    load_f(ks + d, tfw[d], gfw[kRingF ? 0 : d]);   // (kRingF: the ring starts with ks+3)
+    for (int x = 0; x < 4; ++x) {
+      BT[x][tid] = T(0);
+      if constexpr (kRingB) {
+        if (has_ring) BG[x][tid] = T(0);
+      }
+    }
+  }
+#pragma unroll
+  for (int d = RHO ? 0 : 3; d < 4; ++d) {
+    load_f(ks + d, tfw[RHO ? d : 0], gfw[kRingF ? 0 : d]);   // (kRingF: the ring starts with ks+3)
     if constexpr (RU) {   // planes below the chunk: converted, not written; ks+3 in the first step
       load_w(ks + d);
-      if (d < 3) update_r(ks + d, tfw[d], gfw[kRingF ? 0 : d]);
+      if (d < 3) update_r(ks + d, tfw[RHO ? d : 0], gfw[kRingF ? 0 : d]);
     }
   }
   __builtin_amdgcn_s_waitcnt(0);
@@ -439,7 +510,20 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
         FG[(k + 3 - ks) & 3][1][tid] = gfw[0].y;
       }
     }
-    load_f(k + 4, tfw[S4::value], gfw[kRingF ? 0 : S4::value]);
+    Faces tfa{}, tfb{}, tbn{};
+    if constexpr (!RHO) {   // plane k+3's f and faces came last step
+      FT[(k + 3 - ks) & 3][0][tid] = tfw[0].x;
+      FT[(k + 3 - ks) & 3][1][tid] = tfw[0].y;
+      tbn = Faces{BT[0][tid], BT[1][tid], BT[2][tid], BT[3][tid], T(0), T(0)};
+      tfa = cell_faces(traw, todd[PAR]);
+      tfb = cell_faces(traw, !todd[PAR]);
+      BT[0][tid] = tfb.xm;
+      BT[1][tid] = tfb.xp;
+      BT[2][tid] = tfb.ym;
+      BT[3][tid] = tfb.yp;
+      load_faces(k + 4, tf_off, traw);
+    }
+    load_f(k + 4, tfw[RHO ? S4::value : 0], gfw[kRingF ? 0 : S4::value]);
     if constexpr (RU) load_w(k + 4);
     V2 wk{T(0), T(0)};   // ZW: w of the tile pair on plane k, read while the step runs
     if constexpr (ZW) wk = ld2(plane_rsrc(w, k, q), tf_off, 0.0);
@@ -449,20 +533,25 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
       const bool odd = todd[PAR];
       const Cell c = cell_at(tcell[PAR], out_off, odd);
       const Faces a2f = ta[PAR], b2f = tb[PAR];   // from step k-2, before this step's A1, B1
-      ta[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
       const T xprev = xt;
-      if constexpr (kXKeep) xt = odd ? ta[PAR].xm : ta[PAR].xp;
+      if constexpr (RHO) {
+        ta[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
+        if constexpr (kXKeep) xt = odd ? ta[PAR].xm : ta[PAR].xp;
+      } else {
+        ta[PAR] = tfa;
+      }
       if (ka >= lo_a1 && ka < n)
-        gs(S3{}, S4{}, c, ta[PAR], Pf[S2::value * kSlot + c.own], odd ? tfw[S3::value].y : tfw[S3::value].x);
+        gs(S3{}, S4{}, c, ta[PAR], Pf[S2::value * kSlot + c.own], tile_f(ka, S3{}, odd));
       if (kb >= lo_b1 && kb < n) {
-        if constexpr (kXKeep) tb[PAR] = faces_b1x(R2, c, a2f.zp, ta[PAR].zm, xprev, odd);
+        if constexpr (!RHO) tb[PAR] = Faces{tbn.xm, tbn.xp, tbn.ym, tbn.yp, a2f.zp, ta[PAR].zm};
+        else if constexpr (kXKeep) tb[PAR] = faces_b1x(R2, c, a2f.zp, ta[PAR].zm, xprev, odd);
         else tb[PAR] = faces_b1(R2, c, a2f.zp, ta[PAR].zm);
-        gs(S2{}, S3{}, c, tb[PAR], Pf[S1::value * kSlot + c.own], odd ? tfw[S2::value].y : tfw[S2::value].x);
+        gs(S2{}, S3{}, c, tb[PAR], Pf[S1::value * kSlot + c.own], tile_f(kb, S2{}, odd));
       }
       if (kA >= lo_a2 && kA < n)
-        gs(S1{}, S2{}, c, a2f, Pf[S0::value * kSlot + c.own], odd ? tfw[S1::value].y : tfw[S1::value].x);
+        gs(S1{}, S2{}, c, a2f, Pf[S0::value * kSlot + c.own], tile_f(kA, S1{}, odd));
       if (k >= k0 && k < n) {
-        gs(S0{}, S1{}, c, b2f, below_p[PAR], odd ? tfw[S0::value].y : tfw[S0::value].x);
+        gs(S0{}, S1{}, c, b2f, below_p[PAR], tile_f(k, S0{}, odd));
         // plane k is final in both columns of the pair (the other one since A2 at step k-1)
         const T v0 = Pf[S0::value * kSlot + out_off], v1 = Pf[S0::value * kSlot + out_off + kWP];
         *reinterpret_cast<V2*>(reinterpret_cast<char*>(pout + (static_cast<long long>(k) << (2 * q))) + tf_off) =
@@ -478,16 +567,37 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
       const Cell c = cell_at(gcell[PAR], ring_off, odd);
       const int d = gd[PAR];
       const Faces a2f = ga[PAR];
+      Faces gfa{}, gbn{};
+      if constexpr (!RHO) {   // (here, so that these are registers in the ring's part alone)
+        gfa = cell_faces(graw, odd);
+        const Faces gfb = cell_faces(graw, !odd);
+        if constexpr (kRingB) {
+          gbn = Faces{BG[0][tid], BG[1][tid], BG[2][tid], BG[3][tid], T(0), T(0)};
+          BG[0][tid] = gfb.xm;
+          BG[1][tid] = gfb.xp;
+          BG[2][tid] = gfb.ym;
+          BG[3][tid] = gfb.yp;
+        } else {
+          gbn = gnext;
+          gnext = gfb;
+        }
+        load_faces(k + 4, gf_off, graw);
+      }
       const T xgprev = xg;
       if (d <= 3) {   // every ring pair's columns are within 3 cells of the tile
-        ga[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
-        if constexpr (kXKeep) xg = odd ? ga[PAR].xm : ga[PAR].xp;
+        if constexpr (RHO) {
+          ga[PAR] = faces(R3, R4, c, Rf[R2 + c.own]);
+          if constexpr (kXKeep) xg = odd ? ga[PAR].xm : ga[PAR].xp;
+        } else {
+          ga[PAR] = gfa;
+        }
         if (ka >= lo_a1 && ka < n)
           gs(S3{}, S4{}, c, ga[PAR], Pf[S2::value * kSlot + c.own], ring_f(ka, S3{}, odd));
       }
       if (d <= 2 && kb >= lo_b1 && kb < n) {
         Faces fb;
-        if constexpr (kXKeep) fb = faces_b1x(R2, c, a2f.zp, ga[PAR].zm, xgprev, odd);
+        if constexpr (!RHO) fb = Faces{gbn.xm, gbn.xp, gbn.ym, gbn.yp, a2f.zp, ga[PAR].zm};
+        else if constexpr (kXKeep) fb = faces_b1x(R2, c, a2f.zp, ga[PAR].zm, xgprev, odd);
         else fb = faces_b1(R2, c, a2f.zp, ga[PAR].zm);
         gs(S2{}, S3{}, c, fb, Pf[S1::value * kSlot + c.own], ring_f(kb, S2{}, odd));
       }
@@ -531,15 +641,16 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
 int fused2_supported(int q) { return (1 << q) >= 128; }
 
 template <typename T>
-hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, int q, double h, int order,
-                              const double* fshift, int zero_in, hipStream_t s, int sharing, const T* ec,
-                              const Fused2Extra* x, int* nblocks) {
+hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt,
+                              int q, double h, int order, const double* fshift, int zero_in, hipStream_t s, int sharing,
+                              const T* ec, const Fused2Extra* x, int* nblocks) {
   constexpr int TX = Shape<T>::TX, TY = Shape<T>::TY;
   const int n = 1 << q;
-  if (!fused2_supported(q) || !rt || pin == pout) return hipErrorInvalidValue;
-  if (ec && zero_in) return hipErrorInvalidValue;
+  if (!fused2_supported(q) || (!rt && (!bx || !by || !bz)) || pin == pout)
+    return hipErrorInvalidValue;
+  if (ec && (zero_in || !rt)) return hipErrorInvalidValue;
   const bool wx = x != nullptr && x->w != nullptr;
-  if (wx && (sizeof(T) != 8 || !x->partials || !nblocks)) return hipErrorInvalidValue;
+  if (wx && (sizeof(T) != 8 || !rt || !x->partials || !nblocks)) return hipErrorInvalidValue;
   if (wx && zero_in && (!x->rnew || static_cast<const void*>(x->rnew) == static_cast<const void*>(f) || !x->s_dr || !x->s_dw || !x->s_alpha || fshift))
     return hipErrorInvalidValue;
   const long long tiles = static_cast<long long>(n / TX) * (n / TY);
@@ -558,29 +669,33 @@ hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, in
   const int first = order == 0 ? 0 : 1;   // pre-smoothing: red first; post-smoothing: black first
   const dim3 grid(static_cast<unsigned>(blocks)), block(TX / 2 * TY);
   const Fused2Extra none{};
-  auto launch = [&](auto kernel, const Fused2Extra& xa) {
-    hipLaunchKernelGGL(kernel, grid, block, 0, s, pin, pout, f, rt, ec, q, kc, h2, first, fshift, xa);
+  auto launch = [&](auto kernel, const T* c0, const T* c1, const T* c2, const Fused2Extra& xa) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, s, pin, pout, f, c0, c1, c2, ec, q, kc, h2, first, fshift, xa);
   };
+  auto from_rho = [&](auto kernel, const Fused2Extra& xa) { launch(kernel, rt, nullptr, nullptr, xa); };
   if (wx) {
     if constexpr (sizeof(T) == 8) {
-      if (zero_in) launch(k_rbgs_fused2<T, true, true, false>, *x);
-      else if (ec) launch(k_rbgs_fused2<T, false, true, true>, *x);
+      if (zero_in) from_rho(k_rbgs_fused2<T, true, true, false, true>, *x);
+      else if (ec) from_rho(k_rbgs_fused2<T, false, true, true, true>, *x);
       else return hipErrorInvalidValue;   // (the sum of z.w ends a cycle)
     }
     *nblocks = static_cast<int>(blocks);
+  } else if (!rt) {
+    if (zero_in) launch(k_rbgs_fused2<T, true, false, false, false>, bx, by, bz, none);
+    else launch(k_rbgs_fused2<T, false, false, false, false>, bx, by, bz, none);
   } else if (zero_in) {
-    launch(k_rbgs_fused2<T, true, false, false>, none);
+    from_rho(k_rbgs_fused2<T, true, false, false, true>, none);
   } else if (ec) {
-    launch(k_rbgs_fused2<T, false, false, true>, none);
+    from_rho(k_rbgs_fused2<T, false, false, true, true>, none);
   } else {
-    launch(k_rbgs_fused2<T, false, false, false>, none);
+    from_rho(k_rbgs_fused2<T, false, false, false, true>, none);
   }
   return hipGetLastError();
 }
 
-template hipError_t launch_rbgs_fused2<float>(const float*, float*, const float*, const float*, int, double, int,
+template hipError_t launch_rbgs_fused2<float>(const float*, float*, const float*, const float*, const float*, const float*, const float*, int, double, int,
                                               const double*, int, hipStream_t, int, const float*, const Fused2Extra*, int*);
-template hipError_t launch_rbgs_fused2<double>(const double*, double*, const double*, const double*, int, double, int,
+template hipError_t launch_rbgs_fused2<double>(const double*, double*, const double*, const double*, const double*, const double*, const double*, int, double, int,
                                                const double*, int, hipStream_t, int, const double*, const Fused2Extra*, int*);
 
 }  // namespace mg

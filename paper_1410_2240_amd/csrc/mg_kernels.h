@@ -176,20 +176,20 @@ struct Fused2Extra {
   const double* s_dw = nullptr;
   double* s_alpha = nullptr;        // also stored here
 };
-// Two red-black sweeps in one pass (density form, grids of 128^3 and up): pin -> pout
-// (distinct), order as launch_rbgs_fused; bit for bit two one-pass sweeps.  With x->w
-// (FP64): one partial sum per workgroup into x->partials, their number into *nblocks
-// (at most kNumPartials); without zero_in the sum is pout . w; with zero_in (the first
+// Two red-black sweeps in one pass (grids of 128^3 and up): pin -> pout (distinct), order
+// and rt as launch_rbgs_fused; bit for bit two one-pass sweeps.  With x->w (FP64, density
+// form): one partial sum per workgroup into x->partials, their number into *nblocks (at
+// most kNumPartials); without zero_in the sum is pout . w; with zero_in (the first
 // pre-smoothing of a preconditioner, f = r, no fshift) the pass sweeps with and writes
 // r - alpha w to x->rnew (not f), and the sum is its squared norm.  sharing: how many
 // right-hand sides are being solved at once (the split into z-chunks follows it).  ec (not
-// with zero_in; needed for the sum of pout . w): the coarse correction of the grid below,
+// with zero_in; density form; needed for the sum of pout . w): the coarse correction of the grid below,
 // added to pin as launch_prolong_add does, bit for bit; pin itself is not changed.
 int fused2_supported(int q);
 template <typename T>
-hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* rt, int q, double h, int order,
-                              const double* fshift, int zero_in, hipStream_t s, int sharing, const T* ec = nullptr,
-                              const Fused2Extra* x = nullptr, int* nblocks = nullptr);
+hipError_t launch_rbgs_fused2(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt,
+                              int q, double h, int order, const double* fshift, int zero_in, hipStream_t s, int sharing,
+                              const T* ec = nullptr, const Fused2Extra* x = nullptr, int* nblocks = nullptr);
 template <typename T>
 hipError_t launch_rbgs_fused(const T* pin, T* pout, const T* f, const T* bx, const T* by, const T* bz, const T* rt,
                              int q, double h, int order, const double* fshift, int zero_in, hipStream_t s);

@@ -323,3 +323,25 @@ def test_correction_inside_the_post_smoothing(N, dtype):
     ec = below.vcycle(torch.zeros_like(fc), fc)
     want = mg.smooth(0, mg.prolong_add(0, ec, want), f, 2, 1)
     assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("N", [128, 256])
+def test_two_sweep_pass_from_face_arrays(N, dtype):
+    """The two-sweep pass reading face arrays (FP32 from 256^3) against one-pass sweeps, bit
+    for bit: random faces of contrast 1000 with a body, the bottom wall and the top one, both
+    orders, even and odd counts."""
+    from paper_1410_2240_amd import MG
+    bx, by, bz, mask = raw_problem(N, N)
+    mg = MG(dev(bx), dev(by), dev(bz), dev(mask), mixed=True)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    live = mg.level_coeffs(0)[3].bool()
+    for order in (0, 1):
+        for sweeps in (2, 3, 4):
+            print(f"two-sweep pass, faces {N}^3 {dtype} order={order} sweeps={sweeps}", flush=True)
+            p, f = (torch.randn(bx.shape, generator=g, device="cuda", dtype=dtype) * live for _ in range(2))
+            got = mg.smooth(0, p.clone(), f, sweeps, order)
+            want = p.clone()
+            for _ in range(sweeps):
+                want = mg.smooth(0, want, f, 1, order)
+            assert torch.equal(got, want), (order, sweeps)
