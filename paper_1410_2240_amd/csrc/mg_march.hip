@@ -832,6 +832,97 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_lds(MarchArgs<double> a)
   }
 }
 
+// FCGX on 32^3 and 64^3, where the arrays sit in the caches and a pass lasts as long as its
+// chain of dependent loads: one x-pair per thread, so that every load of the stencil is
+// issued at once, and the x neighbours by shuffles (a row is kPairs lanes, periodic as the
+// grid is).  FP64 at 64^3 from the density: 6.6 us (13.5 us for a march of two planes a
+// thread, whose 128 workgroups load plane by plane).  The same operations per cell as the
+// march.
+template <bool RHO, int N>
+__global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a) {
+  constexpr int kPairs = N / 2;
+  constexpr int q = N == 64 ? 6 : 5;
+  const int tid = threadIdx.x, bid = blockIdx.x;
+  const int row = (bid * kMarchThreads + tid) / kPairs;
+  const int j = row & (N - 1);
+  const int k = (bid * kMarchThreads / kPairs) >> q;   // uniform: a block stays within a plane
+  const int ip = 2 * (tid % kPairs);
+  const unsigned o = off_of<double>(ip, j, q), od = off_of<double>(ip, j - 1, q), ou = off_of<double>(ip, j + 1, q);
+  const bool first = a.s_zw == nullptr;
+  // the stencil's five pairs of d_old and z, the coefficients, r and p: all in flight together
+  auto z2 = [&](int kk, unsigned off) -> double2 {
+    if (a.zx64) return ld2(plane_rsrc(a.zx64, kk, q), off, 0.0);
+    const float2 zf = ld2(plane_rsrc(a.zx32, kk, q), off >> 1, 0.0f);
+    return double2{static_cast<double>(zf.x), static_cast<double>(zf.y)};
+  };
+  const double2 zc = z2(k, o), zd = z2(k, od), zu = z2(k, ou), zl = z2(k - 1, o), zh = z2(k + 1, o);
+  double2 dc{0.0, 0.0}, dd = dc, du = dc, dl = dc, dh = dc;
+  double beta = 0.0;
+  if (!first) {   // d_old is not read on the first step
+    const Rsrc dk = plane_rsrc(a.p, k, q);
+    dc = ld2(dk, o, 0.0);
+    dd = ld2(dk, od, 0.0);
+    du = ld2(dk, ou, 0.0);
+    dl = ld2(plane_rsrc(a.p, k - 1, q), o, 0.0);
+    dh = ld2(plane_rsrc(a.p, k + 1, q), o, 0.0);
+    beta = -*a.s_zw / *a.s_dw;
+  }
+  const double2 rv = ld2(plane_rsrc(a.r, k, q), o, 0.0);
+  const long long c = (static_cast<long long>(k) << (2 * q)) + o / sizeof(double);
+  double2 xv{0.0, 0.0};
+  double alpha = 0.0;
+  if (a.pp) {
+    xv = *reinterpret_cast<const double2*>(a.pp + c);
+    alpha = *a.s_alpha;
+  }
+  auto left = [&](double v) { return __shfl(v, (tid + kPairs - 1) % kPairs, kPairs); };
+  auto right = [&](double v) { return __shfl(v, (tid + 1) % kPairs, kPairs); };
+  PF<double> F;
+  if constexpr (RHO) {
+    const Rsrc rk = plane_rsrc(a.rt, k, q);
+    const double2 rc = ld2(rk, o, 0.0), rd = ld2(rk, od, 0.0), ru = ld2(rk, ou, 0.0);
+    const double2 rl = ld2(plane_rsrc(a.rt, k - 1, q), o, 0.0), rh = ld2(plane_rsrc(a.rt, k + 1, q), o, 0.0);
+    const bool lo = k > 0, hi = k + 1 < N;   // the walls are closed
+    F.x0 = face_beta(left(rc.y), rc.x);
+    F.x1 = face_beta(rc.x, rc.y);
+    F.x2 = face_beta(rc.y, right(rc.x));
+    F.ym0 = face_beta(rd.x, rc.x);
+    F.ym1 = face_beta(rd.y, rc.y);
+    F.yp0 = face_beta(rc.x, ru.x);
+    F.yp1 = face_beta(rc.y, ru.y);
+    F.zm0 = lo ? face_beta(rl.x, rc.x) : 0.0;
+    F.zm1 = lo ? face_beta(rl.y, rc.y) : 0.0;
+    F.zp0 = hi ? face_beta(rc.x, rh.x) : 0.0;
+    F.zp1 = hi ? face_beta(rc.y, rh.y) : 0.0;
+  } else {
+    const Rsrc yk = plane_rsrc(a.by, k, q);
+    const double2 fx = ld2(plane_rsrc(a.bx, k, q), o, 0.0);
+    const double2 fy = ld2(yk, o, 0.0), fyu = ld2(yk, ou, 0.0);
+    const double2 fz = ld2(plane_rsrc(a.bz, k, q), o, 0.0), fzh = ld2(plane_rsrc(a.bz, k + 1, q), o, 0.0);
+    F = PF<double>{fx.x, fx.y, right(fx.x), fy.x, fy.y, fyu.x, fyu.y, fz.x, fz.y, fzh.x, fzh.y};
+  }
+  auto dn2 = [&](double2 d, double2 z) -> double2 {
+    return first ? z : double2{__builtin_fma(beta, d.x, z.x), __builtin_fma(beta, d.y, z.y)};
+  };
+  const double2 pc = dn2(dc, zc);
+  double r0, r1;
+  pair_r(F, pc, left(pc.y), right(pc.x), dn2(dd, zd), dn2(du, zu), dn2(dl, zl), dn2(dh, zh), double2{0.0, 0.0}, 0.0,
+         a.inv_h2, r0, r1);
+  const double2 w{-r0, -r1};   // the residual of f = 0 is -A d
+  *reinterpret_cast<double2*>(a.w + c) = w;
+  *reinterpret_cast<double2*>(a.dn + c) = pc;
+  if (a.pp)
+    *reinterpret_cast<double2*>(a.pp + c) =
+        double2{__builtin_fma(alpha, dc.x, xv.x), __builtin_fma(alpha, dc.y, xv.y)};
+  const double s1 = block_sum(fmad(pc.y, w.y, pc.x * w.x));
+  __syncthreads();
+  const double s2 = block_sum(fmad(pc.y, rv.y, pc.x * rv.x));
+  if (tid == 0) {
+    a.partials[bid] = s1;
+    a.partials2[bid] = s2;
+  }
+}
+
 // 128 x 8 tiles, z-chunks as launch_mode takes them
 template <typename T, int MODE>
 hipError_t launch_lds(MarchArgs<T> a, int* nblocks, hipStream_t s) {
@@ -859,6 +950,16 @@ hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
   if constexpr (RHO)
     if (through_lds(a.rt, a.q)) return launch_lds<T, MODE>(a, nblocks, s);
   const int n = 1 << a.q;
+  if constexpr (MODE == kModeFcgX)
+    if (n == 32 || n == 64) {
+      const int blocks = n * n * n / (2 * kMarchThreads);
+      *nblocks = blocks;
+      if (n == 64)
+        hipLaunchKernelGGL((k_fcgx_pair<RHO, 64>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
+      else
+        hipLaunchKernelGGL((k_fcgx_pair<RHO, 32>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
+      return hipGetLastError();
+    }
   const int TX = n >= 128 ? 128 : n;
   const int TY = 2 * (kMarchThreads / (TX / 2));
   if (n < 32 || TY > n) return hipErrorInvalidValue;
@@ -874,6 +975,8 @@ hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
   if (TX == 128) {
     if constexpr (!RHO)
       hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 128>), grid, block, 0, s, a);
+  } else if constexpr (MODE == kModeFcgX) {
+    return hipErrorInvalidValue;
   } else if (TX == 64)
     hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 64>), grid, block, 0, s, a);
   else

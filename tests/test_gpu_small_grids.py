@@ -345,3 +345,30 @@ def test_two_sweep_pass_from_face_arrays(N, dtype):
             for _ in range(sweeps):
                 want = mg.smooth(0, want, f, 1, order)
             assert torch.equal(got, want), (order, sweeps)
+
+
+@pytest.mark.parametrize("N", [32, 64])
+@pytest.mark.parametrize("form", ["rho", "faces"])
+def test_direction_pass_one_pair_per_thread(N, form):
+    """The flexible-CG direction pass of 32^3 and 64^3, from both forms of the coefficients:
+    FP64 histories step by step against the oracle's (to 1e-5 of each entry: rounding of
+    1e-16 times the residual's fall to 1e-7 and its growth over the recurrences), a warm
+    start, and mixed preconditioning (FP32 z) to the same solution."""
+    from paper_1410_2240_amd import MG
+    inp = fields.make("c2", N)
+    faces = face_coeffs_from_rho(inp.rho, inp.mask)
+    H = omg.setup(*faces, inp.mask, inp.h)
+    f = dev(inp.f)
+    make = lambda **kw: (MG.from_rho(dev(inp.rho), dev(inp.mask), krylov=True, **kw) if form == "rho"
+                         else MG(*(dev(b) for b in faces), dev(inp.mask), krylov=True, **kw))
+    print(f"direction pass {N}^3 {form}", flush=True)
+    p, hist, _ = make().solve(f, tol=1e-11, max_cycles=60)
+    want_p, want = omg.solve_fcg(H, inp.f, tol=1e-11, max_iters=60)[:2]
+    for got, ref in zip(hist, want):
+        if ref > 1e-7:
+            assert abs(got - ref) <= 1e-5 * ref
+    assert maxrel(host(p), want_p) <= 1e-8
+    q, again, _ = make().solve(f, 0.5 * p, tol=1e-11, max_cycles=60)
+    assert abs(again[0] - 0.5) <= 1e-9 and maxrel(host(q), want_p) <= 1e-8
+    q, mixed, _ = make(mixed=True).solve(f, tol=1e-11, max_cycles=60)
+    assert maxrel(host(q), want_p) <= 1e-8 and abs(len(mixed) - len(hist)) <= 2
