@@ -559,9 +559,15 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
       return first_sweep<double>(c, kz, kr, nullptr, true);
     };
     // the new direction from z and the current one, with w = A d' and the two sums into
-    // partial sets 0 and 1; first: d' = z, no update of p
-    auto direction = [&](bool first) -> int {
-      const double* s_zw = first ? nullptr : c->scal + S_ZW;
+    // partial sets 0 and 1; first: d' = z, no update of p.  zw_parts > 0: that many partial
+    // sums of z.w in set 3.  Where the passes add the partials themselves, those of the two
+    // sums are left for the update of r.
+    const bool inside = mg::sums_inside(q);
+    mg::FcgSums sums;
+    sums.dr = c->scal + S_DR;
+    sums.dw = c->scal + S_DW;
+    auto direction = [&](bool first, int zw_parts) -> int {
+      const double* s_zw = first ? nullptr : zw_parts ? part(c, 3) : c->scal + S_ZW;
       const double* s_dw = first ? nullptr : c->scal + S_DW;
       double* dnew = dirs[next_dir(cur)];
       int nb = 0;
@@ -580,7 +586,7 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
         }
         MG_HIP(mg::launch_fcg_x_march(z64, z32, dirs[cur], dnew, p, s_zw, s_dw, c->scal + S_ALPHA, kr, a.bx, a.by,
                                       a.bz, a.rt, q, a.h, kw, part(c, 0), part(c, 1), &nb, c->stream,
-                                      use_df ? &df : nullptr));
+                                      use_df ? &df : nullptr, zw_parts));
       } else {
         MG_HIP(mg::launch_fcg_dir(z64, z32, dirs[cur], dnew, first ? nullptr : p, s_zw, s_dw, c->scal + S_ALPHA, q,
                                   c->stream));
@@ -588,13 +594,21 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
                                  c->stream));
       }
       cur = next_dir(cur);
+      if (inside) {
+        sums.dr = part(c, 1);
+        sums.dw = part(c, 0);
+        sums.nparts = nb;
+        sums.dr_out = c->scal + S_DR;
+        sums.dw_out = c->scal + S_DW;
+        return MG_OK;
+      }
       MG_HIP(mg::launch_reduce_final2(part(c, 0), part(c, 1), nb, c->scal + S_DW, c->scal + S_DR, c->stream));
       return MG_OK;
     };
     double* kz_zero = (mixed || zin) ? nullptr : kz;
     if (std::isfinite(r) && r > tol && max_cycles > 0) {
       MG_TRY(precondition(false));
-      MG_TRY(direction(true));
+      MG_TRY(direction(true, 0));
     }
     while (std::isfinite(r) && r > tol && *cycles < max_cycles) {
       int nb = 0;
@@ -611,8 +625,8 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
         MG_HIP(launch_two_sweeps<double>(c, 0, kz, a.t, kr, nullptr, MG_PRE, true, nullptr, &ru));
         std::swap(kr, kr_other);
       } else {
-        MG_HIP(mg::launch_fcg_rupdate(kr, kw, c->scal + S_DR, c->scal + S_DW, c->scal + S_ALPHA, q, kz_zero,
-                                      mixed ? r32 : nullptr, mixed ? e32_zero : nullptr, part(c, 2), &nb, c->stream));
+        MG_HIP(mg::launch_fcg_rupdate(kr, kw, sums, c->scal + S_ALPHA, q, kz_zero, mixed ? r32 : nullptr,
+                                      mixed ? e32_zero : nullptr, part(c, 2), &nb, c->stream));
       }
       MG_TRY(reduce_and_publish(c, 2, nb, S_RNORM2, 8));
       ++*cycles;
@@ -646,8 +660,8 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
         MG_TRY(precondition(ahead));
         MG_HIP(mg::launch_fcg_zw(z64, z32, kw, q, part(c, 3), &nb, c->stream));
       }
-      MG_TRY(reduce_set(c, 3, nb, S_ZW));
-      MG_TRY(direction(false));
+      if (!inside) MG_TRY(reduce_set(c, 3, nb, S_ZW));
+      MG_TRY(direction(false, inside ? nb : 0));
     }
   }
   // Mixed refinement on a density-form finest grid: the FP64 update p + e and the next

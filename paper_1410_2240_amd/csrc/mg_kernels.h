@@ -246,6 +246,23 @@ hipError_t launch_small_solve(const SmallSolve& a, hipStream_t s);
 // Same results as the grid-stride kernels below (per cell), each plane of p and of the
 // coefficients read once per column; rt != nullptr selects the density form.
 int march_supported(int q);
+// Flexible CG on 32^3 and 64^3: a sum's partials (512 at most) are added by each workgroup
+// of the pass that needs it, two loads a thread, instead of by a launch of their own: 3 us
+// and the gap before it, twice a step of about 80 us.  At 128^3 a workgroup would add 4096
+// and more, in each of 1024 workgroups.
+inline bool sums_inside(int q) { return q == 5 || q == 6; }
+// the sum of n partials (n <= kSumInside), in every thread of a workgroup of 256; the same
+// order in every workgroup
+constexpr int kSumInside = 512;
+__device__ __forceinline__ double sum_inside(const double* __restrict__ parts, int n, double* red) {
+  const int t = threadIdx.x;
+  double s = t < n ? parts[t] : 0.0;
+  if (t + 256 < n) s += parts[t + 256];
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  if ((t & 63) == 0) red[t >> 6] = s;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
 hipError_t launch_residual_norm_march(const double* p, const double* f, const double* bx, const double* by,
                                       const double* bz, const double* rt, int q, double h, const double* fshift,
                                       float* r32, double* r64, double* partials, int* nblocks, hipStream_t s);
@@ -277,11 +294,13 @@ struct FcgxDefer {
   const double* s_alpha_prev = nullptr;
 };
 int fcgx_defer_supported(const double* rt, int q);
+// With zw_parts > 0, s_zw holds that many partial sums, which every workgroup adds for
+// itself (grids of sums_inside only).
 hipError_t launch_fcg_x_march(const double* z64, const float* z32, const double* d, double* dn, double* p,
                               const double* s_zw, const double* s_dw, const double* s_alpha, const double* r,
                               const double* bx, const double* by, const double* bz, const double* rt, int q, double h,
                               double* w, double* part_dw, double* part_dr, int* nblocks, hipStream_t s,
-                              const FcgxDefer* df = nullptr);
+                              const FcgxDefer* df = nullptr, int zw_parts = 0);
 
 // ---- FP64 finest-grid passes ------------------------------------------------------
 // partials[blockIdx] = sum over active cells of r^2, r = (f - fshift) - A p; optional
@@ -298,9 +317,17 @@ hipError_t launch_residual_norm(const double* p, const double* f, const double* 
 hipError_t launch_fcg_aw(const double* d, const double* r, const double* bx, const double* by, const double* bz,
                          const double* rt, int q, double h, double* w, double* part_dw, double* part_dr, int* nblocks,
                          hipStream_t s);
-hipError_t launch_fcg_rupdate(double* r, const double* w, const double* s_dr, const double* s_dw, double* s_alpha,
-                              int q, double* z_zero, float* r32, float* e32_zero, double* part_rr, int* nblocks,
-                              hipStream_t s);
+// The two sums alpha = dr / dw is formed from: as scalars (nparts = 0), or as nparts partial
+// sums each (grids of sums_inside), whose totals the pass also leaves in dr_out and dw_out.
+struct FcgSums {
+  const double* dr = nullptr;
+  const double* dw = nullptr;
+  int nparts = 0;
+  double* dr_out = nullptr;
+  double* dw_out = nullptr;
+};
+hipError_t launch_fcg_rupdate(double* r, const double* w, const FcgSums& sums, double* s_alpha, int q, double* z_zero,
+                              float* r32, float* e32_zero, double* part_rr, int* nblocks, hipStream_t s);
 hipError_t launch_fcg_padd(double* p, const double* d, const double* s_alpha, int q, hipStream_t s);
 // p += *s_alpha0 d0, then p += *s_alpha d (two updates left pending, in their order)
 hipError_t launch_fcg_padd2(double* p, const double* d0, const double* s_alpha0, const double* d, const double* s_alpha,

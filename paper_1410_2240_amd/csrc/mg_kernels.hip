@@ -824,12 +824,21 @@ __global__ __launch_bounds__(kBlock) void k_fcg_aw(const double* __restrict__ d,
 // partial ||r||^2.  Leaves the next preconditioner input ready: FP64 z = 0, or FP32
 // r32 = r and e32 = 0.
 __global__ __launch_bounds__(kBlock) void k_fcg_rupdate(double* __restrict__ r, const double* __restrict__ w,
-                                                        const double* __restrict__ s_dr,
-                                                        const double* __restrict__ s_dw,
-                                                        double* __restrict__ s_alpha, int total,
+                                                        FcgSums sums, double* __restrict__ s_alpha, int total,
                                                         double* __restrict__ z_zero, float* __restrict__ r32,
                                                         float* __restrict__ e32_zero, double* __restrict__ part_rr) {
-  const double alpha = *s_dr / *s_dw;
+  double alpha;
+  if (sums.nparts > 0) {   // (uniform; the partials are not written here)
+    __shared__ double red[2][kBlock / 64];
+    const double dr = sum_inside(sums.dr, sums.nparts, red[0]), dw = sum_inside(sums.dw, sums.nparts, red[1]);
+    alpha = dr / dw;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *sums.dr_out = dr;
+      *sums.dw_out = dw;
+    }
+  } else {
+    alpha = *sums.dr / *sums.dw;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) *s_alpha = alpha;
   double rr = 0.0;
   for (int c = 2 * (blockIdx.x * kBlock + threadIdx.x); c < total; c += 2 * gridDim.x * kBlock) {
@@ -1145,12 +1154,13 @@ hipError_t launch_fcg_aw(const double* d, const double* r, const double* bx, con
   return hipGetLastError();
 }
 
-hipError_t launch_fcg_rupdate(double* r, const double* w, const double* s_dr, const double* s_dw, double* s_alpha,
-                              int q, double* z_zero, float* r32, float* e32_zero, double* part_rr, int* nblocks,
-                              hipStream_t s) {
+hipError_t launch_fcg_rupdate(double* r, const double* w, const FcgSums& sums, double* s_alpha, int q, double* z_zero,
+                              float* r32, float* e32_zero, double* part_rr, int* nblocks, hipStream_t s) {
+  if (sums.nparts < 0 || sums.nparts > kSumInside || (sums.nparts > 0 && (!sums.dr_out || !sums.dw_out)))
+    return hipErrorInvalidValue;
   const int nb = reduction_blocks(1LL << (3 * q - 1));
-  hipLaunchKernelGGL(k_fcg_rupdate, dim3(nb), dim3(kBlock), 0, s, r, w, s_dr, s_dw, s_alpha, 1 << (3 * q), z_zero, r32,
-                     e32_zero, part_rr);
+  hipLaunchKernelGGL(k_fcg_rupdate, dim3(nb), dim3(kBlock), 0, s, r, w, sums, s_alpha, 1 << (3 * q), z_zero, r32, e32_zero,
+                     part_rr);
   *nblocks = nb;
   return hipGetLastError();
 }

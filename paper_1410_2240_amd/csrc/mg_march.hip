@@ -76,6 +76,7 @@ struct MarchArgs {
   const double* zx64;
   const float* zx32;
   const double* s_zw;
+  int zw_parts;       // > 0: s_zw holds that many partial sums
   const double* s_dw;
   const double* s_alpha;
   double* dn;
@@ -865,7 +866,7 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a
     du = ld2(dk, ou, 0.0);
     dl = ld2(plane_rsrc(a.p, k - 1, q), o, 0.0);
     dh = ld2(plane_rsrc(a.p, k + 1, q), o, 0.0);
-    beta = -*a.s_zw / *a.s_dw;
+    if (a.zw_parts == 0) beta = -*a.s_zw / *a.s_dw;
   }
   const double2 rv = ld2(plane_rsrc(a.r, k, q), o, 0.0);
   const long long c = (static_cast<long long>(k) << (2 * q)) + o / sizeof(double);
@@ -900,6 +901,10 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a
     const double2 fy = ld2(yk, o, 0.0), fyu = ld2(yk, ou, 0.0);
     const double2 fz = ld2(plane_rsrc(a.bz, k, q), o, 0.0), fzh = ld2(plane_rsrc(a.bz, k + 1, q), o, 0.0);
     F = PF<double>{fx.x, fx.y, right(fx.x), fy.x, fy.y, fyu.x, fyu.y, fz.x, fz.y, fzh.x, fzh.y};
+  }
+  if (a.zw_parts > 0) {   // (uniform)
+    __shared__ double sums[kMarchThreads / 64];
+    beta = -sum_inside(a.s_zw, a.zw_parts, sums) / *a.s_dw;
   }
   auto dn2 = [&](double2 d, double2 z) -> double2 {
     return first ? z : double2{__builtin_fma(beta, d.x, z.x), __builtin_fma(beta, d.y, z.y)};
@@ -1061,8 +1066,10 @@ hipError_t launch_fcg_x_march(const double* z64, const float* z32, const double*
                               const double* s_zw, const double* s_dw, const double* s_alpha, const double* r,
                               const double* bx, const double* by, const double* bz, const double* rt, int q, double h,
                               double* w, double* part_dw, double* part_dr, int* nblocks, hipStream_t s,
-                              const FcgxDefer* df) {
+                              const FcgxDefer* df, int zw_parts) {
   if ((z64 == nullptr) == (z32 == nullptr) || !d || !dn || dn == d || (s_zw == nullptr) != (s_dw == nullptr))
+    return hipErrorInvalidValue;
+  if (zw_parts < 0 || zw_parts > kSumInside || (zw_parts > 0 && (!s_zw || !sums_inside(q))))
     return hipErrorInvalidValue;
   if (df && (!fcgx_defer_supported(rt, q) || !s_zw || (df->skip ? !df->s_alpha_save
                                                                 : (!df->d_prev || !df->s_alpha_prev ||
@@ -1083,6 +1090,7 @@ hipError_t launch_fcg_x_march(const double* z64, const float* z32, const double*
   a.zx64 = z64;
   a.zx32 = z32;
   a.s_zw = s_zw;
+  a.zw_parts = zw_parts;
   a.s_dw = s_dw;
   a.s_alpha = s_alpha;
   a.dn = dn;
