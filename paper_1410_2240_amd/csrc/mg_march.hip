@@ -833,14 +833,17 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_lds(MarchArgs<double> a)
   }
 }
 
-// FCGX on 32^3 and 64^3, where the arrays sit in the caches and a pass lasts as long as its
-// chain of dependent loads: one x-pair per thread, so that every load of the stencil is
-// issued at once, and the x neighbours by shuffles (a row is kPairs lanes, periodic as the
-// grid is).  FP64 at 64^3 from the density: 6.6 us (13.5 us for a march of two planes a
-// thread, whose 128 workgroups load plane by plane).  The same operations per cell as the
-// march.
-template <bool RHO, int N>
-__global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a) {
+// FCGX and NORM on 32^3 and 64^3, where the arrays sit in the caches and a pass lasts as
+// long as its chain of dependent loads: one x-pair per thread, so that every load of the
+// stencil is issued at once, and the x neighbours by shuffles (a row is kPairs lanes,
+// periodic as the grid is).  FCGX, FP64 at 64^3 from the density: 6.6 us (13.5 us for a
+// march of two planes a thread, whose 128 workgroups load plane by plane); NORM at
+// 32^3: 3.2 us (5.4 us as a march of 16 workgroups).  The same operations per cell as
+// the march.
+template <bool RHO, int N, int MODE>
+__global__ __launch_bounds__(kMarchThreads) void k_pair(MarchArgs<double> a) {
+  static_assert(MODE == kModeNorm || MODE == kModeFcgX, "");
+  constexpr bool FX = MODE == kModeFcgX;
   constexpr int kPairs = N / 2;
   constexpr int q = N == 64 ? 6 : 5;
   const int tid = threadIdx.x, bid = blockIdx.x;
@@ -849,32 +852,41 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a
   const int k = (bid * kMarchThreads / kPairs) >> q;   // uniform: a block stays within a plane
   const int ip = 2 * (tid % kPairs);
   const unsigned o = off_of<double>(ip, j, q), od = off_of<double>(ip, j - 1, q), ou = off_of<double>(ip, j + 1, q);
-  const bool first = a.s_zw == nullptr;
-  // the stencil's five pairs of d_old and z, the coefficients, r and p: all in flight together
-  auto z2 = [&](int kk, unsigned off) -> double2 {
-    if (a.zx64) return ld2(plane_rsrc(a.zx64, kk, q), off, 0.0);
-    const float2 zf = ld2(plane_rsrc(a.zx32, kk, q), off >> 1, 0.0f);
-    return double2{static_cast<double>(zf.x), static_cast<double>(zf.y)};
-  };
-  const double2 zc = z2(k, o), zd = z2(k, od), zu = z2(k, ou), zl = z2(k - 1, o), zh = z2(k + 1, o);
+  const long long c = (static_cast<long long>(k) << (2 * q)) + o / sizeof(double);
+  // the five pairs of p (FCGX: of d_old and z), the coefficients and the cell's own values:
+  // all in flight together
+  const bool first = FX && a.s_zw == nullptr;   // d_old is not read on the first step
   double2 dc{0.0, 0.0}, dd = dc, du = dc, dl = dc, dh = dc;
-  double beta = 0.0;
-  if (!first) {   // d_old is not read on the first step
+  if (!first) {
     const Rsrc dk = plane_rsrc(a.p, k, q);
     dc = ld2(dk, o, 0.0);
     dd = ld2(dk, od, 0.0);
     du = ld2(dk, ou, 0.0);
     dl = ld2(plane_rsrc(a.p, k - 1, q), o, 0.0);
     dh = ld2(plane_rsrc(a.p, k + 1, q), o, 0.0);
-    if (a.zw_parts == 0) beta = -*a.s_zw / *a.s_dw;
   }
-  const double2 rv = ld2(plane_rsrc(a.r, k, q), o, 0.0);
-  const long long c = (static_cast<long long>(k) << (2 * q)) + o / sizeof(double);
-  double2 xv{0.0, 0.0};
-  double alpha = 0.0;
-  if (a.pp) {
-    xv = *reinterpret_cast<const double2*>(a.pp + c);
-    alpha = *a.s_alpha;
+  double2 zc{0.0, 0.0}, zd = zc, zu = zc, zl = zc, zh = zc, xv = zc, rv;
+  double beta = 0.0, alpha = 0.0, fs = 0.0;
+  if constexpr (FX) {
+    auto z2 = [&](int kk, unsigned off) -> double2 {
+      if (a.zx64) return ld2(plane_rsrc(a.zx64, kk, q), off, 0.0);
+      const float2 zf = ld2(plane_rsrc(a.zx32, kk, q), off >> 1, 0.0f);
+      return double2{static_cast<double>(zf.x), static_cast<double>(zf.y)};
+    };
+    zc = z2(k, o);
+    zd = z2(k, od);
+    zu = z2(k, ou);
+    zl = z2(k - 1, o);
+    zh = z2(k + 1, o);
+    if (!first && a.zw_parts == 0) beta = -*a.s_zw / *a.s_dw;
+    rv = ld2(plane_rsrc(a.r, k, q), o, 0.0);
+    if (a.pp) {
+      xv = *reinterpret_cast<const double2*>(a.pp + c);
+      alpha = *a.s_alpha;
+    }
+  } else {
+    rv = ld2(plane_rsrc(a.f, k, q), o, 0.0);
+    fs = a.fshift ? *a.fshift : 0.0;
   }
   auto left = [&](double v) { return __shfl(v, (tid + kPairs - 1) % kPairs, kPairs); };
   auto right = [&](double v) { return __shfl(v, (tid + 1) % kPairs, kPairs); };
@@ -901,6 +913,15 @@ __global__ __launch_bounds__(kMarchThreads) void k_fcgx_pair(MarchArgs<double> a
     const double2 fy = ld2(yk, o, 0.0), fyu = ld2(yk, ou, 0.0);
     const double2 fz = ld2(plane_rsrc(a.bz, k, q), o, 0.0), fzh = ld2(plane_rsrc(a.bz, k + 1, q), o, 0.0);
     F = PF<double>{fx.x, fx.y, right(fx.x), fy.x, fy.y, fyu.x, fyu.y, fz.x, fz.y, fzh.x, fzh.y};
+  }
+  if constexpr (!FX) {
+    double r0, r1;
+    pair_r(F, dc, left(dc.y), right(dc.x), dd, du, dl, dh, rv, fs, a.inv_h2, r0, r1);
+    if (a.r32) *reinterpret_cast<float2*>(a.r32 + c) = float2{static_cast<float>(r0), static_cast<float>(r1)};
+    if (a.r64) *reinterpret_cast<double2*>(a.r64 + c) = double2{r0, r1};
+    const double s = block_sum(fmad(r1, r1, r0 * r0));
+    if (tid == 0) a.partials[bid] = s;
+    return;
   }
   if (a.zw_parts > 0) {   // (uniform)
     __shared__ double sums[kMarchThreads / 64];
@@ -955,14 +976,15 @@ hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
   if constexpr (RHO)
     if (through_lds(a.rt, a.q)) return launch_lds<T, MODE>(a, nblocks, s);
   const int n = 1 << a.q;
-  if constexpr (MODE == kModeFcgX)
+  constexpr bool kPair = MODE == kModeFcgX || MODE == kModeNorm;
+  if constexpr (kPair)
     if (n == 32 || n == 64) {
       const int blocks = n * n * n / (2 * kMarchThreads);
       *nblocks = blocks;
       if (n == 64)
-        hipLaunchKernelGGL((k_fcgx_pair<RHO, 64>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
+        hipLaunchKernelGGL((k_pair<RHO, 64, MODE>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
       else
-        hipLaunchKernelGGL((k_fcgx_pair<RHO, 32>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
+        hipLaunchKernelGGL((k_pair<RHO, 32, MODE>), dim3(blocks), dim3(kMarchThreads), 0, s, a);
       return hipGetLastError();
     }
   const int TX = n >= 128 ? 128 : n;
@@ -980,7 +1002,7 @@ hipError_t launch_mode(MarchArgs<T> a, int* nblocks, hipStream_t s) {
   if (TX == 128) {
     if constexpr (!RHO)
       hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 128>), grid, block, 0, s, a);
-  } else if constexpr (MODE == kModeFcgX) {
+  } else if constexpr (kPair) {
     return hipErrorInvalidValue;
   } else if (TX == 64)
     hipLaunchKernelGGL((k_residual_march<T, RHO, MODE, 64>), grid, block, 0, s, a);

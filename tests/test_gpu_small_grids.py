@@ -372,3 +372,30 @@ def test_direction_pass_one_pair_per_thread(N, form):
     assert abs(again[0] - 0.5) <= 1e-9 and maxrel(host(q), want_p) <= 1e-8
     q, mixed, _ = make(mixed=True).solve(f, tol=1e-11, max_cycles=60)
     assert maxrel(host(q), want_p) <= 1e-8 and abs(len(mixed) - len(hist)) <= 2
+
+
+@pytest.mark.parametrize("N", [32, 64])
+@pytest.mark.parametrize("form", ["rho", "faces"])
+def test_norm_pass_one_pair_per_thread(N, form):
+    """The residual norm of 32^3 and 64^3, from both forms of the coefficients: V-cycle
+    histories against the oracle's (to 1e-6 of each entry down to 1e-8, where rounding takes
+    over), a source with a mean, a warm start, and the FP32 copy that a mixed solve takes."""
+    from paper_1410_2240_amd import MG
+    inp = fields.make("c2", N)
+    faces = face_coeffs_from_rho(inp.rho, inp.mask)
+    H = omg.setup(*faces, inp.mask, inp.h)
+    src = inp.f + 0.25 * np.abs(inp.f).max()
+    f = dev(src)
+    make = lambda **kw: (MG.from_rho(dev(inp.rho), dev(inp.mask), **kw) if form == "rho"
+                         else MG(*(dev(b) for b in faces), dev(inp.mask), **kw))
+    print(f"norm pass {N}^3 {form}", flush=True)
+    p, hist, _ = make().solve(f, tol=1e-11, max_cycles=100)
+    want_p, want = omg.solve(H, src, tol=1e-11, max_cycles=100)
+    for got, ref in zip(hist, want):
+        if ref > 1e-8:
+            assert abs(got - ref) <= 1e-6 * ref
+    assert maxrel(host(p), want_p) <= 1e-8
+    _, again, _ = make().solve(f, 0.5 * p, tol=1e-11, max_cycles=100)
+    assert abs(again[0] - 0.5) <= 1e-9
+    q, mixed, _ = make(mixed=True).solve(f, tol=1e-11, max_cycles=100)
+    assert maxrel(host(q), want_p) <= 1e-8 and abs(len(mixed) - len(hist)) <= 2
