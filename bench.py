@@ -31,9 +31,13 @@ HBM_PEAK_GBS = 8000.0
 # FP64 and in the FP32 cycle alike: 4 x 4 + 3.125 + 2.125 = 21.25, plus 31.25 / 7 for
 # the coarser grids.
 VCYCLE_SCALARS_ONE = 21.25 + 31.25 / 7
-# On grids of 256^3 and up the finest grid sweeps two at a time, FP64 and FP32 alike (p,
-# f and the density read once, p written once per pair): 2 x 4 + 3.125 + 2.125 = 13.25
-VCYCLE_SCALARS_TWO = 13.25 + 31.25 / 7
+# On grids of 128^3 and up the finest grid sweeps two at a time, FP64 and FP32 alike (p,
+# f and the density read once, p written once per pair): 2 x 4 + 3.125 + 2.125 = 13.25.
+VCYCLE_SCALARS_128 = 13.25 + 31.25 / 7
+# From 256^3 its second pass also adds the coarse correction (ec read, 0.125, instead of a
+# pass of 2.125), and the grids below sweep two at a time from their face arrays:
+# 2 x 6 + 5.125 + 2.125 = 19.25
+VCYCLE_SCALARS_TWO = 11.25 + 19.25 / 7
 # the same count with three face arrays on the finest grid too (31.25 x 8 / 7)
 VCYCLE_SCALARS_FACE = 31.25 * 8 / 7
 
@@ -175,9 +179,9 @@ def main():
     vc64 = vcycle_ms(mg64, f, mask, torch.float64)
 
     # dominant kernel: the finest-grid smoother, timed on the stream it runs on.  On grids
-    # of 256^3 and up it sweeps two at a time: four sweeps are two launches p -> t -> p, as
+    # of 128^3 and up it sweeps two at a time: four sweeps are two launches p -> t -> p, as
     # in a cycle; below, two sweeps are two one-pass launches.
-    two64 = N >= 256
+    two64 = N >= 128
     fz = torch.zeros_like(f)
     ps = torch.zeros_like(f)
     sweeps = 4 if two64 else 2
@@ -259,7 +263,7 @@ def main():
         legs["differentiation"] = differentiation_leg(args)
         legs["rk2_projection"] = rk2_leg(256, args)
     traffic = recorded_traffic(inp.name, N)
-    scalars = VCYCLE_SCALARS_TWO if N >= 256 else VCYCLE_SCALARS_ONE
+    scalars = VCYCLE_SCALARS_TWO if N >= 256 else VCYCLE_SCALARS_128 if N >= 128 else VCYCLE_SCALARS_ONE
     out = {
         "metric": METRIC,
         "value_definition": f"grid points x V-cycles / time of the FP64 projection (setup from rho + solve to "
@@ -612,7 +616,7 @@ def coarsening_sweep(args):
     return out
 
 
-TRAFFIC_KERNEL = "k_rbgs_fused2<double, false, false>"
+TRAFFIC_KERNEL = "k_rbgs_fused2<double, false, false, false, true>"
 
 
 def kernel_source_hash():

@@ -27,7 +27,9 @@
  *
  * Ownership.  The caller owns every array and the workspace (device memory of
  * mg_workspace_size() bytes, 256-byte aligned).  The library never allocates device
- * memory.  mg_setup copies the finest coefficients into the workspace, so the caller
+ * memory; the scalars a call waits for come back through pinned host memory (1 KiB a
+ * context and lane, of one 64 KiB block per process, or an allocation of their own once
+ * that is given out).  mg_setup copies the finest coefficients into the workspace, so the caller
  * may free or reuse its beta arrays afterwards; the workspace must outlive the
  * context.  A context is not thread-safe; distinct contexts are independent.
  *
@@ -130,7 +132,8 @@ int mg_coeffs_from_rho(const double* rho, const uint8_t* mask, const int dims[3]
  * the workspace, zero faces touching the body and the bottom wall, mark fluid cells
  * with no open face inactive, coarsen the face products level by level (coarse face
  * = mean of its 4 fine faces, coarse cell active if any child is and it keeps an open
- * face), and form the FP64 pseudo-inverse of the 4^3 operator on the host.
+ * face), and form the FP64 pseudo-inverse of the 4^3 operator (on the device; on the
+ * host where its elimination meets a pivot too small).
  * beta must be >= 0 and finite; h > 0.  On success *out is a new context.
  */
 int mg_setup(mg_ctx** out, void* workspace, size_t ws_bytes,
@@ -185,7 +188,7 @@ int mg_solve(mg_ctx* ctx, const double* f, double* p, int batch, double tol, int
  * context).  workspace: DEVICE memory of at least lanes x mg_lane_workspace_size bytes,
  * 256-byte aligned, owned by the caller and outliving ctx; lane w uses the w-th slice.
  * Each lane gets a non-blocking HIP stream of default priority (created on the current
- * device, destroyed by mg_destroy), a pinned read-back buffer and two events; no device
+ * device, destroyed by mg_destroy), pinned read-back memory and an event; no device
  * memory is allocated.  From then on mg_solve with batch > 1 solves up to 1 + lanes
  * items at a time: item b on lane b mod (1 + lanes), lane 0 being ctx on its own stream,
  * each extra lane driven by a host thread of its own.  The lane streams start after the

@@ -13,6 +13,7 @@
 //   UPDATE    NORM of p + e (e in FP32, added on active cells), which is also written out
 //   RESTRICT  fc = mean of r over the 8 children of each coarse cell (the pair's two
 //             cells on two rows and two planes), ec = 0
+//             (NORM and FCGX on 32^3 and 64^3: k_pair, one x-pair a thread and no march)
 //   FCGX      the flexible-CG direction and product in one pass: d = z + beta d_old
 //             (z in FP64 or FP32; d = z on the first step), w = A d, partial sums of
 //             d.w and d.r, and the previous step's p += alpha d_old, deferred to this
