@@ -822,7 +822,10 @@ __global__ __launch_bounds__(kTailThreads) void k_coarse_setup(CoarseSetup a) {
   }
 #pragma unroll
   for (int c = 0; c < 8; ++c) a.pinv[lane * 64 + wave * 8 + c] = zz[c] - m[c];
-  __syncthreads();   // every wave's stores are out before the ticket
+  // The host takes the ticket for the end of the setup, and may go on from another stream:
+  // each wave waits here until its stores can be seen (the barrier alone orders LDS only).
+  __threadfence_system();
+  __syncthreads();
   if (tid == 0) {
 #pragma unroll
     for (int x = 0; x < 3; ++x) {
