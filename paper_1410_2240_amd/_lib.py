@@ -56,6 +56,7 @@ SIGNATURES = {
     "mg_merge_rhs": (_I, [_P, _P, _P, _DIMS, _P]),
     "mg_merge_fill": (_I, [_P, _P, _DIMS, _P]),
     "mg_destroy": (None, [_P]),
+    "mg_release": (None, [_P]),
     "mg_last_error": (ctypes.c_char_p, []),
     "mg_level_info": (_I, [_P, _I, ctypes.POINTER(_I), ctypes.POINTER(_D)]),
     "mg_level_coeffs": (_I, [_P, _I, _P, _P, _P, _P]),

@@ -107,7 +107,7 @@ struct mg_ctx {
   std::vector<mg_ctx*> lanes;
   bool own_stream = false;              // a lane: `stream` was created by the library
   hipEvent_t order_event = nullptr;     // joins this context's stream with the caller's
-  int device = 0;                       // a lane: the device its stream belongs to
+  int device = 0;                       // the device its stream (and the workspace) belongs to
   int sharing = 1;   // right-hand sides being solved at once, this context's own among them
 
   View<double> v64(int l) const {
@@ -800,10 +800,28 @@ extern "C" void mg_destroy(mg_ctx* ctx);
 
 namespace {
 
+int device_of(hipStream_t s) {
+  int device = 0;
+  hipDevice_t d = 0;
+  if (s && hipStreamGetDevice(s, &d) == hipSuccess) return static_cast<int>(d);
+  (void)hipGetDevice(&device);
+  return device;
+}
+
+// Everything queued on the context's device, whichever streams its calls ran on (the
+// caller may have destroyed those since).
+void wait_device(const mg_ctx* c) {
+  int current = 0;
+  if (hipGetDevice(&current) != hipSuccess) return;
+  if (current != c->device) (void)hipSetDevice(c->device);
+  (void)hipDeviceSynchronize();
+  if (current != c->device) (void)hipSetDevice(current);
+}
+
 // The pinned memory scalars come back in; coherent, since the host polls it while kernels
-// run.  Allocating and freeing it for every context cost a setup and a destroy about 60 us
-// (the free waits for the device), so contexts take slots of one block, made for the first
-// of them; with every slot taken a context gets an allocation of its own, as before.
+// run.  Allocating and freeing it for every context cost a setup and a destroy about 60 us,
+// so contexts take slots of one block, made for the first of them; with every slot taken a
+// context gets an allocation of its own.
 constexpr size_t kSlotBytes = sizeof(double) * (S_COUNT + kHostHistory) + sizeof(unsigned long long);
 constexpr int kSlots = 64;
 static_assert(kSlotBytes % 64 == 0, "slots on cache lines of their own");
@@ -840,7 +858,7 @@ int alloc_host(mg_ctx* c) {
 void free_host(mg_ctx* c) {
   if (!c->host) return;
   // after an error scalars may still be on their way
-  if (__atomic_load_n(ticket_of(c), __ATOMIC_ACQUIRE) < c->published) (void)hipStreamSynchronize(c->stream);
+  if (__atomic_load_n(ticket_of(c), __ATOMIC_ACQUIRE) < c->published) wait_device(c);
   unsigned char* p = reinterpret_cast<unsigned char*>(c->host);
   c->host = nullptr;
   {
@@ -879,6 +897,7 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
   c->flags = flags;
   c->L = plan.levels;
   c->stream = static_cast<hipStream_t>(hip_stream);
+  c->device = device_of(c->stream);
   c->ws = static_cast<unsigned char*>(workspace);
   for (int l = 0; l < c->L; ++l) {
     const mg::LevelPlan& lp = plan.lv[l];
@@ -1459,7 +1478,13 @@ int mg_project(mg_ctx* ctx, double* ux, double* uy, double* uz, const double* rx
 
 void mg_destroy(mg_ctx* ctx) {
   if (!ctx) return;
-  for (mg_ctx* lane : ctx->lanes) mg_destroy(lane);
+  wait_device(ctx);
+  mg_release(ctx);
+}
+
+void mg_release(mg_ctx* ctx) {
+  if (!ctx) return;
+  for (mg_ctx* lane : ctx->lanes) mg_release(lane);
   free_host(ctx);   // (before its stream goes)
   if (ctx->own_stream && ctx->stream) {
     (void)hipStreamSynchronize(ctx->stream);
@@ -1507,7 +1532,7 @@ int mg_add_lanes(mg_ctx* ctx, void* workspace, size_t ws_bytes, int lanes) {
                              device, &lane);
     made.push_back(lane);
     if (rc != MG_OK) {
-      for (mg_ctx* m : made) mg_destroy(m);
+      for (mg_ctx* m : made) mg_release(m);
       return rc;
     }
   }

@@ -92,18 +92,22 @@ class MG:
         size = lib.mg_workspace_size(_lib.dims3(n), flags)
         if size == 0:
             raise ValueError(f"unsupported grid {n}^3")
+        stream = _stream(ref.device)
+        self._home = stream.value   # the stream whose order the workspace is handed back in
         self.workspace = torch.empty(size, dtype=torch.uint8, device=ref.device)
         ctx = ctypes.c_void_p()
         if _rho is None:
             rc = lib.mg_setup(ctypes.byref(ctx), _ptr(self.workspace), size, _ptr(bx, torch.float64),
                               _ptr(by, torch.float64), _ptr(bz, torch.float64), _ptr(mask, torch.uint8),
-                              _lib.dims3(n), self.h, flags, _stream(ref.device))
+                              _lib.dims3(n), self.h, flags, stream)
         else:
             rc = lib.mg_setup_from_rho(ctypes.byref(ctx), _ptr(self.workspace), size, _ptr(_rho, torch.float64),
-                                       _ptr(mask, torch.uint8), _lib.dims3(n), self.h, flags, _stream(ref.device))
+                                       _ptr(mask, torch.uint8), _lib.dims3(n), self.h, flags, stream)
         _check(rc, "mg_setup")
         self._ctx = ctx
-        self._destroy = lib.mg_destroy   # kept so that teardown at interpreter exit still finds it
+        # the allocator takes the workspace back in stream order (_sync_stream), so teardown need
+        # not wait; kept so that teardown at interpreter exit still finds it
+        self._destroy = lib.mg_release
         self.levels = lib.mg_level_info(ctx, 0, None, None)
         self.lanes = int(lanes)
         self.lane_workspace = None
@@ -130,7 +134,13 @@ class MG:
             self._ctx = None
 
     def _sync_stream(self):
-        _lib.load().mg_set_stream(self._ctx, _stream(self.device))
+        stream = _stream(self.device)
+        if stream.value != self._home:   # the workspace is not reused before this call's work is done
+            current = torch.cuda.current_stream(self.device)
+            self.workspace.record_stream(current)
+            if self.lane_workspace is not None:
+                self.lane_workspace.record_stream(current)
+        _lib.load().mg_set_stream(self._ctx, stream)
 
     # ---------------------------------------------------------------- solve
 

@@ -35,3 +35,71 @@ def test_a_setup_is_done_when_it_returns(N, mixed):
         got = used(mg)
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def pending(stream):
+    """Work of some 20 ms on the stream, and an event after it."""
+    torch.cuda._sleep(40_000_000)
+    return stream.record_event()
+
+
+@pytest.mark.parametrize("lanes", [0, 2])
+@pytest.mark.parametrize("N", [16, 128])
+def test_workspace_is_kept_for_another_stream(N, lanes):
+    """Built on one stream, solved and applied on another, dropped while that one has work
+    to do, and memory of the workspace's size allocated and filled on the first at once: the
+    results are those of a context used on one stream."""
+    from paper_1410_2240_amd import MG
+    inp = fields.make("c2", N)
+    rho, mask, f = dev(inp.rho), dev(inp.mask), dev(fields.batch_rhs(inp.mask, 3))
+    one = MG.from_rho(rho, mask, lanes=lanes)
+    want = one.solve(f, tol=1e-9)[0]
+    want_ap = one.apply(want)
+    del one
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    print(f"dropped while in use on another stream {N}^3 lanes={lanes}", flush=True)
+    mg = MG.from_rho(rho, mask, lanes=lanes)
+    with torch.cuda.stream(side):
+        p = mg.solve(f, tol=1e-9)[0]
+        busy = pending(side)
+        ap = mg.apply(p)
+    sizes = [t.numel() for t in (mg.workspace, mg.lane_workspace) if t is not None]
+    del mg
+    filled = [torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda") for n in sizes]
+    assert not busy.query()   # all that happened before the other stream went on
+    torch.cuda.synchronize()
+    assert torch.equal(p, want) and torch.equal(ap, want_ap)
+    assert all(int(t.min()) == 0xFF for t in filled)
+
+
+@pytest.mark.parametrize("changed", [False, True])
+def test_destroy_waits(changed):
+    """mg_destroy returns when the context's work is done, on the stream it was set up on or
+    a later one; mg_release does not wait."""
+    import ctypes
+    from paper_1410_2240_amd import _lib
+    lib = _lib.load()
+    N = 16
+    inp = fields.make("c2", N)
+    rho, mask, p = dev(inp.rho), dev(inp.mask), dev(inp.f)
+    ap = torch.empty_like(p)
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    home, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    size = lib.mg_workspace_size(_lib.dims3(N), 0)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    for end, done in ((lib.mg_release, False), (lib.mg_destroy, True)):
+        print(f"{end.__name__}, stream changed: {changed}", flush=True)
+        ctx = ctypes.c_void_p()
+        assert lib.mg_setup_from_rho(ctypes.byref(ctx), ptr(ws), size, ptr(rho), ptr(mask), _lib.dims3(N), 1.0 / N, 0,
+                                     ctypes.c_void_p(home.cuda_stream)) == 0, _lib.last_error()
+        use = side if changed else home
+        assert lib.mg_set_stream(ctx, ctypes.c_void_p(use.cuda_stream)) == 0
+        with torch.cuda.stream(use):
+            pending(use)
+            assert lib.mg_apply(ctx, ptr(p), ptr(ap), 1) == 0
+            event = use.record_event()
+        end(ctx)
+        assert event.query() == done
+        torch.cuda.synchronize()
