@@ -106,7 +106,7 @@ typedef struct {
   long long active_cells;  /* fluid cells with at least one open face on the finest grid */
   long long dropped_cells; /* fluid cells with no open face: no equation, treated as body */
   double removed_mean;  /* fluid mean removed from f (last batch item) */
-  double final_relres;  /* ||P f - A p|| / ||P f|| at exit (largest over the batch) */
+  double final_relres;  /* ||P f - A p|| / ||P f|| at exit (largest over the batch; NaN if any is) */
   double seconds;       /* host wall time of the call */
   size_t ws_bytes;      /* workspace bytes in use */
 } mg_stats;

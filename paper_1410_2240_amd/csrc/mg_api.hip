@@ -525,6 +525,8 @@ int solve_one(mg_ctx* c, const double* f, double* p, double tol, int max_cycles,
   if (hist) hist[nh] = r;
   ++nh;
   int status = MG_OK;
+  if (!std::isfinite(r))   // a guess that is not finite
+    status = fail(MG_EBREAKDOWN, "residual %g after %d cycles (initial %g)", r, *cycles, r0);
   if (c->flags & MG_KRYLOV) {
     // flexible CG: r, z, two directions and w in the workspace; z = V(r) in FP64, or V32
     // on float(r).  One step: r -= alpha w (alpha = d.r / d.w); the convergence check;
@@ -1085,6 +1087,9 @@ int make_lane(mg_ctx* ctx, unsigned char* ws, const mg::Plan& lp, int device, mg
   return MG_OK;
 }
 
+// the largest relative residual of a batch: a NaN is larger than any number
+double worse(double a, double b) { return std::isnan(a) || b <= a ? a : b; }
+
 struct LaneResult {
   int rc = MG_OK, nh = 0, cyc = 0;
   double rm = 0.0, fr = 0.0;
@@ -1350,7 +1355,7 @@ int mg_solve(mg_ctx* ctx, const double* f, double* p, int batch, double tol, int
     if (n_hist) n_hist[b] = o.nh;
     total_cycles += o.cyc;
     removed = o.rm;
-    worst = std::fmax(worst, o.fr);
+    worst = worse(worst, o.fr);
     if (o.rc == MG_EINVAL || o.rc == MG_EHIP) {
       g_error = o.err;
       return o.rc;
@@ -1415,7 +1420,7 @@ int mg_solve_static(mg_ctx* ctx, const double* f, double* p, int batch, double t
       if (rc == MG_EINVAL || rc == MG_EHIP) return rc;   // g_error holds the message
       total_cycles += cyc;
       removed = rm;
-      worst = std::fmax(worst, fr);
+      worst = worse(worst, fr);
       if (rc != MG_OK && status == MG_OK) {
         status = rc;
         std::snprintf(first_msg, sizeof first_msg, "%s", g_error.c_str());

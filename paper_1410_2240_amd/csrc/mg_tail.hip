@@ -592,6 +592,7 @@ __global__ __launch_bounds__(kTailThreads) void k_small_solve(SmallSolve a) {
   } else {
     r = r0 = sqrt(residual2()) / nf;
     record(r);
+    if (!__builtin_isfinite(r)) how = kSmallBreakdown;   // (a guess that is not finite)
     while (__builtin_isfinite(r) && r > a.tol && cycles < a.max_cycles) {
       t.cycle();
       ++cycles;
