@@ -203,13 +203,15 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
   };
   auto coarse_store = [&](auto s_tag, T v) {
     if constexpr (PRO) {
-      if (tid < kCCells) C[decltype(s_tag)::value][tid] = v;
+      if (tid < kCCells) C[decltype(s_tag)::value][tid] = v * (T(1) / 64);
     }
   };
-  // 64 times the correction of the staged pair at LDS offset e (box row r, pair x) of a fine
-  // plane whose distance from ks is U mod 6: its parents' plane and the nearer neighbour's,
-  // with weights 3 and 1 in each direction (scaling by powers of two is exact: the bits are
-  // those of 3/4 and 1/4)
+  // The correction of the staged pair at LDS offset e (box row r, pair x) of a fine plane
+  // whose distance from ks is U mod 6: its parents' plane and the nearer neighbour's, with
+  // weights 3 and 1 in each direction of values stored as 1/64 of theirs.  The bits are those
+  // of weights 3/4 and 1/4, whatever the size (scaled afterwards instead, 64 times the
+  // correction had to be in range), but for corrections within 2^7 of the smallest normal
+  // number, where 1/64 of them rounds.
   auto correction = [&](int e, auto u_tag) {
     constexpr int U = decltype(u_tag)::value;
     constexpr int K1 = (U / 2) % 3, K2 = (U & 1) ? (K1 + 1) % 3 : (K1 + 2) % 3;
@@ -245,8 +247,8 @@ __global__ __launch_bounds__(Shape<T>::TX / 2 * Shape<T>::TY) void k_rbgs_fused2
         if (sl[u] >= 0) {
           if constexpr (PRO) {
             const V2 add = correction(sl[u], s_tag);
-            if (rn[u].x < inf) pn[u].x = fma_t(T(1) / 64, add.x, pn[u].x);
-            if (rn[u].y < inf) pn[u].y = fma_t(T(1) / 64, add.y, pn[u].y);
+            if (rn[u].x < inf) pn[u].x += add.x;
+            if (rn[u].y < inf) pn[u].y += add.y;
           }
           Pf[S + sl[u]] = pn[u].x;
           Pf[S + sl[u] + kWP] = pn[u].y;
