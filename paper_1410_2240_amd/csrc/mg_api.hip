@@ -141,10 +141,10 @@ long long cells(const Level& a) { return static_cast<long long>(a.n) * a.n * a.n
 // `sweeps` red-black sweeps of A p = f on level l.  Grids of 128^3 and up use the one-pass
 // and two-pass fused sweeps, 32^3 and 64^3 grids the block-per-workgroup sweep; these
 // alternate p with the level's second buffer, and an odd count of passes ends with a copy
-// back.  Smaller grids use two in-place half-sweeps per sweep.  zero_in: p is known to
-// be zero, so the first out-of-place sweep does not read it (p's memory may then hold
-// anything; half-sweep grids still need it zeroed).  first_done: the first sweep
-// (p -> second buffer) has already been queued (see first_sweep), so start from its output.
+// back.  Smaller grids use two in-place half-sweeps per sweep.  zero_in (one-pass sweeps
+// only): p is known to be zero, so the first sweep does not read it and p's memory may hold
+// anything.  first_done (one-pass sweeps only): the first sweep (p -> second buffer) has
+// already been queued (see first_sweep), so start from its output.
 bool out_of_place_sweeps(int q) { return mg::fused_sweep_supported(q) || mg::box_sweep_supported(q); }
 
 // The density form a block sweep of level l reads, or null: it reads the face arrays.
@@ -194,11 +194,10 @@ int smooth(mg_ctx* c, int l, T* p, const T* f, const double* fshift, int sweeps,
   if (out_of_place_sweeps(a.q)) {
     T* src = first_done ? v.t : p;
     T* dst = first_done ? p : v.t;
-    const bool two = two_sweep_grid<T>(c, l);
-    int s = first_done ? (two ? 2 : 1) : 0;   // first_sweep queued one pass
-    if (two) {   // pairs of sweeps in one pass each
+    int s = first_done ? 1 : 0;
+    if (two_sweep_grid<T>(c, l)) {   // pairs of sweeps in one pass each
       for (; s + 2 <= sweeps; s += 2) {
-        MG_HIP(launch_two_sweeps<T>(c, l, src, dst, f, fshift, order, zero_in && s == 0));
+        MG_HIP(launch_two_sweeps<T>(c, l, src, dst, f, fshift, order, false));
         T* tmp = src;
         src = dst;
         dst = tmp;
@@ -206,8 +205,8 @@ int smooth(mg_ctx* c, int l, T* p, const T* f, const double* fshift, int sweeps,
     }
     for (; s < sweeps; ++s) {
       if (box)
-        MG_HIP(mg::launch_rbgs_box<T>(src, dst, f, v.bx, v.by, v.bz, box_rt<T>(c, l), a.q, a.h, order, fshift,
-                                      zero_in && s == 0, c->stream));
+        MG_HIP(mg::launch_rbgs_box<T>(src, dst, f, v.bx, v.by, v.bz, box_rt<T>(c, l), a.q, a.h, order, fshift, 0,
+                                      c->stream));
       else
         MG_HIP(mg::launch_rbgs_fused<T>(src, dst, f, v.bx, v.by, v.bz, v.rt, a.q, a.h, order, fshift,
                                         zero_in && s == 0, c->stream));
@@ -265,6 +264,8 @@ template <typename T>
 mg::CoarseCycle<T> coarse_cycle_args(const mg_ctx* c, int l, T* p, const T* f, const double* fshift) {
   mg::CoarseCycle<T> a{};
   a.nlev = c->L - l;
+  a.f = f;
+  a.e = p;
   for (int k = 0; k < a.nlev; ++k) {
     const Level& lv = c->lv[l + k];
     const View<T> v = c->view<T>(l + k);
@@ -273,8 +274,6 @@ mg::CoarseCycle<T> coarse_cycle_args(const mg_ctx* c, int l, T* p, const T* f, c
     a.by[k] = v.by;
     a.bz[k] = v.bz;
     a.mask[k] = lv.mask;
-    a.f[k] = k == 0 ? const_cast<T*>(f) : v.f;
-    a.e[k] = k == 0 ? p : v.e;
     a.h2[k] = static_cast<T>(lv.h * lv.h);
     a.inv_h2[k] = static_cast<T>(1.0 / (lv.h * lv.h));
   }
@@ -960,7 +959,7 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
     f0.rt = at<double>(c->ws, plan.lv[0].rt);
     f0.rt32 = at<float>(c->ws, plan.lv[0].rt32);
     if (f0.rt32 && !out_of_place_sweeps(f0.q))
-      return cleanup(fail(MG_EINVAL, "internal: FP32 density copy below 64^3"));
+      return cleanup(fail(MG_EINVAL, "internal: FP32 density copy of a grid swept in place"));
     if (density) {
       // open-face areas into the workspace, then validation and activity without
       // rewriting them, then the density form

@@ -203,8 +203,8 @@ template <typename T>
 hipError_t launch_coarse_solve(const T* f, T* e, const double* pinv, const uint8_t* mask, hipStream_t s);
 
 // Levels of the single-workgroup sub-cycle: entry 0 is the first grid it handles
-// (at most 16^3), the last entry the 4^3 grid.  e[0] must be zero on entry (or hold
-// the guess), f[0] the right-hand side; fshift applies to level 0 only.
+// (at most 16^3), the last entry the 4^3 grid.  e and f are that first grid's: e must be
+// zero on entry (or hold the guess), f the right-hand side, and fshift applies to it.
 constexpr int kCoarseCycleMaxN = 16;
 template <typename T>
 struct CoarseCycle {
@@ -214,8 +214,8 @@ struct CoarseCycle {
   const T* by[4];
   const T* bz[4];
   const uint8_t* mask[4];
-  T* f[4];
-  T* e[4];
+  const T* f;
+  T* e;
   T h2[4];
   T inv_h2[4];
   const double* pinv;
@@ -224,7 +224,7 @@ struct CoarseCycle {
 template <typename T>
 hipError_t launch_coarse_cycle(const CoarseCycle<T>& a, hipStream_t s);
 
-// A whole FP64 V-cycle solve on a 16^3 or 8^3 finest grid in one launch (cyc.e[0]: the guess
+// A whole FP64 V-cycle solve on a 16^3 or 8^3 finest grid in one launch (cyc.e: the guess
 // in, the solution out; cyc.fshift unused): the mean removed from f, the cycles until the
 // relative residual is at most tol (or max_cycles, or a breakdown), and the gauge.  pub.host
 // receives the removed mean, the last and the first relative residual, the number of

@@ -117,7 +117,7 @@ struct Tail {
 #pragma unroll
         for (int dy = 0; dy < 2; ++dy) {
           const int c = at(2 * I, 2 * J + dy, 2 * K + dz);
-          const V2 xv = pair_at(bx, c), fv = pair_at(a.f[0], c);
+          const V2 xv = pair_at(bx, c), fv = pair_at(a.f, c);
           fx[0][dy][dz] = xv.x;
           fx[1][dy][dz] = xv.y;
           fx[2][dy][dz] = bx[at((2 * I + 2) & 15, 2 * J + dy, 2 * K + dz)];
@@ -183,7 +183,7 @@ struct Tail {
 #pragma unroll
           for (int x = 0; x < 8; ++x) s.pair[x][col][tid] = v[x];
         } else {
-          q.f = a.f[0][c] - fs;
+          q.f = a.f[c] - fs;
           p1[col] = q;
         }
       }
@@ -233,12 +233,12 @@ struct Tail {
       for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
         for (int dy = 0; dy < 2; ++dy) {
-          const V2 v = pair_at(a.e[0], ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I);
+          const V2 v = pair_at(a.e, ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I);
           e[dz][dy][0] = v.x;
           e[dz][dy][1] = v.y;
         }
     } else {
-      s.e1[tid] = a.e[0][tid];
+      s.e1[tid] = a.e[tid];
     }
   }
 
@@ -249,10 +249,10 @@ struct Tail {
       for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
         for (int dy = 0; dy < 2; ++dy)
-          *reinterpret_cast<V2*>(a.e[0] + ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I) =
+          *reinterpret_cast<V2*>(a.e + ((2 * K + dz) << 8) + ((2 * J + dy) << 4) + 2 * I) =
               V2{e[dz][dy][0], e[dz][dy][1]};
     } else {
-      a.e[0][tid] = s.e1[tid];
+      a.e[tid] = s.e1[tid];
     }
   }
 
