@@ -24,21 +24,32 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# Algorithmic scalars moved per finest cell by one V(2,2) cycle.  A grid with the face
-# arrays: 4 sweeps x 6 (p, f, bx, by, bz read, p written) + residual-and-restrict 5.125
-# + prolongation 2.125 = 31.25, and each coarser grid 1/8 of the one above.  The finest
-# grid of a hierarchy built from rho reads one density instead of three face arrays, in
-# FP64 and in the FP32 cycle alike: 4 x 4 + 3.125 + 2.125 = 21.25, plus 31.25 / 7 for
-# the coarser grids.
-VCYCLE_SCALARS_ONE = 21.25 + 31.25 / 7
-# On grids of 128^3 and up the finest grid sweeps two at a time, FP64 and FP32 alike (p,
-# f and the density read once, p written once per pair): 2 x 4 + 3.125 + 2.125 = 13.25.
-VCYCLE_SCALARS_128 = 13.25 + 31.25 / 7
-# From 256^3 its second pass also adds the coarse correction (ec read, 0.125, instead of a
-# pass of 2.125), and the grids below sweep two at a time from their face arrays:
-# 2 x 6 + 5.125 + 2.125 = 19.25
-VCYCLE_SCALARS_TWO = 11.25 + 19.25 / 7
-# the same count with three face arrays on the finest grid too (31.25 x 8 / 7)
+def vcycle_scalars(n, fp64):
+    """Algorithmic scalars moved per finest cell by one V(2,2) cycle of a hierarchy built from
+    rho: each array of a launch once, halos not counted.  A launch that sweeps moves p, f and
+    the coefficients in (three face arrays, or one density on the finest grid) and p out; the
+    residual and restriction p, f, the coefficients and 1/8; a prolongation of its own 2 1/8."""
+    total, part, finest = 0.0, 1.0, True
+    while n > 16:
+        faces = not finest or (n == 128 and fp64) or n == 32   # what the sweeps read
+        sweep = 6 if faces else 4
+        residual = 3.125 if finest else 5.125
+        if n <= 64:      # four block sweeps, the restriction and prolongation inside
+            count = 4 * sweep + 0.25
+        elif n == 128 and not fp64 and not finest:   # one-pass sweeps
+            count = 4 * sweep + residual + 2.125
+        else:            # two sweeps to a pass; the finest from 256^3 adds the correction itself
+            count = 2 * sweep + residual + (0.125 if finest and n >= 256 else 2.125)
+        total += part * count
+        n, part, finest = n // 2, part / 8, False
+    total += part * 6    # 16^3 (or 8^3): one launch, each array once
+    while n > 4:
+        n, part = n // 2, part / 8
+        total += part * 3
+    return total
+
+
+# four one-pass sweeps and three face arrays on every grid: (4 x 6 + 5.125 + 2.125) 8/7
 VCYCLE_SCALARS_FACE = 31.25 * 8 / 7
 
 METRIC = "grid-pts/s per V-cycle + time-to-1e-10 residual (FP64 vs mixed), % HBM peak"
@@ -180,8 +191,9 @@ def main():
 
     # dominant kernel: the finest-grid smoother, timed on the stream it runs on.  On grids
     # of 128^3 and up it sweeps two at a time: four sweeps are two launches p -> t -> p, as
-    # in a cycle; below, two sweeps are two one-pass launches.
+    # in a cycle; below, two sweeps are two launches (two pairs of them up to 16^3).
     two64 = N >= 128
+    faces64 = N == 128 or N <= 32   # their sweeps read the stored faces
     fz = torch.zeros_like(f)
     ps = torch.zeros_like(f)
     sweeps = 4 if two64 else 2
@@ -195,9 +207,10 @@ def main():
     b.record()
     torch.cuda.synchronize()
     launch_ms = a.elapsed_time(b) / (2 * reps)
-    # algorithmic bytes of one launch on the finest grid of a hierarchy built from rho: p,
-    # f and the density form of the coefficients read, p written (for two sweeps or one)
-    sweep_bytes = n * 8 * 4
+    # algorithmic bytes of one launch on the finest grid of a hierarchy built from rho: p, f
+    # and the coefficients (the density, or three face arrays) read, p written (for two
+    # sweeps or one)
+    sweep_bytes = n * 8 * (6 if faces64 else 4)
     achieved = sweep_bytes / (launch_ms * 1e-3) / 1e9
     del fz, ps
     r64.pop("mg"), r64.pop("p")
@@ -263,7 +276,6 @@ def main():
         legs["differentiation"] = differentiation_leg(args)
         legs["rk2_projection"] = rk2_leg(256, args)
     traffic = recorded_traffic(inp.name, N)
-    scalars = VCYCLE_SCALARS_TWO if N >= 256 else VCYCLE_SCALARS_128 if N >= 128 else VCYCLE_SCALARS_ONE
     out = {
         "metric": METRIC,
         "value_definition": f"grid points x V-cycles / time of the FP64 projection (setup from rho + solve to "
@@ -286,17 +298,18 @@ def main():
         "peak_memory_bytes": {"fp64": peak64, "mixed": peakmx},
         "vcycle_ms": {"fp64": vc64, "fp32": vc32},
         "vcycle_pts_per_s": {"fp64": n / (vc64 * 1e-3), "fp32": n / (vc32 * 1e-3)},
-        # algorithmic scalars per finest cell per V(2,2) cycle of the design that runs
-        # (density form on the finest grid), and against the face-array count
-        "vcycle_roofline_frac": {"fp64": scalars * 8 * n / (vc64 * 1e-3) / (HBM_PEAK_GBS * 1e9),
-                                 "fp32": scalars * 4 * n / (vc32 * 1e-3) / (HBM_PEAK_GBS * 1e9),
+        # algorithmic scalars per finest cell per V(2,2) cycle of the design that runs, and
+        # against the face-array count
+        "vcycle_roofline_frac": {"fp64": vcycle_scalars(N, True) * 8 * n / (vc64 * 1e-3) / (HBM_PEAK_GBS * 1e9),
+                                 "fp32": vcycle_scalars(N, False) * 4 * n / (vc32 * 1e-3) / (HBM_PEAK_GBS * 1e9),
                                  "fp64_face_array_count": VCYCLE_SCALARS_FACE * 8 * n / (vc64 * 1e-3)
                                  / (HBM_PEAK_GBS * 1e9),
                                  "fp32_face_array_count": VCYCLE_SCALARS_FACE * 4 * n / (vc32 * 1e-3)
                                  / (HBM_PEAK_GBS * 1e9)},
         "roofline": {"bound": "hbm",
-                     "kernel": ("rbgs_fused2 (finest grid, FP64 density form, two red-black sweeps per launch)"
-                                if two64 else "rbgs_fused (finest grid, FP64 density form, one red-black sweep)"),
+                     "kernel": (("rbgs_fused2" if two64 else "rbgs_box" if N >= 32 else "rbgs_half")
+                                + f" (finest grid, FP64 {'face arrays' if faces64 else 'density form'}, "
+                                + ("two red-black sweeps per launch)" if two64 else "one red-black sweep)")),
                      "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "launch_ms": launch_ms, "bytes_per_launch": sweep_bytes},
