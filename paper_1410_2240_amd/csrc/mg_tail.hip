@@ -826,8 +826,9 @@ __global__ __launch_bounds__(kTailThreads) void k_coarse_setup(CoarseSetup a) {
 #pragma unroll
   for (int c = 0; c < 8; ++c) a.pinv[lane * 64 + wave * 8 + c] = zz[c] - m[c];
   // The host takes the ticket for the end of the setup, and may go on from another stream:
-  // each wave waits here until its stores can be seen (the barrier alone orders LDS only).
-  __threadfence_system();
+  // each wave waits here until its stores are in the L2 (the barrier alone orders LDS only),
+  // which the fence before the ticket writes back.  A fence in every wave costs 2 us.
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (tid == 0) {
 #pragma unroll
