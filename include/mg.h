@@ -34,7 +34,7 @@
  * context.  A context is not thread-safe; distinct contexts are independent.
  *
  * Streams.  All device work is ordered on the HIP stream given to mg_setup (or set
- * later with mg_set_stream); NULL means the default stream.  mg_setup and
+ * later with mg_set_stream); NULL and hipStreamLegacy mean the default stream.  mg_setup and
  * mg_setup_from_rho return when their device work is done, so that later calls may run on
  * any stream.  mg_solve returns once it has the last residual; the passes that give p its
  * zero mean may then still be queued on the stream.  A context

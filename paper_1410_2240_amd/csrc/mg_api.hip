@@ -802,10 +802,20 @@ extern "C" void mg_destroy(mg_ctx* ctx);
 
 namespace {
 
+// The caller's stream.  Event and device queries read through the special handle of the
+// default stream, as launches do not: it is taken as NULL, which names the same stream.
+hipStream_t stream_of(void* s) { return s == hipStreamLegacy ? nullptr : static_cast<hipStream_t>(s); }
+
+// A stream with a device of its own: the others stand for one of the current device.
+bool stream_has_device(hipStream_t s) { return s && s != hipStreamPerThread; }
+
 int device_of(hipStream_t s) {
   int device = 0;
   hipDevice_t d = 0;
-  if (s && hipStreamGetDevice(s, &d) == hipSuccess) return static_cast<int>(d);
+  if (stream_has_device(s)) {
+    if (hipStreamGetDevice(s, &d) == hipSuccess) return static_cast<int>(d);
+    (void)hipGetLastError();   // (a launch would report it)
+  }
   (void)hipGetDevice(&device);
   return device;
 }
@@ -898,7 +908,7 @@ int setup_impl(mg_ctx** out, void* workspace, size_t ws_bytes, const double* bx,
   c->plan = plan;
   c->flags = flags;
   c->L = plan.levels;
-  c->stream = static_cast<hipStream_t>(hip_stream);
+  c->stream = stream_of(hip_stream);
   c->device = device_of(c->stream);
   c->ws = static_cast<unsigned char*>(workspace);
   for (int l = 0; l < c->L; ++l) {
@@ -1328,7 +1338,7 @@ int mg_setup_from_rho(mg_ctx** out, void* workspace, size_t ws_bytes, const doub
 
 int mg_set_stream(mg_ctx* ctx, void* hip_stream) {
   if (!ctx) return fail(MG_EINVAL, "null context");
-  ctx->stream = static_cast<hipStream_t>(hip_stream);
+  ctx->stream = stream_of(hip_stream);
   return MG_OK;
 }
 
@@ -1396,7 +1406,7 @@ int mg_solve_static(mg_ctx* ctx, const double* f, double* p, int batch, double t
                 ctx->lv[0].n, ctx->flags, lp.total, kStaticScratchBytes);
   int device = 0;
   MG_HIP(hipGetDevice(&device));
-  if (ctx->stream) {
+  if (stream_has_device(ctx->stream)) {
     hipDevice_t sdev = 0;
     MG_HIP(hipStreamGetDevice(ctx->stream, &sdev));
     if (static_cast<int>(sdev) != device)
@@ -1519,7 +1529,7 @@ int mg_add_lanes(mg_ctx* ctx, void* workspace, size_t ws_bytes, int lanes) {
     return fail(MG_EWORKSPACE, "workspace %zu bytes < %d x %zu needed", ws_bytes, lanes, lp.total);
   int device = 0;
   MG_HIP(hipGetDevice(&device));
-  if (ctx->stream) {   // the lanes' streams must live on the device of the context's stream
+  if (stream_has_device(ctx->stream)) {   // the lanes' streams must live on the device of the context's stream
     hipDevice_t sdev = 0;
     MG_HIP(hipStreamGetDevice(ctx->stream, &sdev));
     if (static_cast<int>(sdev) != device)

@@ -103,3 +103,34 @@ def test_destroy_waits(changed):
         end(ctx)
         assert event.query() == done
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("handle", [None, 1, 2], ids=["null", "legacy", "per_thread"])
+def test_special_stream_handles(handle):
+    """The handles that name the default and the per-thread stream: setup, solves (one item,
+    static scratch, a batch on lanes) and destruction, the bits of the null stream."""
+    import ctypes
+    from paper_1410_2240_amd import MG, _lib
+    lib = _lib.load()
+    N = 32
+    inp = fields.make("c2", N)
+    rho, mask, f = dev(inp.rho), dev(inp.mask), dev(fields.batch_rhs(inp.mask, 3))
+    want = MG.from_rho(rho, mask).solve(f, tol=1e-9)[0]
+    ptr = lambda t: ctypes.c_void_p(t.data_ptr())
+    empty = lambda n: torch.empty(n, dtype=torch.uint8, device="cuda")
+    size, per = lib.mg_workspace_size(_lib.dims3(N), 0), lib.mg_lane_workspace_size(_lib.dims3(N), 0)
+    ws, lane_ws = empty(size), empty(2 * per)
+    p = [torch.zeros_like(f) for _ in range(3)]
+    torch.cuda.synchronize()
+    print(f"stream handle {handle}", flush=True)
+    ctx = ctypes.c_void_p()
+    assert lib.mg_setup_from_rho(ctypes.byref(ctx), ptr(ws), size, ptr(rho), ptr(mask), _lib.dims3(N), 1.0 / N, 0,
+                                 ctypes.c_void_p(handle)) == 0, _lib.last_error()
+    solve = lambda entry, x: entry(ctx, ptr(f), ptr(x), 3, 1e-9, 100, None, None, None)
+    assert solve(lib.mg_solve, p[0]) == 0, _lib.last_error()
+    assert solve(lib.mg_solve_static, p[1]) == 0, _lib.last_error()
+    assert lib.mg_add_lanes(ctx, ptr(lane_ws), 2 * per, 2) == 0, _lib.last_error()
+    assert lib.mg_set_stream(ctx, ctypes.c_void_p(handle)) == 0
+    assert solve(lib.mg_solve, p[2]) == 0, _lib.last_error()
+    lib.mg_destroy(ctx)
+    assert all(torch.equal(x, want) for x in p)
