@@ -38,8 +38,8 @@ def test_a_setup_is_done_when_it_returns(N, mixed):
 
 
 def pending(stream):
-    """Work of some 20 ms on the stream, and an event after it."""
-    torch.cuda._sleep(40_000_000)
+    """Work of some 40 ms on the stream, and an event after it."""
+    torch.cuda._sleep(100_000_000)
     return stream.record_event()
 
 
